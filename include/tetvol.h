@@ -99,22 +99,21 @@ typedef struct {
   int32_t max_bounces;        /* real collisions per path, >= 1 */
   int32_t transmittance;      /* light: 0 analytic, 1 ratio tracking, 2 delta tracking */
   int64_t max_steps_per_path; /* exit evaluations per path (all walks); default 2^31 - 1.  At that value
-                                 (and above), on tet grids without a density model, with analytic light
-                                 transmittance, the light rays of a render's passes are queued, sorted by
-                                 where they start (column of the grid along the light, then depth) and
-                                 walked together after each pass (a light walk then runs on its own,
-                                 bounded by the tet count; the estimate is the same unless a path takes
-                                 more than 2^31 - 1 steps); their terms reach the pixels apart from the
-                                 rest of their samples (FP32 sums in another order).  Grids with extra
-                                 channels and the radiance cache's image paths queue theirs too; its
-                                 training paths, batches and tet_render_noalloc walk their own */
+                                 (and above) the light rays of a render's passes are queued and walked
+                                 together after each pass (a light walk then runs on its own, bounded by
+                                 the tet count; the estimate is the same unless a path takes more than
+                                 2^31 - 1 steps), in single renders sorted by where they start (column of
+                                 the grid along the light, then depth); their terms reach the pixels apart
+                                 from the rest of their samples (FP32 sums in another order).  A full
+                                 queue leaves the rest to the tracing lanes */
   int32_t sample_offset;      /* render samples [offset, offset + spp) */
-  int32_t samples_per_item;   /* samples one lane takes at a time (0 = all of a pixel) */
+  int32_t samples_per_item;   /* >= 0; checked only: every sample is scheduled by itself */
   int32_t block_size;         /* threads per block: 64, 128, 192 or 256 (0 = default) */
   int32_t blocks_per_cu;      /* persistent blocks per compute unit (0 = default) */
-  int32_t waves_per_simd;     /* register budget of the tracing kernel: 4, 5, 6 or 8 waves (0 = default 5) */
+  int32_t waves_per_simd;     /* occupancy target of the tracing kernel: 4, 5, 6 or 8 waves (0 = default 5; on
+                                 tet grids 6 and 8 mean 5, what the on-chip memory of a CU allows) */
   int32_t record_layout;      /* tet records walked: 32 (compact), 48, or 0 = compact when the grid has them */
-  int32_t batch_items;        /* work items a wave takes at a time (0 = default 64; batches always take 64) */
+  int32_t batch_items;        /* paths a wave takes at a time, at most (0 = default 64; batches always take 64) */
   int32_t event_wait;         /* lanes of a wave that wait for an event before events run (0 = default: 32;
                                  48 when collecting training paths) */
   const tet_nrc* nrc;         /* radiance cache: NULL = plain estimator; else paths stop at the cache's
@@ -237,17 +236,16 @@ int tet_render(const tet_grid* grid, const tet_camera* camera, const tet_medium*
 /* tet_render for callers that cannot allocate device memory: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * The same render (same kernels, same image up to FP32 summation order),
- * with its scratch -- per-pass entry records and counters -- in a fixed
- * device array of 64 MiB + 256 bytes that the library holds on each device
- * it runs on until the process ends, instead of memory it allocates; the
- * call makes
- * no hipMalloc or hipFree and launches on the stream without waiting (the
+ * with its scratch -- per-pass entry records, their lists, queued light rays
+ * and counters -- in a fixed device array of 73 MiB that the library holds
+ * on each device it runs on until the process ends, instead of memory it
+ * allocates; the call makes no hipMalloc or hipFree and launches on the stream without waiting (the
  * image is complete once the stream is).  Limits: a tet grid built on the
  * current device, no radiance cache (opts->nrc NULL), out_rgb on the
  * device; one sample of every pixel must fit the array (2^21 entry
  * records: images of up to 2^21 pixels once rounded up to 8 x 8 tiles, e.g.
- * 2048 x 1024), else TET_ERR_CAPACITY; a frame takes ceil(spp / floor(2^21
- * / tiled pixels)) passes.  Every call on a device shares its array: calls that
+ * 2048 x 1024), else TET_ERR_CAPACITY; a frame takes as many passes as its
+ * samples and a light ray for each need (about 2^20 samples a pass).  Every call on a device shares its array: calls that
  * overlap on one device race (serialise them, e.g. on one stream). */
 int tet_render_noalloc(const tet_grid* grid, const tet_camera* camera, const tet_medium* medium,
                        const tet_light* light, int32_t spp, uint64_t seed, const tet_render_opts* opts,

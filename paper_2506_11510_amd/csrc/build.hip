@@ -1506,8 +1506,9 @@ __global__ __launch_bounds__(kRecordsBlock) void k_records(int64_t n, const uint
 #pragma unroll
       for (int k = 0; k < 4; k++) {
         if (k == f) {
-          offs[k] = ldexpf((float)off, -kLatBits);
-          ioff[k] = (int32_t)off;
+          const int64_t pc = (code & 1) ? -off : off;  // along +dir_N
+          offs[k] = ldexpf((float)pc, -kLatBits);
+          ioff[k] = (int32_t)pc;
         }
       }
     }

@@ -271,14 +271,15 @@ __global__ void k_export_faces(int64_t n, const TetRec* __restrict__ rec, const 
                            ((int32_t)(r.w[2] << 4)) >> 9};
     for (int f = 0; f < 4; f++) {
       if (codes) codes[4 * i + f] = (uint8_t)code_of32(r.w[4 + f]);
-      if (offs) offs[4 * i + f] = io[f];
+      if (offs) offs[4 * i + f] = (r.w[4 + f] >> 31) ? -io[f] : io[f];  // stored along +dir_N
       if (links) links[4 * i + f] = r.w[4 + f] & kLink27Boundary;
     }
   } else {
     const TetRec r = rec[i];
     for (int f = 0; f < 4; f++) {
       if (codes) codes[4 * i + f] = (uint8_t)((r.codes >> (8 * f)) & 0xFFu);
-      if (offs) offs[4 * i + f] = (int32_t)(r.off[f] * 0x1p20f);  // n_f . v * 2^-20, exact
+      const int32_t pc = (int32_t)(r.off[f] * 0x1p20f);  // dir_N . v * 2^-20, exact
+      if (offs) offs[4 * i + f] = ((r.codes >> (8 * f)) & 1u) ? -pc : pc;
       if (links) links[4 * i + f] = r.nbr[f];
     }
   }

@@ -20,7 +20,7 @@ constexpr int kMaxLevels = 13;          // pyramid levels for n <= 4096
 // Traversal record of one tet: everything a walk step reads, 48 bytes,
 // fetched as three 16-byte loads.
 struct alignas(16) TetRec {
-  float off[4];      // face plane offsets n_f . v in world units
+  float off[4];      // face plane constants dir_N . v in world units
   uint32_t nbr[4];   // (index << 2) | back face, or kBoundary
   uint32_t codes;    // byte f: orientation code 2 N + s of face f (outward normal = (-1)^s dir_N)
   float sigma;       // extinction
@@ -32,7 +32,7 @@ static_assert(sizeof(TetRec) == 48, "record size");
 // Compact traversal record, 32 bytes (two 16-byte loads, never straddling a
 // 64-byte sector); the same values as TetRec for grids of < 2^27 tets with
 // tight majorants:
-//   w[0..2]: the 4 plane offsets n_f . v in lattice units as 23-bit two's
+//   w[0..2]: the 4 plane constants dir_N . v in lattice units as 23-bit two's
 //            complement integers, packed little-endian at bits 0, 23, 46, 69
 //            (world offset = offset * 2^-20, exact in FP32);
 //   w[3]:    extinction (FP32 bits);

@@ -2,30 +2,35 @@
 // (paper, "Volumetric Path Tracing": Algorithm 1 and "Path Tracing within
 // Tetrahedral Grids").
 //
-// Two kernels per pass of samples:
-//   k_raygen  -- one thread per (pixel, sample): camera ray, entry into the
-//                grid, point location and the first free-flight depth,
-//                written as a 32-byte entry record (coherent, no divergence
-//                beyond the point-location search);
-//   k_render  -- persistent: every lane runs a small state machine over its
-//                own paths (fetch work -> load an entry -> walk steps of the
-//                main path -> walk steps of the light (shadow) ray ->
-//                scatter).  Each loop iteration advances every walking lane
-//                by one cell, so lanes whose paths differ in length stay
-//                busy; idle lanes take new work items from a device counter
-//                with one atomic per wave (ballot + popcount).  All rare
-//                events (collision, light estimate and phase sampling,
-//                escape, end of sample, new work) sit in one section the
-//                wave enters only when some lane needs it; the common
-//                iteration is a bare walk step.
+// Three kernels per pass of samples:
+//   k_first   -- one thread per (pixel, sample): camera ray, entry into the
+//                grid, point location, and the walk of the camera segment up
+//                to its first real collision or its escape.  The samples of
+//                a pixel are neighbouring lanes, so a wave's lanes walk the
+//                same tets side by side and leave together.  Escaped samples
+//                are done; the others leave their collision in their
+//                32-byte entry record and their index in a list;
+//   k_render  -- persistent, over the listed paths only: every lane runs a
+//                small state machine over its own paths (fetch work -> light
+//                estimate -> scatter -> walk steps of the scattered segment,
+//                and of the light (shadow) ray where it is not queued).  Each
+//                loop iteration advances every walking lane by one cell, so
+//                lanes whose paths differ in length stay busy; idle lanes
+//                take new paths from a device counter with one atomic per
+//                wave (ballot + popcount).  All rare events (collision, light
+//                estimate and phase sampling, escape, end of path, new work)
+//                sit in one section the wave enters only when some lane
+//                needs it; the common iteration is a bare walk step;
+//   k_resolve -- sums the samples' radiance per pixel, in sample order.
 //
-// One walk step reads one 48-byte tet record (face plane offsets, face
-// orientation codes, 4 neighbour links, extinction, majorant) and evaluates
-// only faces whose outward normal faces the ray (n.d > 0, at most 3).  The
-// dot products of the segment's origin and direction with the 9 possible
-// face directions are computed once per segment into a per-lane LDS table,
-// so a face costs one LDS read pair and a sign flip; every value is rounded
-// exactly as the direct FP32 dot product would be.  The free flight is delta tracking against the
+// One walk step reads one 48- or 32-byte tet record (face plane constants, face
+// orientation codes, 4 neighbour links, extinction) and leaves by a face
+// whose outward normal faces the ray (n.d > 0, at most 3).  The dot products
+// of the segment's origin and direction with the 9 possible face directions,
+// and the latter's reciprocals, are computed once per segment into a per-lane
+// LDS table, so a face costs one LDS read pair, a subtraction and a product
+// (exit_face); every dot product is rounded exactly as the direct FP32 one
+// would be.  The free flight is delta tracking against the
 // per-tet majorant with an optical depth carried across cells; real
 // collisions scatter by Henyey-Greenstein after a next-event estimate of the
 // directional light (transmittance by walking the light ray to the grid
@@ -49,20 +54,20 @@
 
 namespace tv {
 
-// Entry of one camera sample into the grid (32 bytes): entry point, tet
-// (kMiss if the ray misses the grid), direction, first free-flight depth.
+// Entry record of one camera sample (32 bytes).  From k_first: the first real
+// collision (point, tet, direction of the segment that reached it, walk
+// steps so far), or, with cell = kDone, the finished sample's radiance.
+// k_render replaces the collisions by the radiance their paths gathered.
 struct alignas(16) RayEntry {
   float px, py, pz;
   uint32_t cell;
   float dx, dy, dz;
-  float tau;
+  uint32_t steps;
 };
-constexpr uint32_t kMiss = 0xFFFFFFFFu;
+constexpr uint32_t kDone = 0xFFFFFFFFu;
 
-// One scene of a batch (several grids rendered by one launch sequence).
-// Work items and entry records of all scenes are concatenated; a scene's
-// items start at a multiple of 64, so the 64-item batches waves take never
-// straddle two scenes.
+// One scene of a batch (several grids rendered by one launch sequence):
+// the scenes' entry records are concatenated.
 // Extra per-tet data a scene may carry: channels (null = absent) with the
 // emitted radiance per unit temperature, and the density model inside the
 // tets (0 = constant; 1 linear coefficients; 2 voxel lookup in an n^3
@@ -86,9 +91,6 @@ struct SceneDesc {
   int32_t spp, tiles_x;
   uint64_t seed;
   uint32_t s0;       // first sample index
-  uint32_t items;    // slots x spp (the scene's work items, one sample each)
-  uint32_t item0;    // first work item (multiple of 64)
-  uint32_t pad0;
   uint64_t entry0;   // first entry record
   uint64_t pix0;     // first pixel in the concatenated images
   const void* rec;   // traversal records (TetRec32 or TetRec)
@@ -113,14 +115,35 @@ __device__ inline int scene_search(int n, uint64_t v, F key) {
 }
 
 // A light ray whose walk is deferred: its origin (the real collision), the
-// collision's tet, the light estimate's weight per channel (throughput after
-// the albedo x phase function x irradiance) and the pixel it adds to.
+// collision's tet, the light estimate's weight before the irradiance
+// (throughput after the albedo x phase function), what it adds to, and its
+// random stream (ratio and delta tracking).
 struct alignas(16) LightRec {
   float x, y, z;
-  uint32_t cell;
-  float w0, w1, w2;
-  uint32_t pix;
+  uint32_t cell;  // kDone: an unused record (the end of a wave's last chunk)
+  float bp;
+  uint32_t to;      // pixel; entry record (batches); light term (training paths)
+  uint32_t sample;
+  uint32_t bounce;  // | kToTerm for training paths
 };
+constexpr uint32_t kToTerm = 0x80000000u;
+
+// The launches' counters in device memory (kHeadBytes at the start of the
+// scratch), each on a 128-byte line of its own: atomics on one line serialise.
+// Lists 0..7 are the eight contiguous bands of the entry records (one per
+// XCD), list 8 the radiance cache's training paths.
+constexpr int kLists = 9, kTrainList = 8;
+constexpr int kLine = 32;                              // 32-bit words per line
+constexpr int kTakenAt = 0;                            // listed paths taken so far, per list
+constexpr int kCountAt = kLists * kLine;               // listed paths, per list
+constexpr int kQueryAt = 2 * kLists * kLine;           // radiance-cache queries of the pass
+constexpr int kChunkAt = (2 * kLists + 1) * kLine;     // light-ray queue chunks taken in the pass
+constexpr int kPassWords = (2 * kLists + 2) * kLine;   // the words above are zeroed before each pass
+// Statistics: blocks add to the slot of their index, the host sums the slots
+// (262 K blocks adding to one address took longer than their walks).
+constexpr int kStatSlots = 64;
+constexpr int kStatAt = (kPassWords + 63) / 64 * 64;
+constexpr size_t kHeadBytes = (size_t)(kStatAt + kStatSlots * kLine) * 4;
 
 struct RenderArgs {
   Frame fr;
@@ -129,21 +152,24 @@ struct RenderArgs {
   int32_t spp;          // samples per pixel of the whole render (divisor)
   int32_t pass_start;   // first sample index of this pass
   int32_t pass_spp;     // samples of this pass
-  int32_t per_item, items_per_pixel, max_bounces, transmittance;
+  int32_t max_bounces, transmittance;
   uint32_t max_steps;
   uint64_t seed;
-  uint32_t items, slots;
-  uint32_t range_size;  // work items per XCD range (8 contiguous ranges)
-  uint32_t batch;       // work items a wave takes per atomic
+  uint32_t slots;
+  uint32_t batch;       // paths a wave takes per atomic
   int32_t event_wait;   // lanes waiting for an event before the wave handles events
   int32_t tiles_x;
-  const RayEntry* entries;
+  RayEntry* entries;
   float* out;
-  uint32_t* counter;
-  unsigned long long* stats;
-  int accumulate;
+  uint32_t* head;       // counters and statistics
+  // listed paths: list b starts at list + b * band_size, the training
+  // paths' (radiance cache, with an image) at list + train_list0
+  uint32_t* list;
+  uint32_t band_size;
+  uint32_t chunk_blocks;  // blocks of neighbouring entries dealt to one list at a time
+  uint32_t train_list0;
   // radiance cache
-  int32_t train;         // work items are training paths (pixel from train_pixel, sample = item)
+  int32_t train;         // the entries are training paths (pixel from train_pixel, sample = entry)
   uint32_t npix;         // width * height
   int32_t truncate;      // real vertex where a path queries the cache
   int32_t rec_vertices;  // vertices recorded per training path
@@ -153,7 +179,8 @@ struct RenderArgs {
   float4* vrec;          // training-path vertex records
   float4* path_l;        // training-path radiance and vertex count
   const tet_nrc* nrc;    // host handle (the query pass), never read on the device
-  uint32_t train_items;  // cache mode 1: the first items are training paths (first pass only)
+  uint32_t train_items;  // cache mode 1: training paths traced with the image (first pass only)
+  uint32_t train_blocks; // blocks of k_first that trace them
   uint32_t train_ent0;   // their entry records follow the image's
   uint64_t train_seed;   // their Philox key
   // batch of scenes
@@ -161,15 +188,21 @@ struct RenderArgs {
   int32_t nscenes;
   uint64_t total_entries;
   ExtArgs ex;  // channels and density model of a single-scene render
-  // deferred light rays (defer != 0): block b of the tracing kernel queues
-  // its light rays at lq + b * lq_region (lq_count[b] of them), walked after
-  // the pass in the order of their start tets
+  // deferred light rays (defer != 0): a wave of the tracing kernel takes
+  // chunks of lq_chunk records of the queue as it fills them (lq_chunks in
+  // all); they are walked after the pass in the order of where they start
   LightRec* lq;
-  uint32_t* lq_count;
-  uint32_t lq_cap;
-  uint32_t lq_region;
+  uint32_t lq_chunk, lq_chunks;
+  // training paths with deferred light rays: the light (and emission) each
+  // vertex gathers, terms[2 (path max_bounces + vertex)] (and + 1), summed by
+  // k_gather_terms in path order
+  float4* terms;
   int32_t defer;
 };
+
+__device__ inline unsigned long long* stat_slot(const RenderArgs& A) {
+  return (unsigned long long*)(A.head + kStatAt + (blockIdx.x & (kStatSlots - 1)) * kLine);
+}
 
 // Extinction at o + t d inside tet `cell` under the grid's density model:
 // linear ((c0 + gx x) + gy y) + gz z, or the scale times the voxel
@@ -274,8 +307,156 @@ __device__ inline int64_t locate_point(const uint64_t* __restrict__ keys, const 
   return search_keys_idx(keys, kidx, kbits, h << (60 - dmax));
 }
 
+// Per-lane LDS table of a segment with direction d from origin o, for the 9
+// face directions dir_N: [0, 9) the reciprocals of dir_N . d, [9, 18)
+// dir_N . o times kOriginScale, [18, 27) dir_N . d; each dot product rounded
+// as (n.x a.x + n.y a.y) + n.z a.z would be (its zero terms are exact).  The
+// reciprocal is the correctly rounded one; NaN where dir_N . d = 0 (such a
+// face is never crossed), and 0 for all 9 when a dot product is too small
+// for exit_face's bounds (|dir_N . d| < 2^-40, or NaN, or d = 0), which makes every
+// step of the segment take its general path.
+// Entry k of the block's lane i is at k * kTabRow + i: a lane's reads stay in
+// its own bank whichever entry it reads.
+constexpr int kTabRow = 256;  // lanes (the largest block)
+constexpr int kTabDot = 9, kTabDen = 18, kTabRows = 27;
+
+struct SegDirs {
+  float r[9], d[9];
+};
+
+__host__ __device__ inline void seg_dirs(float x, float y, float z, SegDirs& s) {
+  const float d[9] = {x, y, z, x + y, x - y, x + z, x - z, y + z, y - z};
+  bool tiny = x == 0.0f && y == 0.0f && z == 0.0f;
+  for (int N = 0; N < 9; N++) tiny = tiny || (d[N] != 0.0f && !(d[N] <= -0x1p-40f || d[N] >= 0x1p-40f));
+  for (int N = 0; N < 9; N++) {
+    s.d[N] = d[N];
+    s.r[N] = tiny ? 0.0f : (d[N] == 0.0f ? __builtin_nanf("") : 1.0f / d[N]);
+  }
+}
+
+// The origin's 9 entries, at tab[N * kTabRow].
+__device__ inline void set_origin(float* tab, float3 o, float oscale) {
+  o = make_float3(o.x * oscale, o.y * oscale, o.z * oscale);
+  const float v[9] = {o.x, o.y, o.z, o.x + o.y, o.x - o.y, o.x + o.z, o.x - o.z, o.y + o.z, o.y - o.z};
+#pragma unroll
+  for (int N = 0; N < 9; N++) tab[N * kTabRow] = v[N];
+}
+
+template <class Med>
+__device__ inline void set_segment(float* tab, float3 o, float3 d) {
+  if constexpr (Med::kTabled) {
+    SegDirs s;
+    seg_dirs(d.x, d.y, d.z, s);
+#pragma unroll
+    for (int N = 0; N < 9; N++) {
+      tab[N * kTabRow] = s.r[N];
+      tab[(kTabDen + N) * kTabRow] = s.d[N];
+    }
+    set_origin(tab + kTabDot * kTabRow, o, Med::kOriginScale);
+  }
+}
+
+__device__ inline uint64_t ballot64(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+__device__ inline bool lane_of(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Bits 27..30 as one bit-field extract: left to the compiler it becomes
+// shift, mask and add before an address add.
+__device__ inline uint32_t bits27_30(uint32_t x) {
+  uint32_t r;
+  asm("v_bfe_u32 %0, %1, 27, 4" : "=v"(r) : "v"(x));
+  return r;
+}
+
+// Exit of a tet along a segment: faces whose outward normal n has n . d > 0
+// are candidates; the exit face has the smallest exact quotient num / den of
+// num = offset - n . o and den = n . d (both FP32), the lowest face on ties;
+// bt = that quotient correctly rounded.  c[f] is face f's plane constant along
+// +dir_N, dn[f] its N, the sign bit of w[f] says that n = -dir_N (num and den
+// then both change sign, the quotient does not).  False: no candidate.
+//
+// A wave spends its time on VALU issue here, so the common path avoids FP64 and
+// division: q = num * RN(1 / den) is within 2^-22 (relative) of the exact
+// quotient, so a candidate whose q is the only one up to min q (1 + 2^-20)
+// is the exact minimum.  From q, two FMA corrections with the exact
+// remainder give the correctly rounded quotient (the first leaves it within
+// an ulp, the second, from a correctly rounded reciprocal, rounds it
+// correctly; q > 2^-40 and |den| >= 2^-40 keep the remainders exact).  Near
+// ties, smaller or negative q, tiny dens (every candidate's q is then 0) and
+// no candidate at all (at least two q are then infinite: at most two of a
+// tet's four face normals can be normal to a direction) go the general way: exact FP64 cross products and an IEEE division.
+// NPAY: the payload of a face holds its N at bits 27..30.  SHARED: all lanes
+// of the block have one direction, whose entries are dirs[0, 9) (reciprocals)
+// and dirs[9, 18); tab then holds the origins' alone.  Against the FP64
+// cross products and division on every step: 92 -> 73 VALU instructions per
+// step of the light walk.
+template <bool NPAY, bool SHARED>
+__device__ inline bool exit_face(const float* tab, const float* dirs, const float (&c)[4], const uint32_t (&w)[4],
+                                 const uint32_t (&dn)[4], const uint32_t (&pay)[4], float& bt, uint32_t& bpay) {
+  float num[4], q[4], rd[4];
+#pragma unroll
+  for (int f = 0; f < 4; f++) {  // the four faces' table entries, all read before any is used
+    rd[f] = SHARED ? dirs[dn[f]] : tab[dn[f] * kTabRow];
+    num[f] = SHARED ? tab[dn[f] * kTabRow] : tab[(kTabDot + dn[f]) * kTabRow];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int f = 0; f < 4; f++) {
+    num[f] = c[f] - num[f];
+    const float x = num[f] * rd[f];
+    q[f] = (int32_t)(w[f] ^ __float_as_uint(rd[f])) < 0 ? INFINITY : x;
+  }
+  const float b = fminf(fminf(fminf(q[0], q[1]), q[2]), q[3]);
+  const float thr = fmaf(fabsf(b), 0x1p-20f, b);
+  // (lane masks in scalar registers: their logic costs no VALU issue)
+  const uint64_t m0 = ballot64(q[0] <= thr), m1 = ballot64(q[1] <= thr), m2 = ballot64(q[2] <= thr),
+                 m3 = ballot64(q[3] <= thr);
+  const uint64_t two = (m0 & m1) | (m2 & m3) | ((m0 | m1) & (m2 | m3));
+  const uint64_t fast = ballot64(b > 0x1p-40f) & ~two;
+  if (lane_of(fast)) {
+    float n = num[0];
+    bpay = pay[0];
+    uint32_t bn = dn[0];
+    n = lane_of(m1) ? num[1] : n;
+    n = lane_of(m2) ? num[2] : n;
+    n = lane_of(m3) ? num[3] : n;
+    bpay = lane_of(m1) ? pay[1] : bpay;
+    bpay = lane_of(m2) ? pay[2] : bpay;
+    bpay = lane_of(m3) ? pay[3] : bpay;
+    if constexpr (NPAY) {
+      bn = bits27_30(bpay);
+    } else {
+      bn = lane_of(m1) ? dn[1] : bn;
+      bn = lane_of(m2) ? dn[2] : bn;
+      bn = lane_of(m3) ? dn[3] : bn;
+    }
+    const float r = SHARED ? dirs[bn] : tab[bn * kTabRow], den = SHARED ? dirs[9 + bn] : tab[(kTabDen + bn) * kTabRow];
+    const float q1 = fmaf(fmaf(-b, den, n), r, b);
+    bt = fmaf(fmaf(-q1, den, n), r, q1);
+    return true;
+  }
+  bool any = false;
+  float bnum = 0.0f, bden = 1.0f;
+  bpay = 0;
+#pragma unroll
+  for (int f = 0; f < 4; f++) {
+    const uint32_t sg = w[f] & 0x80000000u;
+    const float td = SHARED ? dirs[9 + dn[f]] : tab[(kTabDen + dn[f]) * kTabRow];
+    const float den = __uint_as_float(__float_as_uint(td) ^ sg);
+    const float nf = __uint_as_float(__float_as_uint(num[f]) ^ sg);
+    const bool cand = den > 0.0f;
+    const bool better = cand && (!any || (double)nf * (double)bden < (double)bnum * (double)den);
+    bnum = better ? nf : bnum;
+    bden = better ? den : bden;
+    bpay = better ? pay[f] : bpay;
+    any = any || cand;
+  }
+  bt = bnum / bden;
+  return any;
+}
+
 struct TetMedium {
   static constexpr float kOriginScale = 1.0f;
+  static constexpr bool kTabled = true;  // steps read the segment's LDS table
+  static constexpr bool kTight = false;  // the majorant may exceed the extinction
   const TetRec* __restrict__ rec;
   const uint64_t* __restrict__ keys;
   int64_t n;
@@ -285,64 +466,42 @@ struct TetMedium {
   int kbits;
   __device__ inline int64_t locate(float3 p) const { return locate_point(keys, kidx, kbits, dmax, shapes, p); }
   __device__ inline float sigma_at(uint32_t cell) const { return rec[cell].sigma; }
-  // Exit of the tet along the segment whose direction-dot table is `tab`
-  // (tab[N] = dir_N . d, tab[9 + N] = dir_N . o) from t: faces with
-  // n.d > 0 are candidates; the exit face has the smallest exact quotient
-  // num / den (exact FP64 cross products, lowest face on ties); one FP32
-  // division gives the exit distance.  Branchless, so the whole record is
-  // loaded at once.
-  __device__ inline Step step(uint32_t cell, float3, float3, const float* tab, float t) const {
+  __device__ inline uint32_t most_cells() const { return (uint32_t)n; }  // a straight walk meets
+  // Exit of the tet along the segment whose table is `tab`, from t.
+  template <bool SHARED = false>
+  __device__ inline Step step(uint32_t cell, float3, float3, const float* tab, float t, const float* dirs = nullptr) const {
     const float4* q = (const float4*)(rec + cell);
     const float4 r0 = q[0], r1 = q[1], r2 = q[2];
     const uint32_t codes = __float_as_uint(r2.x);
-    const float off[4] = {r0.x, r0.y, r0.z, r0.w};
+    const float c[4] = {r0.x, r0.y, r0.z, r0.w};
     const uint32_t link[4] = {__float_as_uint(r1.x), __float_as_uint(r1.y), __float_as_uint(r1.z),
                               __float_as_uint(r1.w)};
-    bool any = false;
-    float bnum = 0.0f, bden = 1.0f;
-    uint32_t blink = kBoundary;
-    // the four faces' table entries, all read before any is used
-    float tden[4], tdot[4];
+    uint32_t w[4], dn[4];
 #pragma unroll
     for (int f = 0; f < 4; f++) {
-      const uint32_t c = (codes >> (8 * f)) & 0xFFu;
-      tden[f] = tab[c >> 1];
-      tdot[f] = tab[9 + (c >> 1)];
+      w[f] = codes << (31 - 8 * f);
+      dn[f] = (codes >> (8 * f + 1)) & 0x7Fu;
     }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int f = 0; f < 4; f++) {
-      uint32_t c = (codes >> (8 * f)) & 0xFFu;
-      uint32_t sg = c << 31;
-      float den = __uint_as_float(__float_as_uint(tden[f]) ^ sg);
-      float dot = __uint_as_float(__float_as_uint(tdot[f]) ^ sg);
-      float num = off[f] - dot;
-      bool cand = den > 0.0f;
-      bool better = cand && (!any || (double)num * (double)bden < (double)bnum * (double)den);
-      bnum = better ? num : bnum;
-      bden = better ? den : bden;
-      blink = better ? link[f] : blink;
-      any = any || cand;
-    }
+    float bt;
+    uint32_t blink;
     Step s;
-    float bt = bnum / bden;
+    s.ok = exit_face<false, SHARED>(tab, dirs, c, w, dn, link, bt, blink);
     s.sigma = r2.y;
     s.majorant = r2.z;
-    s.ok = any;
     s.te = bt > t ? bt : t;
-    s.next = (!any || blink == kBoundary) ? -1 : (int32_t)(blink >> 2);
+    s.next = (!s.ok || blink == kBoundary) ? -1 : (int32_t)(blink >> 2);
     return s;
   }
 };
 
 // Same walk on the compact 32-byte records (bitwise the same values).  The
 // LDS table holds origin dots scaled by 2^20 (exact), so the integer
-// offsets need no scaling: num * 2^20 = offset - dot * 2^20 exactly, the
-// quotient comparisons are scale-free, and one final multiply by 2^-20
-// (exact) gives the exit distance.  The running best starts at the
-// quotient 1/0 = +inf, which every candidate beats.
+// plane constants need no scaling: num * 2^20 = c - dot * 2^20 exactly, and
+// one final multiply by 2^-20 (exact) gives the exit distance.
 struct TetMedium32 {
   static constexpr float kOriginScale = 0x1p20f;  // origin dots stored times 2^20
+  static constexpr bool kTabled = true;
+  static constexpr bool kTight = true;            // the majorant is the extinction
   const TetRec32* __restrict__ rec;
   const uint64_t* __restrict__ keys;
   int64_t n;
@@ -352,70 +511,39 @@ struct TetMedium32 {
   int kbits;
   __device__ inline int64_t locate(float3 p) const { return locate_point(keys, kidx, kbits, dmax, shapes, p); }
   __device__ inline float sigma_at(uint32_t cell) const { return __uint_as_float(rec[cell].w[3]); }
-  __device__ inline Step step(uint32_t cell, float3, float3, const float* tab, float t) const {
+  __device__ inline uint32_t most_cells() const { return (uint32_t)n; }
+  template <bool SHARED = false>
+  __device__ inline Step step(uint32_t cell, float3, float3, const float* tab, float t, const float* dirs = nullptr) const {
     // byte offset in 32 bits (cell < 2^27): a uniform base takes the load's
     // scalar-base form
     const uint4* q = (const uint4*)((const char*)rec + (cell << 5));
     const uint4 a = q[0], b = q[1];
-    uint32_t o1 = (uint32_t)((((uint64_t)a.y << 32) | a.x) >> 23);
-    uint32_t o2 = (uint32_t)((((uint64_t)a.z << 32) | a.y) >> 14);
-    const int32_t ioff[4] = {((int32_t)(a.x << 9)) >> 9, ((int32_t)(o1 << 9)) >> 9, ((int32_t)(o2 << 9)) >> 9,
-                             ((int32_t)(a.z << 4)) >> 9};
+    const uint32_t o1 = (uint32_t)((((uint64_t)a.y << 32) | a.x) >> 23);
+    const uint32_t o2 = (uint32_t)((((uint64_t)a.z << 32) | a.y) >> 14);
+    const float c[4] = {(float)(((int32_t)(a.x << 9)) >> 9), (float)(((int32_t)(o1 << 9)) >> 9),
+                        (float)(((int32_t)(o2 << 9)) >> 9), (float)(((int32_t)(a.z << 4)) >> 9)};
     const uint32_t lw[4] = {b.x, b.y, b.z, b.w};
-    // the four faces' table entries, all read before any is used
-    float tden[4], tdot[4];
+    uint32_t dn[4];
 #pragma unroll
-    for (int f = 0; f < 4; f++) {
-      // direction index N (bits 27..30) as one bit-field extract: left to
-      // the compiler it becomes shift, mask and add before the address add
-      uint32_t dn;
-      asm("v_bfe_u32 %0, %1, 27, 4" : "=v"(dn) : "v"(lw[f]));
-      const float* e = tab + dn;
-      tden[f] = e[0];
-      tdot[f] = e[9];
-    }
-    __builtin_amdgcn_sched_barrier(0);  // keep the four reads ahead of their uses
-    float bnum, bden;
-    uint32_t bw;  // link word of the best face (all ones: none yet)
-    {  // face 0 against the start quotient 1/0: it wins exactly when it is a candidate
-      uint32_t sg = lw[0] & 0x80000000u;
-      float den = __uint_as_float(__float_as_uint(tden[0]) ^ sg);
-      float dot = __uint_as_float(__float_as_uint(tdot[0]) ^ sg);
-      float num = (float)ioff[0] - dot;
-      const bool cand = den > 0.0f;
-      bnum = cand ? num : 1.0f;
-      // -0 when there is no candidate: the same comparisons as +0 below (a
-      // candidate's 1 * den is > 0), and a plain select rather than a max
-      bden = cand ? den : -0.0f;
-      bw = cand ? lw[0] : 0xFFFFFFFFu;
-    }
-#pragma unroll
-    for (int f = 1; f < 4; f++) {
-      uint32_t sg = lw[f] & 0x80000000u;
-      float den = __uint_as_float(__float_as_uint(tden[f]) ^ sg);
-      float dot = __uint_as_float(__float_as_uint(tdot[f]) ^ sg);
-      float num = (float)ioff[f] - dot;
-      bool better = den > 0.0f && (double)num * (double)bden < (double)bnum * (double)den;
-      bnum = better ? num : bnum;
-      bden = better ? den : bden;
-      bw = better ? lw[f] : bw;
-    }
-    const uint32_t blink = bw & kLink27Boundary;
+    for (int f = 0; f < 4; f++) dn[f] = bits27_30(lw[f]);
+    float bt;
+    uint32_t bw;
     Step s;
-    bool any = bden > 0.0f;
-    float bt = (bnum / bden) * 0x1p-20f;
+    s.ok = exit_face<true, SHARED>(tab, dirs, c, lw, dn, lw, bt, bw);
+    const uint32_t blink = bw & kLink27Boundary;
+    bt = bt * 0x1p-20f;
     s.sigma = __uint_as_float(a.w);
     s.majorant = s.sigma;
-    s.ok = any;
     s.te = bt > t ? bt : t;
-    s.next = (!any || blink == kLink27Boundary) ? -1 : (int32_t)blink;
+    s.next = (!s.ok || blink == kLink27Boundary) ? -1 : (int32_t)blink;
     return s;
   }
 };
 
 // ---------------------------------------------------------------- voxel medium
 struct VoxelMedium {
-  static constexpr float kOriginScale = 1.0f;
+  static constexpr bool kTabled = false;
+  static constexpr bool kTight = true;
   const float* __restrict__ dens;
   int32_t n;
   float scale;
@@ -430,7 +558,9 @@ struct VoxelMedium {
     return idx[0] + n * (idx[1] + (int64_t)n * idx[2]);
   }
   __device__ inline float sigma_at(uint32_t cell) const { return scale * dens[cell]; }
-  __device__ inline Step step(uint32_t cell, float3 o, float3 d, const float*, float t) const {
+  __device__ inline uint32_t most_cells() const { return 3u * (uint32_t)n; }
+  template <bool SHARED = false>
+  __device__ inline Step step(uint32_t cell, float3 o, float3 d, const float*, float t, const float* = nullptr) const {
     int32_t idx[3] = {(int32_t)(cell % (uint32_t)n), (int32_t)((cell / (uint32_t)n) % (uint32_t)n),
                       (int32_t)(cell / ((uint32_t)n * (uint32_t)n))};
     const float oo[3] = {o.x, o.y, o.z}, dd[3] = {d.x, d.y, d.z};
@@ -507,140 +637,266 @@ __device__ inline bool enter_cube(float3 o, float3 d, float3& p) {
 }
 
 // ---------------------------------------------------------------- kernels
-// Camera ray of sample s of pixel (px, py), its entry into the grid, the
-// entry tet and the first free-flight depth.
+// Camera ray (direction d) of sample s of pixel (px, py), its entry p into
+// the grid and the entry tet (-1: it misses the grid).
 template <class Med>
-__device__ inline RayEntry camera_entry(const Frame& fr, uint64_t seed, const Med& med, int32_t px, int32_t py,
-                                        uint32_t pix, uint32_t s) {
+__device__ inline int64_t camera_entry(const Frame& fr, uint64_t seed, const Med& med, int32_t px, int32_t py,
+                                       uint32_t pix, uint32_t s, float3& p, float3& d) {
   uint2 u = uniform01x2(seed, pix, s, 0, kStreamCamera, 0);
   float u0 = u01(u.x), u1 = u01(u.y);
   float sx = ((2.0f * (((float)px + u0) / (float)fr.w)) - 1.0f) * fr.tan_x;
   float sy = (1.0f - 2.0f * (((float)py + u1) / (float)fr.h)) * fr.tan_y;
   float3 o = make_float3(fr.pos[0], fr.pos[1], fr.pos[2]);
-  float3 d = normalize3(make_float3((fr.f[0] + sx * fr.r[0]) + sy * fr.u[0], (fr.f[1] + sx * fr.r[1]) + sy * fr.u[1],
-                                    (fr.f[2] + sx * fr.r[2]) + sy * fr.u[2]));
-  float3 p = o;
-  int64_t c = -1;
-  if (enter_cube(o, d, p)) c = med.locate(p);
-  RayEntry r;
-  r.px = p.x;
-  r.py = p.y;
-  r.pz = p.z;
-  r.cell = c < 0 ? kMiss : (uint32_t)c;
-  r.dx = d.x;
-  r.dy = d.y;
-  r.dz = d.z;
-  r.tau = c < 0 ? 0.0f : exp_tau(uniform01(seed, pix, s, 0, kStreamFlight, 0));
-  return r;
+  d = normalize3(make_float3((fr.f[0] + sx * fr.r[0]) + sy * fr.u[0], (fr.f[1] + sx * fr.r[1]) + sy * fr.u[1],
+                             (fr.f[2] + sx * fr.r[2]) + sy * fr.u[2]));
+  p = o;
+  return enter_cube(o, d, p) ? med.locate(p) : -1;
 }
 
-__device__ inline RayEntry miss_entry() {
-  RayEntry z;
-  memset(&z, 0, sizeof(z));
-  z.cell = kMiss;
-  return z;
-}
-
-// Entry records of every (pixel, sample) of a batch of scenes.
-template <class Med>
-__global__ __launch_bounds__(256) void k_raygen_batch(RenderArgs A, Med med, RayEntry* __restrict__ entries) {
-  uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= A.total_entries) return;
-  const int k = scene_search(A.nscenes, e, [&](int i) { return A.scenes[i].entry0; });
-  const SceneDesc& S = A.scenes[k];
-  uint64_t local = e - S.entry0;
-  uint32_t slot = (uint32_t)(local / (uint32_t)S.spp);
-  uint32_t s = S.s0 + (uint32_t)(local % (uint32_t)S.spp);
-  int32_t px, py;
-  if (!slot_pixel(slot, S.tiles_x, S.fr.w, S.fr.h, px, py)) {
-    entries[e] = miss_entry();
-    return;
+// Sum of n finished entry records in sample order, four loads at a time (a
+// 128-byte line holds four records).
+__device__ inline float3 sum_samples(const RayEntry* __restrict__ q, int32_t n) {
+  float3 a = make_float3(0, 0, 0);
+  int32_t k = 0;
+  for (; k + 4 <= n; k += 4) {
+    float4 v[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) v[j] = *(const float4*)(q + k + j);
+#pragma unroll
+    for (int j = 0; j < 4; j++) a = make_float3(a.x + v[j].x, a.y + v[j].y, a.z + v[j].z);
   }
-  Med m = med;
-  m.rec = (decltype(m.rec))S.rec;
-  m.keys = S.keys;
-  m.kidx = S.kidx;
-  m.kbits = S.kbits;
-  m.n = S.n;
-  m.dmax = S.dmax;
-  entries[e] = camera_entry(S.fr, S.seed, m, px, py, (uint32_t)(py * S.fr.w + px), s);
+  for (; k < n; k++) {
+    const float4 v = *(const float4*)(q + k);
+    a = make_float3(a.x + v.x, a.y + v.y, a.z + v.z);
+  }
+  return a;
 }
 
-// Zeroes (zero != 0) or divides by spp every pixel of a batch's images.
-__global__ void k_batch_images(const SceneDesc* __restrict__ sc, int32_t n, uint64_t total_px, int zero) {
-  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The pass's samples summed per pixel (thread = slot).  mode 0: the image's
+// only contribution, divided by the samples; 1: the first of several; 2: one
+// more of them.
+__global__ __launch_bounds__(256) void k_resolve(RenderArgs A, int mode) {
+  const uint32_t slot = blockIdx.x * blockDim.x + threadIdx.x;
+  int32_t px, py;
+  if (slot >= A.slots || !slot_pixel(slot, A.tiles_x, A.fr.w, A.fr.h, px, py)) return;
+  const float3 a = sum_samples(A.entries + (size_t)slot * (uint32_t)A.pass_spp, A.pass_spp);
+  float* o = A.out + 3 * ((size_t)py * (uint32_t)A.fr.w + (uint32_t)px);
+  if (mode == 0) {
+    const float div = (float)A.spp;
+    o[0] = a.x / div;
+    o[1] = a.y / div;
+    o[2] = a.z / div;
+  } else if (mode == 1) {
+    o[0] = a.x;
+    o[1] = a.y;
+    o[2] = a.z;
+  } else {
+    o[0] = o[0] + a.x;
+    o[1] = o[1] + a.y;
+    o[2] = o[2] + a.z;
+  }
+}
+
+// The same for a batch of scenes: every pixel of every image; divided by the
+// samples unless light rays are still to be added.
+__global__ __launch_bounds__(256) void k_resolve_batch(RenderArgs A, uint64_t total_px) {
+  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total_px) return;
-  const int k = scene_search(n, i, [&](int j) { return sc[j].pix0; });
-  float* o = sc[k].out + 3 * (i - sc[k].pix0);
-  if (zero) {
-    o[0] = 0.0f;
-    o[1] = 0.0f;
-    o[2] = 0.0f;
-  } else {
-    float div = (float)sc[k].spp;
-    o[0] = o[0] / div;
-    o[1] = o[1] / div;
-    o[2] = o[2] / div;
-  }
+  const SceneDesc& S = A.scenes[scene_search(A.nscenes, i, [&](int j) { return A.scenes[j].pix0; })];
+  const uint32_t p = (uint32_t)(i - S.pix0), x = p % (uint32_t)S.fr.w, y = p / (uint32_t)S.fr.w;
+  const uint32_t slot = ((y >> 3) * (uint32_t)S.tiles_x + (x >> 3)) * 64u + (y & 7u) * 8u + (x & 7u);
+  const float3 a = sum_samples(A.entries + S.entry0 + (uint64_t)slot * (uint32_t)S.spp, S.spp);
+  const float div = A.defer ? 1.0f : (float)S.spp;
+  float* o = S.out + 3 * (size_t)p;
+  o[0] = a.x / div;
+  o[1] = a.y / div;
+  o[2] = a.z / div;
 }
 
-template <class Med>
-__global__ __launch_bounds__(256) void k_raygen(RenderArgs A, Med med, RayEntry* __restrict__ entries) {
-  uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (uint64_t)A.slots * (uint64_t)A.pass_spp) return;
-  uint32_t pix, s;
-  int32_t px, py;
-  if (A.train) {
-    s = (uint32_t)e;
-    pix = train_pixel(A.seed, s, A.npix);
-    px = (int32_t)(pix % (uint32_t)A.fr.w);
-    py = (int32_t)(pix / (uint32_t)A.fr.w);
-  } else {
-    uint32_t slot = (uint32_t)(e / (uint32_t)A.pass_spp);
-    s = (uint32_t)(A.pass_start + (int32_t)(e % (uint32_t)A.pass_spp));
-    if (!slot_pixel(slot, A.tiles_x, A.fr.w, A.fr.h, px, py)) {
-      entries[e] = miss_entry();  // padding slot of an edge tile: never traced, never queried
-      return;
-    }
-    pix = (uint32_t)(py * A.fr.w + px);
-  }
-  entries[e] = camera_entry(A.fr, A.seed, med, px, py, pix, s);
+// Divides every pixel of a batch's images by its scene's samples.
+__global__ __launch_bounds__(256) void k_scale_batch(RenderArgs A, uint64_t total_px) {
+  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total_px) return;
+  const SceneDesc& S = A.scenes[scene_search(A.nscenes, i, [&](int j) { return A.scenes[j].pix0; })];
+  float* o = S.out + 3 * (i - S.pix0);
+  const float div = (float)S.spp;
+  o[0] = o[0] / div;
+  o[1] = o[1] / div;
+  o[2] = o[2] / div;
 }
 
 enum { M_TRACK = 0, M_SHADOW = 1, M_COLLIDE = 2, M_SCATTER = 3, M_ESCAPE = 4, M_FINISH = 5, M_FETCH = 6,
-       M_START = 7, M_DONE = 8 };
+       M_DONE = 7 };
 
-constexpr int kTabStride = 19;  // floats per lane in the LDS dot table (odd: no bank conflicts)
-
-// Dot products of the 9 face directions with the segment's direction d and
-// origin o, each rounded as (n.x a.x + n.y a.y) + n.z a.z would be (its
-// zero terms are exact).
-__device__ inline void set_segment(float* tab, float3 o, float3 d, float oscale) {
-  o = make_float3(o.x * oscale, o.y * oscale, o.z * oscale);
-  tab[0] = d.x;
-  tab[1] = d.y;
-  tab[2] = d.z;
-  tab[3] = d.x + d.y;
-  tab[4] = d.x - d.y;
-  tab[5] = d.x + d.z;
-  tab[6] = d.x - d.z;
-  tab[7] = d.y + d.z;
-  tab[8] = d.y - d.z;
-  tab[9] = o.x;
-  tab[10] = o.y;
-  tab[11] = o.z;
-  tab[12] = o.x + o.y;
-  tab[13] = o.x - o.y;
-  tab[14] = o.x + o.z;
-  tab[15] = o.x - o.z;
-  tab[16] = o.y + o.z;
-  tab[17] = o.y - o.z;
+constexpr uint32_t kMinTake = 16;  // paths a wave takes at least
+// Adds each lane's v[0..n) to the block's statistics slot: wave reductions,
+// one atomic per wave and counter.
+template <int N>
+__device__ inline void add_stats(const RenderArgs& A, const uint32_t (&v)[N]) {
+#pragma unroll
+  for (int q = 0; q < N; q++) {
+    unsigned long long x = v[q];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    if (__lane_id() == 0 && x) atomicAdd(stat_slot(A) + q, x);
+  }
 }
 
+// Camera rays and their walk to the first real collision, one thread per
+// entry record in record order: the samples of a pixel are neighbouring
+// lanes, which walk the same tets, so a wave reads a few record lines per step
+// and its lanes stay together until they collide or all leave the grid.
+// Blocks are dealt to eight lists round-robin, as the hardware deals blocks to
+// the XCDs (the lists follow the blocks of an image's training paths, a
+// multiple of 8); list r takes chunks r, r + 8, ... of chunk_blocks blocks, so
+// that neighbouring rays share an XCD's L2 and every XCD gets its share of
+// the image's dense part (one contiguous eighth each left half the XCDs idle
+// at the end: 17.4 ms on the 33 M rays of the 1024^2 x 32 cloud frame,
+// 2.8 of 5 resident waves per SIMD on average).  A block lists its colliding samples with one atomic on its
+// band's count.  MODEL: the grid carries a density model.
+template <class Med, bool BATCH, bool MODEL>
+__global__ __launch_bounds__(256) void k_first(RenderArgs A, Med med) {
+  __shared__ float s_tab[Med::kTabled ? kTabRows * kTabRow : 1];
+  __shared__ uint32_t s_n[4], s_base;
+  float* tab = s_tab + threadIdx.x;
+  const int lane = __lane_id();
+  // the first blocks trace the training paths that go with an image
+  const bool with = !BATCH && blockIdx.x < A.train_blocks, train = with || (!BATCH && A.train);
+  const uint32_t blk = blockIdx.x - (with ? 0u : A.train_blocks);
+  const uint32_t band = with ? 0u : blk & 7u, j = blk >> 3, g = A.chunk_blocks;
+  const uint64_t e = (with ? (uint64_t)blk : ((uint64_t)(j / g) * 8u + band) * g + j % g) * 256u + threadIdx.x;
+  const uint64_t total = BATCH ? A.total_entries : (with ? A.train_items : (uint64_t)A.slots * (uint64_t)A.pass_spp);
+  RayEntry* const entries = A.entries + (with ? A.train_ent0 : 0u);
+  uint32_t n_stat[5] = {0, 0, 0, 0, 0};  // steps, null collisions, real collisions, escapes, truncated
+  bool hit = false;
+  if (e < total) {
+    // the sample
+    uint32_t pix = 0, smp;
+    int32_t px, py, sc = 0;
+    bool real_pixel = true;
+    uint64_t seed = with ? A.train_seed : A.seed;
+    if constexpr (BATCH) {
+      sc = scene_search(A.nscenes, e, [&](int i) { return A.scenes[i].entry0; });
+      const SceneDesc& S = A.scenes[sc];
+      const uint64_t l = e - S.entry0;
+      smp = S.s0 + (uint32_t)(l % (uint32_t)S.spp);
+      real_pixel = slot_pixel((uint32_t)(l / (uint32_t)S.spp), S.tiles_x, S.fr.w, S.fr.h, px, py);
+      pix = (uint32_t)(py * S.fr.w + px);
+      seed = S.seed;
+    } else if (train) {
+      smp = (uint32_t)e;
+      pix = train_pixel(seed, smp, A.npix);
+      px = (int32_t)(pix % (uint32_t)A.fr.w);
+      py = (int32_t)(pix / (uint32_t)A.fr.w);
+    } else {
+      smp = (uint32_t)(A.pass_start + (int32_t)(e % (uint32_t)A.pass_spp));
+      real_pixel = slot_pixel((uint32_t)(e / (uint32_t)A.pass_spp), A.tiles_x, A.fr.w, A.fr.h, px, py);
+      pix = (uint32_t)(py * A.fr.w + px);
+    }
+    if (real_pixel) {  // (a padding slot of an edge tile is never read)
+      Med m = med;
+      if constexpr (BATCH) {
+        const SceneDesc& S = A.scenes[sc];
+        m.rec = (decltype(m.rec))S.rec;
+        m.keys = S.keys;
+        m.kidx = S.kidx;
+        m.kbits = S.kbits;
+        m.n = S.n;
+        m.dmax = S.dmax;
+      }
+      float3 o, d;
+      const int64_t c = camera_entry(BATCH ? A.scenes[sc].fr : A.fr, seed, m, px, py, pix, smp, o, d);
+      float3 L = make_float3(BATCH ? A.scenes[sc].env[0] : A.env[0], BATCH ? A.scenes[sc].env[1] : A.env[1],
+                             BATCH ? A.scenes[sc].env[2] : A.env[2]);
+      uint32_t steps = 0, cell = (uint32_t)c;
+      float t = 0.0f;
+      if (c >= 0) {
+        float tau = exp_tau(uniform01(seed, pix, smp, 0, kStreamFlight, 0));
+        uint32_t jf = 1;  // flight draw 0 made tau
+        set_segment<Med>(tab, o, d);
+        for (;;) {
+          Step st;
+          float sb, dtau;
+          bool out, cut;
+          for (;;) {  // cells without a tentative collision
+            cut = steps >= A.max_steps;
+            if (cut) break;
+            st = m.step(cell, o, d, tab, t);
+            steps++;
+            sb = st.majorant;
+            dtau = sb * (st.te - t);  // (0 in an empty cell)
+            out = !st.ok || st.next < 0;
+            if (out || tau < dtau) break;
+            tau = tau - dtau;
+            t = st.te;
+            cell = (uint32_t)st.next;
+          }
+          if (cut) {  // a truncated path keeps what it has gathered: nothing
+            n_stat[4] = 1;
+            L = make_float3(0, 0, 0);
+            break;
+          }
+          if (st.ok) {
+            while (tau < dtau) {
+              const float tc = t + tau / sb;
+              float sg = st.sigma;
+              if constexpr (MODEL) {  // extinction at the tentative point
+                const ExtArgs& X = BATCH ? A.scenes[sc].ex : A.ex;
+                if (X.model) sg = model_sigma(X, cell, o, d, tc);
+              }
+              t = tc;
+              if ((Med::kTight && !MODEL) || !(sg < sb) ||
+                  uniform01(seed, pix, smp, 0, kStreamFlight, jf++) < sg / sb) {
+                hit = true;
+                break;
+              }
+              n_stat[1]++;
+              tau = exp_tau(uniform01(seed, pix, smp, 0, kStreamFlight, jf++));
+              dtau = sb * (st.te - t);
+            }
+            if (hit) break;
+          }
+          if (out) {
+            n_stat[3] = 1;
+            break;
+          }
+          tau = tau - dtau;
+          t = st.te;
+          cell = (uint32_t)st.next;
+        }
+      }
+      float4* q = (float4*)(entries + e);
+      if (hit) {
+        q[0] = make_float4(o.x + t * d.x, o.y + t * d.y, o.z + t * d.z, __uint_as_float(cell));
+        q[1] = make_float4(d.x, d.y, d.z, __uint_as_float(steps));
+      } else {
+        n_stat[0] = steps;
+        q[0] = make_float4(L.x, L.y, L.z, __uint_as_float(kDone));
+        if (train) A.path_l[e] = make_float4(L.x, L.y, L.z, __uint_as_float(0u));
+      }
+    }
+  }
+  const unsigned long long m = __ballot(hit);
+  if (lane == 0) s_n[threadIdx.x >> 6] = (uint32_t)__popcll(m);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t n = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+    s_base = n ? atomicAdd(A.head + kCountAt + (with ? kTrainList : (int)band) * kLine, n) : 0u;
+  }
+  __syncthreads();
+  if (hit) {
+    uint32_t at = s_base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+    for (uint32_t w = 0; w < (threadIdx.x >> 6); w++) at += s_n[w];
+    A.list[(with ? (uint64_t)A.train_list0 : (uint64_t)band * A.band_size) + at] = (uint32_t)e;
+  }
+  add_stats(A, n_stat);
+}
+
+// The listed paths, from their first real collision on.
 // W: occupancy target in waves per SIMD (the register budget follows).
 // NRC: 0 plain estimator; 1 paths stop at real vertex A.truncate and leave
-// a query for the radiance cache in their entry record; 2 training paths
-// (A.train), whose first vertices and final radiance are recorded.
+// a query for the radiance cache; 2 training paths (A.train), whose first
+// vertices and final radiance are recorded.
 // BATCH: the lanes' samples come from a batch of scenes (A.scenes); each
 // lane keeps its sample's scene index and that grid's record pointer, and
 // reads the scene's light, medium, seed and image from the table at events.
@@ -648,28 +904,32 @@ __device__ inline void set_segment(float* tab, float3 o, float3 d, float oscale)
 // (the plain variant carries none of that code).
 template <class Med, int W, int NRC, bool BATCH = false, bool EXT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) void k_render(RenderArgs A, Med med) {
-  __shared__ float s_tab[256 * kTabStride];
-  __shared__ uint32_t s_lq;  // light rays this block queued
-  float* tab = s_tab + threadIdx.x * kTabStride;
+  __shared__ float s_tab[Med::kTabled ? kTabRows * kTabRow : 1];
+  // per wave: its queue chunk's first record, records used, light rays queued
+  // (volatile: different lanes of the wave read and write them in turn)
+  __shared__ volatile uint32_t s_lq[4][3];
+  float* tab = s_tab + threadIdx.x;
   const int lane = __lane_id();
   int mode = M_FETCH;
   uint32_t pix = 0, ent = 0;  // ent: the sample's entry record
-  int32_t s = 0, s_end = 0;
-  float3 o = make_float3(0, 0, 0), d = o, dsave = o, L = o, acc = o;
+  int32_t s = 0;
+  float3 o = make_float3(0, 0, 0), d = o, dsave = o, L = o;
   float beta = 1.0f, t = 0.0f, tau = 0.0f, od = 0.0f;
   uint32_t cell = 0, cell_x = 0, bounce = 0, jf = 0, jn = 0, steps = 0;
   uint32_t n_steps = 0, n_null = 0, n_real = 0, n_esc = 0, n_trunc = 0, n_query = 0;
-  int range = blockIdx.x & 7, tried = 0;  // wave-uniform work range state
-  uint32_t bnext = 0, bend = 0;          // wave-uniform batch of work items
-  const float3 sun0 = make_float3(A.sun[0], A.sun[1], A.sun[2]);
-  uint32_t sc = 0, bsc = 0;  // lane's scene; wave-uniform scene of the current batch
+  // wave-uniform list state: training paths first (they are the longest),
+  // then this block's band, then the others
+  const int list0 = NRC == 1 && A.train_items ? kTrainList : (int)(blockIdx.x & 7), nlists = NRC == 1 && A.train_items ? 9 : 8;
+  const uint32_t list_waves = max(1u, gridDim.x * (blockDim.x >> 6) / 8u);  // waves per band
+  int range = list0, tried = 0;
+  uint32_t bnext = 0, bend = 0;  // wave-uniform batch of listed paths
+  uint32_t sc = 0;           // the lane's scene
   bool trainp = false;       // cache mode 1: the lane's path is a training path
   Med lm = med;              // the lane's medium (its scene's records)
-  // plain single-scene walks on tet grids may queue their light rays
-  constexpr bool DEFER = NRC != 2 && !BATCH && !std::is_same<Med, VoxelMedium>::value;
-  if constexpr (DEFER) {
-    if (threadIdx.x == 0) s_lq = 0;
-    __syncthreads();
+  const int wv = threadIdx.x >> 6;
+  {
+    if (lane < 3) s_lq[wv][lane] = lane == 1 ? A.lq_chunk : 0u;  // a full chunk: the first ray takes one
+    __builtin_amdgcn_wave_barrier();
   }
 #define TV_SC A.scenes[sc]
 #define TV_SEED (BATCH ? TV_SC.seed : ((NRC == 1 && trainp) ? A.train_seed : A.seed))
@@ -677,8 +937,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
 #define TV_G (BATCH ? TV_SC.g : A.g)
 #define TV_E(i) (BATCH ? TV_SC.E[i] : A.E[i])
 #define TV_ENV(i) (BATCH ? TV_SC.env[i] : A.env[i])
-#define TV_OUT (BATCH ? TV_SC.out : A.out)
-#define TV_SUN (BATCH ? make_float3(TV_SC.sun[0], TV_SC.sun[1], TV_SC.sun[2]) : sun0)
+#define TV_SUN (BATCH ? make_float3(TV_SC.sun[0], TV_SC.sun[1], TV_SC.sun[2]) : make_float3(A.sun[0], A.sun[1], A.sun[2]))
 #define TV_EX (BATCH ? TV_SC.ex : A.ex)
 
   // real collision at t: start the light ray (right after the walk step, or
@@ -690,6 +949,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
     if constexpr (EXT)
       if (TV_EX.model) return model_sigma(TV_EX, cell, o, d, t);
     return lm.sigma_at(cell);
+  };
+  // training paths whose light rays are queued leave each vertex's gathered
+  // radiance in A.terms (their records need what came before each vertex)
+  auto termed = [&]() -> bool { return (NRC == 2 || (NRC == 1 && trainp)) && A.terms; };
+  auto term_index = [&]() -> uint32_t {
+    return (NRC == 2 ? ent : ent - A.train_ent0) * (uint32_t)A.max_bounces + (bounce - 1u);
   };
   auto start_light = [&]() {
     n_real++;
@@ -711,36 +976,64 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
     if (EXT && TV_EX.ch_a) alb = TV_EX.ch_a[cell];
     if (EXT && TV_EX.ch_t) {
       const float e = (1.0f - alb) * TV_EX.ch_t[cell];
-      L.x = L.x + beta * (e * TV_EX.emission[0]);
-      L.y = L.y + beta * (e * TV_EX.emission[1]);
-      L.z = L.z + beta * (e * TV_EX.emission[2]);
+      const float3 em = make_float3(beta * (e * TV_EX.emission[0]), beta * (e * TV_EX.emission[1]),
+                                    beta * (e * TV_EX.emission[2]));
+      if (NRC != 0 && termed()) {
+        A.terms[2 * (size_t)term_index() + 1] = make_float4(em.x, em.y, em.z, 0.0f);
+      } else {
+        L.x = L.x + em.x;
+        L.y = L.y + em.y;
+        L.z = L.z + em.z;
+      }
     }
     beta = beta * alb;
-    if constexpr (DEFER) {
+    {
       // queue the light ray (weight now, walk later); the path goes on to its
-      // scatter (training paths of the cache keep their own walks: their
-      // records need the light gathered before each vertex)
-      if (A.defer && !(NRC == 1 && trainp)) {
+      // scatter
+      if (A.defer && !(NRC == 1 && trainp && !A.terms)) {
         const unsigned long long act = __ballot(1);
         const int lead = __builtin_ctzll(act);
-        uint32_t base = 0;
-        if (lane == lead) base = atomicAdd(&s_lq, (uint32_t)__popcll(act));  // the block's own count, in LDS
-        base = __shfl(base, lead);
-        const uint32_t q = base + (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
-        if (q < A.lq_region) {  // a full region leaves the walk to the lane
+        const uint32_t cnt = (uint32_t)__popcll(act), k = (uint32_t)__popcll(act & ((1ull << lane) - 1ull));
+        uint32_t base = 0, room = 0, next = 0, used = 0;
+        if (lane == lead) {
+          base = s_lq[wv][0];
+          used = s_lq[wv][1];  // kDone: the queue is full
+          room = used == kDone ? 0u : A.lq_chunk - used;
+          next = kDone;
+          uint32_t left = cnt > room ? kDone : used + cnt;
+          if (cnt > room && used != kDone) {
+            const uint32_t c = atomicAdd(A.head + kChunkAt, 1u);
+            if (c < A.lq_chunks) {
+              next = c * A.lq_chunk;
+              s_lq[wv][0] = next;
+              left = cnt - room;
+            }
+          }
+          s_lq[wv][1] = left;
+          s_lq[wv][2] = s_lq[wv][2] + (next != kDone ? cnt : min(cnt, room));
+        }
+        base = __shfl(base, lead) + __shfl(used, lead);
+        room = __shfl(room, lead);
+        next = __shfl(next, lead);
+        if (k < room || next != kDone) {  // a full queue leaves the walk to the lane
+          const uint32_t q = k < room ? base + k : next + (k - room);
           const float gg = (EXT && TV_EX.ch_g) ? TV_EX.ch_g[cell] : TV_G;
-          const float mu = (d.x * sun0.x + d.y * sun0.y) + d.z * sun0.z;
-          const float bp = beta * hg_pdf(gg, mu);
+          const float3 sun = TV_SUN;
+          const float mu = (d.x * sun.x + d.y * sun.y) + d.z * sun.z;
           LightRec r;
           r.x = x.x;
           r.y = x.y;
           r.z = x.z;
           r.cell = cell;
-          r.w0 = bp * A.E[0];
-          r.w1 = bp * A.E[1];
-          r.w2 = bp * A.E[2];
-          r.pix = pix;
-          A.lq[(size_t)blockIdx.x * A.lq_region + q] = r;
+          r.bp = beta * hg_pdf(gg, mu);
+          r.to = BATCH ? ent : pix;
+          r.sample = (uint32_t)s;
+          r.bounce = bounce;
+          if (NRC != 0 && termed()) {
+            r.to = term_index();
+            r.bounce |= kToTerm;
+          }
+          A.lq[q] = r;
           dsave = d;
           o = x;
           t = 0.0f;
@@ -758,16 +1051,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
     cell_x = cell;
     od = A.transmittance == 0 ? 0.0f : 1.0f;
     if (A.transmittance != 0) tau = exp_tau(uniform01(TV_SEED, pix, (uint32_t)s, bounce, kStreamLight, jn++));
-    set_segment(tab, o, d, Med::kOriginScale);
+    set_segment<Med>(tab, o, d);
     mode = M_SHADOW;
   };
 
   for (;;) {
-    // ================= events: run when enough lanes wait for one, or when
-    // no lane is walking (waiting lanes idle meanwhile)
-    unsigned long long waiting = __ballot(mode > M_SHADOW);
-    if (waiting && (__popcll(waiting) >= A.event_wait || __popcll(waiting) == 64 ||
-                    __ballot(mode <= M_SHADOW) == 0)) {
+    // ================= events: run when enough lanes wait (those out of work
+    // count), or when no lane is walking (waiting lanes idle meanwhile)
+    const unsigned long long walking = __ballot(mode <= M_SHADOW);
+    const unsigned long long pending = __ballot(mode > M_SHADOW && mode < M_DONE);
+    if (!(walking | pending)) break;
+    if (pending && (64 - __popcll(walking) >= A.event_wait || !walking)) {
       if (NRC == 1) {  // the cache stands for the rest of the path: append a query
         const bool isq = mode == M_COLLIDE && !trainp && (int32_t)bounce + 1 == A.truncate;
         const unsigned long long qm = __ballot(isq);
@@ -789,16 +1083,102 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
           }
         }
       }
-      if (mode == M_COLLIDE) start_light();
+      if (mode == M_ESCAPE) {  // left the grid: the environment
+        n_esc++;
+        L.x = L.x + beta * TV_ENV(0);
+        L.y = L.y + beta * TV_ENV(1);
+        L.z = L.z + beta * TV_ENV(2);
+        mode = M_FINISH;
+      }
+      if (mode == M_FINISH) {  // path done: its sample's radiance
+        n_steps += steps;
+        *(float4*)(A.entries + ent) = make_float4(L.x, L.y, L.z, __uint_as_float(kDone));
+        if (NRC == 2 || (NRC == 1 && trainp))
+          A.path_l[NRC == 2 ? ent : ent - A.train_ent0] = make_float4(L.x, L.y, L.z, __uint_as_float(bounce));
+        mode = M_FETCH;
+      }
+      // idle lanes take consecutive listed paths from the wave's batch; a
+      // wave refills its batch with one atomic, first from this block's band
+      // (blocks are dealt to the 8 XCDs round-robin, so an XCD's L2 serves
+      // one band of the image), then from the others.
+      bool need = mode == M_FETCH;
+      unsigned long long m = __ballot(need);
+      if (m) {
+        while (bnext >= bend && tried < nlists) {
+          const uint32_t n = A.head[kCountAt + range * kLine];
+          const uint32_t take = min(A.batch, max(kMinTake, n / (range == kTrainList ? 8 * list_waves : list_waves)));
+          uint32_t base = 0;
+          if (lane == 0) base = n ? atomicAdd(A.head + kTakenAt + range * kLine, take) : 0u;
+          base = __shfl(base, 0);
+          if (base < n) {
+            bnext = base;
+            bend = min(base + take, n);
+          } else {  // list drained: move on
+            range = NRC == 1 && range == kTrainList ? (int)(blockIdx.x & 7) : (range + 1) & 7;
+            tried++;
+          }
+        }
+        if (bnext < bend) {
+          const uint32_t at = bnext + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+          if (need && at < bend) {  // the path's first collision
+            const bool tr = NRC == 1 && range == kTrainList;
+            const uint32_t e = A.list[(tr ? (uint64_t)A.train_list0 : (uint64_t)(uint32_t)range * A.band_size) + at];
+            if constexpr (BATCH) {
+              sc = (uint32_t)scene_search(A.nscenes, e, [&](int i) { return A.scenes[i].entry0; });
+              const SceneDesc& S = A.scenes[sc];
+              const uint32_t local = (uint32_t)(e - S.entry0);
+              int32_t px, py;
+              (void)slot_pixel(local / (uint32_t)S.spp, S.tiles_x, S.fr.w, S.fr.h, px, py);
+              pix = (uint32_t)(py * S.fr.w + px);
+              s = (int32_t)(S.s0 + local % (uint32_t)S.spp);
+              lm.rec = (decltype(lm.rec))S.rec;
+              ent = e;
+            } else if (NRC == 2 || tr) {
+              pix = train_pixel(NRC == 2 ? A.seed : A.train_seed, e, A.npix);
+              s = (int32_t)e;
+              ent = NRC == 2 ? e : A.train_ent0 + e;
+              trainp = NRC == 1;
+            } else {
+              int32_t px, py;
+              (void)slot_pixel(e / (uint32_t)A.pass_spp, A.tiles_x, A.fr.w, A.fr.h, px, py);
+              pix = (uint32_t)(py * A.fr.w + px);
+              s = A.pass_start + (int32_t)(e % (uint32_t)A.pass_spp);
+              ent = e;
+              trainp = false;
+            }
+            const float4* q = (const float4*)(A.entries + ent);
+            const float4 a = q[0], b = q[1];
+            o = make_float3(a.x, a.y, a.z);
+            d = make_float3(b.x, b.y, b.z);
+            cell = __float_as_uint(a.w);
+            steps = __float_as_uint(b.w);
+            t = 0.0f;
+            beta = 1.0f;
+            L = make_float3(0, 0, 0);
+            bounce = 0;
+            mode = M_COLLIDE;
+          }
+          bnext = min(bnext + (uint32_t)__popcll(m), bend);
+        } else if (need) {
+          mode = M_DONE;
+        }
+      }
+      if (mode == M_COLLIDE && (NRC != 1 || trainp || (int32_t)bounce + 1 != A.truncate)) start_light();
       if (mode == M_SCATTER) {  // light ray done: light estimate, then phase sampling
         const float gg = (EXT && TV_EX.ch_g) ? TV_EX.ch_g[cell_x] : TV_G;  // the collision tet's phase parameter
-        if (!DEFER || od >= 0.0f) {  // (od < 0: the light ray was queued)
+        if (od >= 0.0f) {  // (od < 0: the light ray was queued)
           float Tr = A.transmittance == 0 ? exp_neg(od) : od;
           float mu = (dsave.x * TV_SUN.x + dsave.y * TV_SUN.y) + dsave.z * TV_SUN.z;
           float ph = hg_pdf(gg, mu);
-          L.x = L.x + ((beta * ph) * TV_E(0)) * Tr;
-          L.y = L.y + ((beta * ph) * TV_E(1)) * Tr;
-          L.z = L.z + ((beta * ph) * TV_E(2)) * Tr;
+          const float3 li = make_float3(((beta * ph) * TV_E(0)) * Tr, ((beta * ph) * TV_E(1)) * Tr,
+                                        ((beta * ph) * TV_E(2)) * Tr);
+          if (NRC != 0 && termed()) {
+            A.terms[2 * (size_t)term_index()] = make_float4(li.x, li.y, li.z, 0.0f);
+          } else {
+            L.x = L.x + li.x;
+            L.y = L.y + li.y;
+            L.z = L.z + li.z;
+          }
         }
         if ((int32_t)bounce >= A.max_bounces) {
           mode = M_FINISH;
@@ -808,151 +1188,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
           t = 0.0f;
           cell = cell_x;
           tau = exp_tau(uniform01(TV_SEED, pix, (uint32_t)s, bounce, kStreamFlight, jf++));
-          set_segment(tab, o, d, Med::kOriginScale);
+          set_segment<Med>(tab, o, d);
           mode = M_TRACK;
         }
       }
-      if (mode == M_ESCAPE) {  // left the grid: the environment
-        n_esc++;
-        L.x = L.x + beta * TV_ENV(0);
-        L.y = L.y + beta * TV_ENV(1);
-        L.z = L.z + beta * TV_ENV(2);
-        mode = M_FINISH;
-      }
-      if (mode == M_FINISH) {  // sample done: accumulate; next sample or next item
-        acc.x = acc.x + L.x;
-        acc.y = acc.y + L.y;
-        acc.z = acc.z + L.z;
-        n_steps += steps;
-        steps = 0;
-        if (NRC == 2 || (NRC == 1 && trainp))
-          A.path_l[NRC == 2 ? ent : ent - A.train_ent0] = make_float4(L.x, L.y, L.z, __uint_as_float(bounce));
-        s++;
-        if (s < s_end) {
-          ent++;
-          mode = M_START;
-        } else if (NRC == 2 || (NRC == 1 && trainp)) {
-          mode = M_FETCH;
-        } else {
-          float* px = TV_OUT + 3 * (size_t)pix;
-          if (A.accumulate) {
-            atomicAdd(px, acc.x);
-            atomicAdd(px + 1, acc.y);
-            atomicAdd(px + 2, acc.z);
-          } else {
-            px[0] = acc.x / (float)A.spp;
-            px[1] = acc.y / (float)A.spp;
-            px[2] = acc.z / (float)A.spp;
-          }
-          mode = M_FETCH;
-        }
-      }
-      // idle lanes take consecutive work items from the wave's batch; a wave
-      // refills its batch with one atomic, first from this block's XCD range
-      // (blocks are dealt to the 8 XCDs round-robin, so an XCD's L2 serves
-      // one band of the image), then from the others.  Consecutive items are
-      // samples of one pixel, so lanes walking side by side share records.
-      bool need = mode == M_FETCH;
-      unsigned long long m = __ballot(need);
-      if (m) {
-        if (bnext >= bend && tried < 8) {
-          uint32_t base = 0;
-          if (lane == 0) base = atomicAdd(A.counter + range, A.batch);
-          base = __shfl(base, 0);
-          uint32_t r0 = (uint32_t)range * A.range_size;
-          uint32_t rend = min(r0 + A.range_size, A.items);
-          if (r0 >= rend || base >= rend - r0) {  // range drained: move on
-            range = (range + 1) & 7;
-            tried++;
-          } else {
-            bnext = r0 + base;
-            bend = min(bnext + A.batch, rend);
-            if constexpr (BATCH) bsc = (uint32_t)scene_search(A.nscenes, bnext, [&](int i) { return A.scenes[i].item0; });
-          }
-        }
-        if (bnext < bend) {
-          uint32_t item = bnext + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-          if (need && item < bend) {
-            if constexpr (BATCH) {
-              const SceneDesc& S = A.scenes[bsc];
-              uint32_t local = item - S.item0;
-              int32_t px, py;
-              if (local < S.items &&
-                  slot_pixel(local / (uint32_t)S.spp, S.tiles_x, S.fr.w, S.fr.h, px, py)) {
-                pix = (uint32_t)(py * S.fr.w + px);
-                s = (int32_t)(S.s0 + local % (uint32_t)S.spp);
-                s_end = s + 1;
-                ent = (uint32_t)(S.entry0 + local);
-                sc = bsc;
-                lm.rec = (decltype(lm.rec))S.rec;
-                acc = make_float3(0, 0, 0);
-                mode = M_START;
-              } else {
-                mode = M_FETCH;  // padding item or slot: take another
-              }
-            } else if (NRC == 2) {
-              pix = train_pixel(TV_SEED, item, A.npix);
-              s = (int32_t)item;
-              s_end = s + 1;
-              ent = item;
-              acc = make_float3(0, 0, 0);
-              mode = M_START;
-            } else if (NRC == 1 && item < A.train_items) {
-              pix = train_pixel(A.train_seed, item, A.npix);
-              s = (int32_t)item;
-              s_end = s + 1;
-              ent = A.train_ent0 + item;
-              trainp = true;
-              acc = make_float3(0, 0, 0);
-              mode = M_START;
-            } else {
-              const uint32_t it = NRC == 1 ? item - A.train_items : item;
-              if (NRC == 1) trainp = false;
-              uint32_t slot = it / (uint32_t)A.items_per_pixel;
-              uint32_t chunk = it % (uint32_t)A.items_per_pixel;
-              int32_t px, py;
-              if (slot_pixel(slot, A.tiles_x, A.fr.w, A.fr.h, px, py)) {
-                pix = (uint32_t)(py * A.fr.w + px);
-                s = A.pass_start + (int32_t)chunk * A.per_item;
-                s_end = min(s + A.per_item, A.pass_start + A.pass_spp);
-                ent = slot * (uint32_t)A.pass_spp + (uint32_t)(s - A.pass_start);
-                acc = make_float3(0, 0, 0);
-                mode = M_START;
-              } else {
-                mode = M_FETCH;  // padding slot of an edge tile: take another item
-              }
-            }
-          }
-          bnext = min(bnext + (uint32_t)__popcll(m), bend);
-        } else if (tried >= 8) {
-          if (need) mode = M_DONE;
-        }
-      }
-      if (mode == M_START) {  // new sample: its precomputed entry into the grid
-        const float4* q = (const float4*)(A.entries + ent);
-        float4 a = q[0], b = q[1];
-        uint32_t c = __float_as_uint(a.w);
-        steps = 0;
-        if (c == kMiss) {
-          L = make_float3(TV_ENV(0), TV_ENV(1), TV_ENV(2));
-          bounce = 0;
-          mode = M_FINISH;
-        } else {
-          o = make_float3(a.x, a.y, a.z);
-          d = make_float3(b.x, b.y, b.z);
-          tau = b.w;
-          cell = c;
-          t = 0.0f;
-          beta = 1.0f;
-          L = make_float3(0, 0, 0);
-          bounce = 0;
-          jf = 1;  // flight draw 0 of bounce 0 made the entry's depth
-          jn = 0;
-          set_segment(tab, o, d, Med::kOriginScale);
-          mode = M_TRACK;
-        }
-      }
-      if (__ballot(mode != M_DONE) == 0) break;
     }
     // ================= one walk step of the main path or of the light ray
     if (mode <= M_SHADOW) {
@@ -1043,43 +1282,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
   }
 #undef TV_EX
 #undef TV_SUN
-#undef TV_OUT
 #undef TV_ENV
 #undef TV_E
 #undef TV_G
 #undef TV_ALBEDO
 #undef TV_SEED
 #undef TV_SC
-  if constexpr (DEFER) {
-    if (A.defer) {
-      __syncthreads();
-      if (threadIdx.x == 0) A.lq_count[blockIdx.x] = min(s_lq, A.lq_region);
+  {
+    if (A.defer) {  // the rest of the wave's chunk is unused
+      const uint32_t base = s_lq[wv][0], used = s_lq[wv][1];
+      if (used != kDone)
+        for (uint32_t q = used + (uint32_t)lane; q < A.lq_chunk; q += 64) A.lq[base + q].cell = kDone;
+      if (lane == 0 && s_lq[wv][2]) atomicAdd(stat_slot(A) + 6, (unsigned long long)s_lq[wv][2]);
     }
   }
-  // ---- counters: wave reductions, one atomic per wave and counter
-  unsigned long long v[6] = {n_steps, n_null, n_real, n_esc, n_trunc, n_query};
-#pragma unroll
-  for (int q = 0; q < 6; q++) {
-    unsigned long long x = v[q];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    if (lane == 0 && x) atomicAdd(A.stats + q, x);
-  }
+  const uint32_t n_stat[6] = {n_steps, n_null, n_real, n_esc, n_trunc, n_query};
+  add_stats(A, n_stat);
 }
 
 // ---------------------------------------------------------------- deferred light rays
-// Offsets of the tracing blocks' light rays in one list (exclusive sum of
-// their counts, in order; off[nb] = the total).
-__global__ void k_light_offsets(const uint32_t* __restrict__ cnt, int nb, uint32_t* __restrict__ off) {
-  if (threadIdx.x != 0) return;
-  uint32_t s = 0;
-  for (int b = 0; b < nb; b++) {
-    off[b] = s;
-    s += cnt[b];
-  }
-  off[nb] = s;
-}
-
 // Bits 0..15 of x to the even bit positions.
 __device__ inline uint32_t spread_bits2(uint32_t x) {
   x &= 0xFFFFu;
@@ -1119,75 +1340,184 @@ __device__ inline uint32_t light_key(float3 p, float3 d, float3 t1, float3 t2, i
   return (bundle << (kDepthBits + 2 * fbits)) | (wq << (2 * fbits)) | fine;
 }
 
-// Keys and queue positions of the light rays of tracing block blockIdx.x,
-// listed from its offset, for the sort.
-__global__ void k_light_keys(const LightRec* __restrict__ lq, uint32_t region, const uint32_t* __restrict__ cnt,
-                             const uint32_t* __restrict__ off, uint32_t* __restrict__ keys, uint32_t* __restrict__ idx,
-                             float3 d, int cbits, int fbits) {
-  const uint32_t b = blockIdx.x, n = cnt[b], o = off[b];
+// Sort keys and queue positions of the n queue records in use.
+__global__ __launch_bounds__(256) void k_light_keys(const LightRec* __restrict__ lq, uint32_t n,
+                                                    uint32_t* __restrict__ keys, uint32_t* __restrict__ idx, float3 d,
+                                                    int cbits, int fbits) {
+  const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
   // an orthonormal basis (t1, t2) of the plane normal to d (Duff et al. 2017)
   const float sg = copysignf(1.0f, d.z);
   const float a = -1.0f / (sg + d.z);
   const float bxy = (d.x * d.y) * a;
   const float3 t1 = make_float3(1.0f + ((sg * d.x) * d.x) * a, sg * bxy, -sg * d.x);
   const float3 t2 = make_float3(bxy, sg + (d.y * d.y) * a, -d.y);
-  for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) {
-    const uint32_t q = b * region + j;
-    const LightRec r = lq[q];
-    keys[o + j] = light_key(make_float3(r.x, r.y, r.z), d, t1, t2, cbits, fbits);
-    idx[o + j] = q;
-  }
+  const float4 r = *(const float4*)(lq + q);
+  keys[q] = __float_as_uint(r.w) == kDone ? 0xFFFFFFFFu
+                                          : light_key(make_float3(r.x, r.y, r.z), d, t1, t2, cbits, fbits);
+  idx[q] = q;
 }
 
-// The queued light rays in the order of their keys (light_key): neighbouring
-// lanes start close together and walk the same direction through the same
-// column of tets, so they read the same records.  Each walks to the grid boundary summing the optical depth
-// (analytic transmittance, as the tracer's own light walk), then adds its
-// weight times e^-depth to its pixel.  A straight walk meets a tet at most
-// once, so the tet count bounds it.
-template <class Med>
-__global__ __launch_bounds__(256) void k_light(RenderArgs A, Med med, const LightRec* __restrict__ lq,
-                                               const uint32_t* __restrict__ order, uint32_t n) {
-  __shared__ float s_tab[256 * kTabStride];
-  float* tab = s_tab + threadIdx.x * kTabStride;
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  uint32_t steps = 0;
-  if (i < n) {
-    const LightRec r = lq[order[i]];
-    const float3 o = make_float3(r.x, r.y, r.z);
-    const float3 d = make_float3(A.sun[0], A.sun[1], A.sun[2]);
-    set_segment(tab, o, d, Med::kOriginScale);
-    uint32_t cell = r.cell;
-    float t = 0.0f, od = 0.0f;
-    for (;;) {
-      const Step st = med.step(cell, o, d, tab, t);
-      steps++;
-      if (!st.ok) break;
-      od = od + st.sigma * (st.te - t);
-      t = st.te;
-      if (st.next < 0 || (int64_t)steps > med.n) break;
-      cell = (uint32_t)st.next;
-    }
-    const float Tr = exp_neg(od);
-    float* px = A.out + 3 * (size_t)r.pix;
-    atomicAdd(px, r.w0 * Tr);
-    atomicAdd(px + 1, r.w1 * Tr);
-    atomicAdd(px + 2, r.w2 * Tr);
+// The queued light rays.  Each walks to the grid boundary by the tracer's own
+// light walk (optical depth, or ratio or delta tracking of the
+// transmittance), then adds its weight times the transmittance to its pixel
+// (atomically), or leaves it as its vertex's term (training paths).  A
+// straight walk meets a tet at most once, so the tet count bounds it.
+// With `order` (the sorted queue positions) neighbouring lanes start close
+// together and walk the same direction through the same column of tets, so
+// they read the same records.  Without it (n on the device, in
+// head[kChunkAt]) the rays are taken as queued.
+template <class Med, bool BATCH, bool EXT>
+__global__ __launch_bounds__(256) void k_light(RenderArgs A, Med med, const uint32_t* __restrict__ order,
+                                               uint32_t n_sorted, SegDirs sun) {
+  constexpr bool SHARED = !BATCH;  // one direction for all rays
+  __shared__ float s_tab[Med::kTabled ? (SHARED ? 9 : kTabRows) * kTabRow : 1];
+  __shared__ float s_dir[18];
+  if (SHARED && threadIdx.x < 9) {
+    s_dir[threadIdx.x] = sun.r[threadIdx.x];
+    s_dir[9 + threadIdx.x] = sun.d[threadIdx.x];
   }
-  unsigned long long x = steps;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  if (__lane_id() == 0 && x) atomicAdd(A.stats + 0, x);
+  __syncthreads();
+  float* tab = s_tab + threadIdx.x;
+  const uint32_t n = order ? n_sorted : min(A.head[kChunkAt], A.lq_chunks) * A.lq_chunk;
+  uint32_t total = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
+    const LightRec r = A.lq[order ? order[i] : (uint32_t)i];
+    if (r.cell == kDone) continue;
+    const uint32_t sc = BATCH ? (uint32_t)scene_search(A.nscenes, r.to, [&](int k) { return A.scenes[k].entry0; }) : 0u;
+    Med lm = med;
+    if constexpr (BATCH) {
+      lm.rec = (decltype(lm.rec))A.scenes[sc].rec;
+      lm.n = A.scenes[sc].n;
+    }
+    const float3 o = make_float3(r.x, r.y, r.z);
+    const float3 d = BATCH ? make_float3(A.scenes[sc].sun[0], A.scenes[sc].sun[1], A.scenes[sc].sun[2])
+                           : make_float3(A.sun[0], A.sun[1], A.sun[2]);
+    if constexpr (Med::kTabled) {
+      if constexpr (SHARED) set_origin(tab, o, Med::kOriginScale);
+      else set_segment<Med>(tab, o, d);
+    }
+    uint32_t cell = r.cell, steps = 0;
+    const uint32_t limit = lm.most_cells();
+    float t = 0.0f, od = 0.0f;
+    const int model = EXT ? (BATCH ? A.scenes[sc].ex.model : A.ex.model) : 0;
+    if (A.transmittance == 0) {
+      for (;;) {
+        const Step st = lm.template step<SHARED>(cell, o, d, tab, t, s_dir);
+        steps++;
+        if (!st.ok) break;
+        if (EXT && model) {  // linear model: exact integral over the segment (trapezoid)
+          const ExtArgs& X = BATCH ? A.scenes[sc].ex : A.ex;
+          od = od + (0.5f * (model_sigma(X, cell, o, d, t) + model_sigma(X, cell, o, d, st.te))) * (st.te - t);
+        } else {
+          od = od + st.sigma * (st.te - t);
+        }
+        t = st.te;
+        if (st.next < 0 || steps > limit) break;
+        cell = (uint32_t)st.next;
+      }
+      od = exp_neg(od);
+    } else {  // ratio (1) or delta (2) tracking: od holds the transmittance
+      uint32_t pix = r.to, smp = r.sample;
+      uint64_t seed = A.seed;
+      if constexpr (BATCH) {
+        const SceneDesc& S = A.scenes[sc];
+        const uint32_t local = (uint32_t)(r.to - S.entry0);
+        int32_t px, py;
+        (void)slot_pixel(local / (uint32_t)S.spp, S.tiles_x, S.fr.w, S.fr.h, px, py);
+        pix = (uint32_t)(py * S.fr.w + px);
+        smp = S.s0 + local % (uint32_t)S.spp;
+        seed = S.seed;
+      }
+      if (r.bounce & kToTerm) {
+        seed = A.train ? A.seed : A.train_seed;
+        pix = train_pixel(seed, smp, A.npix);
+      }
+      const uint32_t bounce = r.bounce & ~kToTerm;
+      uint32_t jn = 0;
+      od = 1.0f;
+      float tau = exp_tau(uniform01(seed, pix, smp, bounce, kStreamLight, jn++));
+      for (bool done = false; !done;) {
+        const Step st = lm.template step<SHARED>(cell, o, d, tab, t, s_dir);
+        steps++;
+        if (!st.ok) break;
+        const float sb = st.majorant;
+        if (sb > 0.0f) {
+          float dtau = sb * (st.te - t);
+          while (tau < dtau) {
+            t = t + tau / sb;
+            float sg = st.sigma;
+            if constexpr (EXT) {
+              const ExtArgs& X = BATCH ? A.scenes[sc].ex : A.ex;
+              if (model) sg = model_sigma(X, cell, o, d, t);
+            }
+            if (A.transmittance == 1) {
+              od = od * (1.0f - sg / sb);
+            } else if (!(sg < sb) || uniform01(seed, pix, smp, bounce, kStreamLight, jn++) < sg / sb) {
+              od = 0.0f;
+              done = true;
+              break;
+            }
+            tau = exp_tau(uniform01(seed, pix, smp, bounce, kStreamLight, jn++));
+            dtau = sb * (st.te - t);
+          }
+          if (!done) tau = tau - dtau;
+        }
+        if (od == 0.0f) done = true;
+        t = st.te;
+        if (st.next < 0 || steps > limit) done = true;
+        else cell = (uint32_t)st.next;
+      }
+    }
+    total += steps;
+    const float w0 = (r.bp * (BATCH ? A.scenes[sc].E[0] : A.E[0])) * od;
+    const float w1 = (r.bp * (BATCH ? A.scenes[sc].E[1] : A.E[1])) * od;
+    const float w2 = (r.bp * (BATCH ? A.scenes[sc].E[2] : A.E[2])) * od;
+    if (!BATCH && (r.bounce & kToTerm)) {
+      A.terms[2 * (size_t)r.to] = make_float4(w0, w1, w2, 0.0f);
+    } else {
+      float* px = A.out + 3 * (size_t)r.to;
+      if constexpr (BATCH) {
+        const SceneDesc& S = A.scenes[sc];
+        int32_t x, y;
+        (void)slot_pixel((uint32_t)(r.to - S.entry0) / (uint32_t)S.spp, S.tiles_x, S.fr.w, S.fr.h, x, y);
+        px = S.out + 3 * (size_t)(y * S.fr.w + x);
+      }
+      atomicAdd(px, w0);
+      atomicAdd(px + 1, w1);
+      atomicAdd(px + 2, w2);
+    }
+  }
+  const uint32_t n_stat[1] = {total};
+  add_stats(A, n_stat);
+}
+
+// Training paths with deferred light rays: what each path gathered, summed in
+// path order -- before each recorded vertex into its record, in all into
+// path_l (which holds the environment term and the vertex count).
+__global__ __launch_bounds__(256) void k_gather_terms(RenderArgs A, uint32_t paths, int emits) {
+  const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+  if (j >= paths) return;
+  const float4 env = A.path_l[j];
+  const uint32_t nv = __float_as_uint(env.w);
+  float3 L = make_float3(0, 0, 0);
+  for (uint32_t k = 0; k < nv; k++) {
+    if ((int32_t)k < A.rec_vertices)
+      A.vrec[((size_t)j * (uint32_t)A.rec_vertices + k) * 3 + 2] = make_float4(L.x, L.y, L.z, 0.0f);
+    const float4* q = A.terms + 2 * ((size_t)j * (uint32_t)A.max_bounces + k);
+    if (emits) {
+      const float4 em = q[1];
+      L = make_float3(L.x + em.x, L.y + em.y, L.z + em.z);
+    }
+    const float4 li = q[0];
+    L = make_float3(L.x + li.x, L.y + li.y, L.z + li.z);
+  }
+  A.path_l[j] = make_float4(L.x + env.x, L.y + env.y, L.z + env.z, env.w);
 }
 
 __global__ void k_zero_u32(uint32_t* p, int n) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
-}
-
-__global__ void k_zero_f32(float* p, int64_t n) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0.0f;
 }
 
 __global__ void k_scale_f32(float* p, int64_t n, float div) {
@@ -1218,8 +1548,10 @@ static int cu_count() {
 }
 
 constexpr int64_t kMaxEntriesPerPass = 1ll << 25;  // 1 GiB of entry records
-constexpr int kMaxTraceBlocks = 8192;               // blocks of one tracing launch with a light-ray queue
-
+// tet_render_noalloc's fixed scratch: counters, 2^21 entry records, their lists
+constexpr int64_t kNoAllocEntries = 1ll << 21;
+constexpr int64_t kListSlack = 8 * 64 * 256;  // the lists' last, incomplete round of chunks
+constexpr size_t kNoAllocBytes = (size_t)kNoAllocEntries * sizeof(RayEntry) + (size_t)(kNoAllocEntries + kListSlack) * 4 + kHeadBytes + 256;
 // Sort buffers of the deferred light rays (keys and positions, both ways)
 // and the sort's own scratch.
 struct LightSort {
@@ -1228,40 +1560,113 @@ struct LightSort {
   void* temp;
   size_t temp_bytes;
   int cbits, fbits;  // key layout (light_key)
-  int64_t queued;    // light rays walked from the queue so far
 };
 
-// The pass's queued light rays: their count, the sort by key, the walks.
+// The walks of a pass's queued light rays, taken as queued (no host
+// synchronisation: capturable).
+template <class Med, bool BATCH>
+static void launch_light(const RenderArgs& P, const Med& med, bool model, const uint32_t* order, uint32_t n,
+                         hipStream_t st) {
+  SegDirs sun;
+  seg_dirs(P.sun[0], P.sun[1], P.sun[2], sun);
+  const unsigned grid = order ? (n + 255) / 256
+                              : (unsigned)std::min<int64_t>((int64_t)cu_count() * 8, ((int64_t)P.lq_chunks * P.lq_chunk + 255) / 256);
+  if constexpr (Med::kTabled) {
+    if (model) {
+      hipLaunchKernelGGL((k_light<Med, BATCH, true>), dim3(grid), dim3(256), 0, st, P, med, order, n, sun);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_light<Med, BATCH, false>), dim3(grid), dim3(256), 0, st, P, med, order, n, sun);
+}
+
+// The pass's queued light rays: the records in use, the sort by key, the walks.
 template <class Med>
-static int walk_light_queue(const Med& med, const RenderArgs& P, int nblocks, LightSort& ls, hipStream_t st) {
-  uint32_t* off = P.lq_count + kMaxTraceBlocks;
-  hipLaunchKernelGGL(k_light_offsets, dim3(1), dim3(64), 0, st, (const uint32_t*)P.lq_count, nblocks, off);
+static int walk_light_queue(const Med& med, const RenderArgs& P, LightSort& ls, hipStream_t st) {
+  if (!ls.temp) {
+    launch_light<Med, false>(P, med, P.ex.model != 0, nullptr, 0, st);
+    return TET_OK;
+  }
   uint32_t n = 0;
-  TV_HIP(hipMemcpyAsync(&n, off + nblocks, 4, hipMemcpyDeviceToHost, st));
+  TV_HIP(hipMemcpyAsync(&n, P.head + kChunkAt, 4, hipMemcpyDeviceToHost, st));
   TV_HIP(hipStreamSynchronize(st));
-  ls.queued += n;
+  n = std::min(n, P.lq_chunks) * P.lq_chunk;
   if (!n) return TET_OK;
-  hipLaunchKernelGGL(k_light_keys, dim3((unsigned)nblocks), dim3(256), 0, st, (const LightRec*)P.lq, P.lq_region,
-                     (const uint32_t*)P.lq_count, (const uint32_t*)off, ls.keys[0], ls.idx[0],
-                     make_float3(P.sun[0], P.sun[1], P.sun[2]), ls.cbits, ls.fbits);
+  hipLaunchKernelGGL(k_light_keys, dim3((n + 255) / 256), dim3(256), 0, st, (const LightRec*)P.lq, n, ls.keys[0],
+                     ls.idx[0], make_float3(P.sun[0], P.sun[1], P.sun[2]), ls.cbits, ls.fbits);
   size_t tb = ls.temp_bytes;
   if (rocprim::radix_sort_pairs(ls.temp, tb, ls.keys[0], ls.keys[1], ls.idx[0], ls.idx[1], n, 0u, 32u, st) !=
       hipSuccess)
     return fail(TET_ERR_DEVICE, "render: sort of the light rays");
-  hipLaunchKernelGGL(k_light<Med>, dim3((n + 255) / 256), dim3(256), 0, st, P, med, (const LightRec*)P.lq,
-                     (const uint32_t*)ls.idx[1], n);
+  launch_light<Med, false>(P, med, P.ex.model != 0, (const uint32_t*)ls.idx[1], n, st);
   TV_HIP(hipGetLastError());
   return TET_OK;
 }
 
+// Light-ray queue of `samples` samples traced by at most `waves` waves: at
+// most 4 rays per sample (a full queue leaves the rest to the tracing lanes),
+// in whole chunks, and one more chunk for each wave (its last is partly used).
+static void size_light_queue(RenderArgs& A, int64_t samples, const tet_render_opts& o) {
+  A.lq_chunk = samples < (1 << 20) ? 64u : 256u;
+  const int64_t waves = std::min<int64_t>((int64_t)cu_count() * (o.blocks_per_cu ? o.blocks_per_cu : 8) * 4,
+                                          (samples + 63) / 64 + 4);
+  A.lq_chunks = (uint32_t)(std::min<int64_t>(1ll << 26, samples * 4) / A.lq_chunk + waves);
+}
+
+// The eight lists of ne entry records: blocks per chunk (at least 16 chunks
+// per list where there are blocks enough) and records per list.
+static uint32_t chunk_blocks_of(uint64_t ne) {
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(64, (ne + 255) / 256 / 128));
+}
+static uint32_t band_size_of(uint64_t ne) {
+  const uint64_t g = chunk_blocks_of(ne), chunks = ((ne + 255) / 256 + g - 1) / g;
+  return (uint32_t)((chunks + 7) / 8 * g * 256);
+}
+
+template <class Med, bool BATCH>
+static void launch_first(const RenderArgs& P, const Med& med, bool model, hipStream_t st) {
+  const unsigned grid = P.train_blocks + 8u * (P.band_size / 256u);
+  if constexpr (!std::is_same<Med, VoxelMedium>::value) {
+    if (model) {
+      hipLaunchKernelGGL((k_first<Med, BATCH, true>), dim3(grid), dim3(256), 0, st, P, med);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_first<Med, BATCH, false>), dim3(grid), dim3(256), 0, st, P, med);
+}
+
+// The tracing kernel at an occupancy target.  Five waves per SIMD fit beside
+// the segments' tables (27 KB of LDS per 256 lanes), so on tet grids 6 and 8
+// mean 5.
+template <class Med, int NRC>
+static void launch_render(const RenderArgs& P, const Med& med, bool ext, int waves, dim3 grid, dim3 block,
+                          hipStream_t st) {
+  if constexpr (!Med::kTabled) {
+    switch (waves) {
+      case 4: hipLaunchKernelGGL((k_render<Med, 4, NRC>), grid, block, 0, st, P, med); break;
+      case 6: hipLaunchKernelGGL((k_render<Med, 6, NRC>), grid, block, 0, st, P, med); break;
+      case 8: hipLaunchKernelGGL((k_render<Med, 8, NRC>), grid, block, 0, st, P, med); break;
+      default: hipLaunchKernelGGL((k_render<Med, 5, NRC>), grid, block, 0, st, P, med); break;
+    }
+  } else if (NRC == 0 && waves == 4) {
+    if (ext) hipLaunchKernelGGL((k_render<Med, 4, 0, false, true>), grid, block, 0, st, P, med);
+    else hipLaunchKernelGGL((k_render<Med, 4, 0>), grid, block, 0, st, P, med);
+  } else {
+    if (ext) hipLaunchKernelGGL((k_render<Med, 5, NRC, false, true>), grid, block, 0, st, P, med);
+    else hipLaunchKernelGGL((k_render<Med, 5, NRC>), grid, block, 0, st, P, med);
+  }
+}
+
 template <class Med, int NRC>
 static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, int32_t spp, int64_t npix,
-                      char* sc, RayEntry* entries, int64_t pass_cap, hipStream_t st, float* ms_total,
-                      float* ms_trace, float* ms_cache, bool timed = true, LightSort* ls = nullptr) {
+                      int64_t pass_cap, hipStream_t st, float* ms_total, float* ms_trace, float* ms_cache,
+                      bool timed = true, LightSort* ls = nullptr) {
   if (A.defer && !ls) return fail(TET_ERR_INTERNAL, "render: light-ray queue without its sort");
   int bs = o.block_size ? o.block_size : 256;
   int bpc = o.blocks_per_cu ? o.blocks_per_cu : 8;
   const bool ext = A.ex.model != 0 || A.ex.ch_t || A.ex.ch_a || A.ex.ch_g;
+  // several contributions per pixel: passes, queued light rays, cache queries
+  const bool several = pass_cap < spp || A.defer || NRC == 1;
   // timed: HIP events around the passes, waited for after each pass;
   // untimed: kernel launches on the stream only
   hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr, t0 = nullptr, t1 = nullptr;
@@ -1283,66 +1688,31 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
   *ms_trace = 0.0f;
   *ms_cache = 0.0f;
   if (timed) TV_HIP(hipEventRecord(e0, st));
-  if (A.accumulate && NRC != 2)
-    hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)((npix * 3 + 255) / 256)), dim3(256), 0, st, A.out, npix * 3);
   for (int32_t done = 0; done < spp; done += (int32_t)pass_cap) {
     A.pass_start = A.pass_start + (done ? (int32_t)pass_cap : 0);
     A.pass_spp = (int32_t)std::min<int64_t>(pass_cap, spp - done);
-    int32_t per = std::min(A.per_item, A.pass_spp);
-    int32_t ipp = (A.pass_spp + per - 1) / per;
     RenderArgs P = A;
-    P.per_item = per;
-    P.items_per_pixel = ipp;
     P.train_items = (NRC == 1 && done == 0) ? A.train_items : 0u;  // training paths ride the first pass
-    P.items = A.slots * (uint32_t)ipp + P.train_items;
-    P.entries = entries;
-    P.range_size = (P.items + 7) / 8;
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, (uint32_t*)sc, 9);  // ranges, query count
-    uint64_t ne = (uint64_t)A.slots * (uint64_t)P.pass_spp;
-    hipLaunchKernelGGL(k_raygen<Med>, dim3((unsigned)((ne + 255) / 256)), dim3(256), 0, st, P, med, entries);
-    if (P.train_items) {  // entry records of the training paths, after the image's
-      RenderArgs T = P;
-      T.train = 1;
-      T.seed = A.train_seed;
-      T.slots = P.train_items;
-      T.pass_spp = 1;
-      hipLaunchKernelGGL(k_raygen<Med>, dim3((P.train_items + 255) / 256), dim3(256), 0, st, T, med,
-                         entries + A.train_ent0);
-    }
-    int64_t grid = (int64_t)cu_count() * bpc;
-    int64_t need = ((int64_t)P.items + bs - 1) / bs;
-    grid = std::max<int64_t>(1, std::min(grid, need));
-    if (A.defer) {  // one queue region per block
-      grid = std::min<int64_t>(grid, kMaxTraceBlocks);
-      P.lq_region = (uint32_t)(A.lq_cap / (uint64_t)grid);
-    }
+    const uint64_t ne = (uint64_t)A.slots * (uint64_t)P.pass_spp;
+    P.band_size = band_size_of(ne);
+    P.chunk_blocks = chunk_blocks_of(ne);
+    hipLaunchKernelGGL(k_zero_u32, dim3((kPassWords + 255) / 256), dim3(256), 0, st, A.head, kPassWords);
     if (timed) TV_HIP(hipEventRecord(t0, st));
-    if (NRC != 0) {
-      if constexpr (!std::is_same<Med, VoxelMedium>::value) {
-        if (ext) hipLaunchKernelGGL((k_render<Med, 5, NRC, false, true>), dim3((unsigned)grid), dim3(bs), 0, st, P, med);
-        else hipLaunchKernelGGL((k_render<Med, 5, NRC>), dim3((unsigned)grid), dim3(bs), 0, st, P, med);
-      }
-    } else if (ext) {
-      if constexpr (!std::is_same<Med, VoxelMedium>::value) {
-        switch (o.waves_per_simd) {
-          case 4: hipLaunchKernelGGL((k_render<Med, 4, 0, false, true>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-          case 6: hipLaunchKernelGGL((k_render<Med, 6, 0, false, true>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-          case 8: hipLaunchKernelGGL((k_render<Med, 8, 0, false, true>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-          default: hipLaunchKernelGGL((k_render<Med, 5, 0, false, true>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-        }
-      }
-    } else {
-      switch (o.waves_per_simd) {
-        case 4: hipLaunchKernelGGL((k_render<Med, 4, 0>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-        case 6: hipLaunchKernelGGL((k_render<Med, 6, 0>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-        case 8: hipLaunchKernelGGL((k_render<Med, 8, 0>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-        default: hipLaunchKernelGGL((k_render<Med, 5, 0>), dim3((unsigned)grid), dim3(bs), 0, st, P, med); break;
-      }
-    }
+    P.train_blocks = (P.train_items + 255) / 256;
+    P.train_blocks = (P.train_blocks + 7) / 8 * 8;
+    launch_first<Med, false>(P, med, A.ex.model != 0, st);
+    int64_t grid = (int64_t)cu_count() * bpc;
+    int64_t need = ((int64_t)ne + P.train_items + bs - 1) / bs;
+    grid = std::max<int64_t>(1, std::min(grid, need));
+    launch_render<Med, NRC>(P, med, ext, o.waves_per_simd, dim3((unsigned)grid), dim3(bs), st);
+    if (NRC != 2)
+      hipLaunchKernelGGL(k_resolve, dim3((A.slots + 255) / 256), dim3(256), 0, st, P, !several ? 0 : (done ? 2 : 1));
     TV_HIP(hipGetLastError());
-    if constexpr (NRC != 2 && !std::is_same<Med, VoxelMedium>::value) {
-      if (A.defer && ls)  // the pass's queued light rays, part of the tracing time
-        if (int rc = walk_light_queue(med, P, (int)grid, *ls, st)) return rc;
+    if (A.defer)  // the pass's queued light rays, part of the tracing time
+      if (int rc = walk_light_queue(med, P, *ls, st)) return rc;
+    if (A.terms && (NRC == 2 || P.train_items)) {
+      const uint32_t paths = NRC == 2 ? A.slots : P.train_items;
+      hipLaunchKernelGGL(k_gather_terms, dim3((paths + 255) / 256), dim3(256), 0, st, P, paths, A.ex.ch_t ? 1 : 0);
     }
     if (timed) TV_HIP(hipEventRecord(t1, st));
     if (NRC == 1)  // the pass's cache queries, added to their pixels
@@ -1357,7 +1727,7 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
       *ms_cache += ms;
     }
   }
-  if (A.accumulate && NRC != 2)
+  if (several && NRC != 2)
     hipLaunchKernelGGL(k_scale_f32, dim3((unsigned)((npix * 3 + 255) / 256)), dim3(256), 0, st, A.out, npix * 3,
                        (float)spp);
   TV_HIP(hipGetLastError());
@@ -1368,6 +1738,33 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
   }
   return TET_OK;
 }
+
+// Whether the vertex terms of n training paths are worth keeping (32 bytes
+// per vertex a path may have): beyond, their lanes walk their own light rays.
+static bool terms_fit(int64_t n, int64_t max_bounces) { return n * max_bounces <= (256ll << 20) / 32; }
+
+// Zeroes the statistics of a call (its passes zero the other counters).
+static void zero_stats(uint32_t* head, hipStream_t st) {
+  constexpr int n = kStatSlots * kLine;
+  hipLaunchKernelGGL(k_zero_u32, dim3((n + 255) / 256), dim3(256), 0, st, head + kStatAt, n);
+}
+
+// The statistics' slots on the host (a stream copy), to be summed once it is complete.
+struct HostStats {
+  uint32_t w[kStatSlots * kLine];
+  hipError_t fetch(const uint32_t* head, hipStream_t st) {
+    return hipMemcpyAsync(w, head + kStatAt, sizeof(w), hipMemcpyDeviceToHost, st);
+  }
+  int64_t sum(int q) const {
+    uint64_t s = 0;
+    for (int k = 0; k < kStatSlots; k++) {
+      uint64_t v;
+      memcpy(&v, w + k * kLine + 2 * q, 8);
+      s += v;
+    }
+    return (int64_t)s;
+  }
+};
 
 static int check_render_opts(const tet_render_opts& o) {
   if (o.max_bounces < 1 || o.transmittance < 0 || o.transmittance > 2 || o.max_steps_per_path < 1 ||
@@ -1474,15 +1871,21 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   int64_t slots = (int64_t)tiles_x * tiles_y * 64;
   if (slots >= (1ll << 31)) return fail(TET_ERR_INVALID_ARG, "render: image too large");
   const int64_t entry_cap =
-      noalloc ? std::min<int64_t>(kMaxEntriesPerPass, ((int64_t)fixed_bytes - 256) / (int64_t)sizeof(RayEntry))
-              : kMaxEntriesPerPass;
+      noalloc ? std::min<int64_t>(kMaxEntriesPerPass, kNoAllocEntries) : kMaxEntriesPerPass;
   if (noalloc && slots > entry_cap)
     return fail(TET_ERR_CAPACITY, "tet_render_noalloc: one sample per pixel of this image does not fit the "
                                   "fixed scratch (" + std::to_string(entry_cap) + " entry records)");
   int64_t pass_cap = std::max<int64_t>(1, std::min<int64_t>(spp, entry_cap / slots));
-  int per_item = (o.samples_per_item <= 0 || o.samples_per_item > pass_cap) ? (int)pass_cap : o.samples_per_item;
-  if (slots * ((pass_cap + per_item - 1) / per_item) >= (1ll << 32))
-    return fail(TET_ERR_INVALID_ARG, "render: too many work items");
+
+  // Light rays are queued and walked after each pass when the step guard is
+  // at its largest value (2^31 - 1: each light walk then runs on its own,
+  // bounded by the tet count, while the guard would count all of a path's
+  // walks together; the estimate is the same unless a path takes more than
+  // 2^31 - 1 steps).  Their terms are added to the pixels apart from the rest
+  // of their samples.
+  const bool defer = o.max_steps_per_path >= 0x7FFFFFFF;
+  if (noalloc && defer)  // room for a light ray per sample beside the entry records
+    while (pass_cap > 1 && (size_t)(slots * pass_cap) * (sizeof(RayEntry) + 4 + sizeof(LightRec)) > fixed_bytes) pass_cap--;
 
   RenderArgs A;
   memset(&A, 0, sizeof(A));
@@ -1490,7 +1893,6 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   if (kind == 0) set_ext(A.ex, g, o);
   A.spp = spp;
   A.pass_start = o.sample_offset;
-  A.per_item = per_item;
   A.max_bounces = o.max_bounces;
   A.transmittance = o.transmittance;
   A.max_steps = (uint32_t)std::min<int64_t>(o.max_steps_per_path, 0x7FFFFFFF);
@@ -1499,16 +1901,6 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   A.tiles_x = tiles_x;
   A.batch = o.batch_items ? (uint32_t)o.batch_items : 64u;
   A.event_wait = o.event_wait ? o.event_wait : 32;
-  // Light rays are queued and walked after each pass, sorted by start tet,
-  // on tet grids without a density model (channels and the radiance cache's
-  // renders included) with analytic light transmittance when the step
-  // guard is at its largest value (2^31 - 1: each light walk then runs on its
-  // own, bounded by the tet count, while the guard would count all of a
-  // path's walks together; the estimate is the same unless a path takes
-  // more than 2^31 - 1 steps).  Their terms are added to the pixels apart
-  // from the rest of their samples.
-  const bool defer = kind == 0 && !model && !noalloc && o.transmittance == 0 && o.max_steps_per_path >= 0x7FFFFFFF;
-  A.accumulate = (pass_cap < spp) || (per_item < pass_cap) || nrc != nullptr || defer;
   if (nrc) {
     A.nrc = nrc;
     A.truncate = nrc->opts.truncate_bounce;
@@ -1521,13 +1913,17 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     A.rec_vertices = kv;
   }
 
+  const bool train_terms = train && defer && terms_fit(n_train, o.max_bounces);
   // scratch: counters, entry records of one pass (then those of the training
-  // paths), image when the output is on the host, training-path records
+  // paths) and their lists, image when the output is on the host,
+  // training-path records
   size_t img_bytes = (size_t)npix * 3 * sizeof(float);
-  size_t ent_bytes = ((size_t)slots * (size_t)pass_cap + (size_t)n_train) * sizeof(RayEntry);
+  size_t n_ent = (size_t)slots * (size_t)pass_cap, list0 = 8 * (size_t)band_size_of(n_ent);
+  size_t ent_bytes = kHeadBytes + (n_ent + (size_t)n_train) * sizeof(RayEntry) + (list0 + (size_t)n_train) * 4;
+  ent_bytes = (ent_bytes + 255) & ~(size_t)255;
   size_t vrec_bytes = (size_t)n_train * (size_t)kv * 48, pl_bytes = (size_t)n_train * 16;
   size_t q_bytes = nrc ? (size_t)slots * (size_t)pass_cap * 36 : 0;  // at most one query per sample
-  size_t scratch = 256 + ent_bytes + (on_device ? 0 : img_bytes) + vrec_bytes + pl_bytes + q_bytes;
+  size_t scratch = ent_bytes + (on_device ? 0 : (img_bytes + 255) & ~(size_t)255) + vrec_bytes + pl_bytes + q_bytes;
   if (noalloc && scratch > fixed_bytes) return fail(TET_ERR_INTERNAL, "tet_render_noalloc: scratch overrun");
   char* sc = noalloc ? fixed : (char*)dev_alloc(scratch);
   if (!sc) return fail(TET_ERR_OUT_OF_MEMORY, "render: scratch");
@@ -1535,16 +1931,17 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     void* p;
     ~Free() { if (p) dev_free(p); }
   } fr_{noalloc ? nullptr : sc};
-  A.counter = (uint32_t*)sc;
-  A.stats = (unsigned long long*)(sc + 64);  // counters: 8 work ranges in sc[0..32), query count at sc[32]
-  RayEntry* entries = (RayEntry*)(sc + 256);
-  A.out = on_device ? out_rgb : (float*)(sc + 256 + ent_bytes);
+  A.head = (uint32_t*)sc;
+  A.entries = (RayEntry*)(sc + kHeadBytes);
+  A.list = (uint32_t*)(A.entries + n_ent + (size_t)n_train);
+  A.train_list0 = (uint32_t)list0;
+  A.out = on_device ? out_rgb : (float*)(sc + ent_bytes);
+  char* tail = sc + ent_bytes + (on_device ? 0 : (img_bytes + 255) & ~(size_t)255);
   if (train) {
-    char* tr = sc + 256 + ent_bytes + (on_device ? 0 : img_bytes);
-    A.vrec = (float4*)tr;
-    A.path_l = (float4*)(tr + vrec_bytes);
+    A.vrec = (float4*)tail;
+    A.path_l = (float4*)(tail + vrec_bytes);
   }
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, (uint32_t*)sc, 64);
+  zero_stats(A.head, st);
 
   // the light-ray queue of a pass (at most 4 light rays per sample, 2^26 in
   // all; a full queue leaves the rest to the tracing lanes) and its sort
@@ -1554,27 +1951,34 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     void* p;
     ~FreeQ() { if (p) dev_free(p); }
   } frq_{nullptr};
-  if (defer) {
-    const uint32_t cap = (uint32_t)std::min<int64_t>(1ll << 26, std::max<int64_t>(1024, slots * pass_cap * 4));
-    // column bundles about as wide as the grid's typical tet: bits per
-    // axis ~ log2(tets) / 3 (8 on a 7 M-tet grid, 9 on 86 M tets)
-    int tet_bits = 0;
-    while (tet_bits < 40 && (int64_t)(1ull << tet_bits) < g->n) tet_bits++;
-    ls.cbits = std::max(4, std::min(11, (tet_bits + 1) / 3));
+  if (defer && noalloc) {  // what the entry records leave of the fixed scratch, walked as queued
+    size_light_queue(A, slots * pass_cap, o);
+    const size_t left = (fixed_bytes - ent_bytes) / sizeof(LightRec);
+    A.lq_chunks = (uint32_t)std::min<size_t>(A.lq_chunks, left / A.lq_chunk);
+    A.lq = (LightRec*)(sc + ent_bytes);
+    A.defer = A.lq_chunks > 0;
+  } else if (defer) {
+    size_light_queue(A, slots * pass_cap + n_train, o);
+    const uint32_t cap = A.lq_chunk * A.lq_chunks;
+    // column bundles about as wide as the grid's typical cell: bits per
+    // axis ~ log2(cells) / 3 (8 on a 7 M-tet grid, 9 on 86 M tets)
+    const int64_t cells = kind == 0 ? g->n : (int64_t)dens->n * dens->n * dens->n;
+    int cell_bits = 0;
+    while (cell_bits < 40 && (int64_t)(1ull << cell_bits) < cells) cell_bits++;
+    ls.cbits = std::max(4, std::min(11, (cell_bits + 1) / 3));
     ls.fbits = (32 - kDepthBits - 2 * ls.cbits) / 2;
     if (rocprim::radix_sort_pairs(nullptr, ls.temp_bytes, (uint32_t*)nullptr, (uint32_t*)nullptr, (uint32_t*)nullptr,
                                   (uint32_t*)nullptr, cap, 0u, 32u, st) != hipSuccess)
       return fail(TET_ERR_DEVICE, "render: light-ray sort size");
-    const size_t head = (size_t)(2 * kMaxTraceBlocks + 64) * 4;  // per-block counts, then their offsets
-    const size_t qb = head + (size_t)cap * sizeof(LightRec) + 4 * (size_t)cap * 4 + ((ls.temp_bytes + 255) & ~size_t(255));
+    const size_t term_bytes = train_terms ? (size_t)n_train * (size_t)o.max_bounces * 32 : 0;
+    const size_t qb = (size_t)cap * sizeof(LightRec) + 4 * (size_t)cap * 4 + ((ls.temp_bytes + 255) & ~size_t(255)) + term_bytes;
     char* q = (char*)dev_alloc(qb);
     if (!q) return fail(TET_ERR_OUT_OF_MEMORY, "render: light-ray queue");
     frq_.p = q;
     A.defer = 1;
-    A.lq_count = (uint32_t*)q;
-    A.lq_cap = cap;
-    A.lq = (LightRec*)(q + head);
-    uint32_t* k = (uint32_t*)(q + head + (size_t)cap * sizeof(LightRec));
+    A.lq = (LightRec*)q;
+    if (train_terms) A.terms = (float4*)(q + qb - term_bytes);
+    uint32_t* k = (uint32_t*)(q + (size_t)cap * sizeof(LightRec));
     ls.keys[0] = k;
     ls.keys[1] = k + cap;
     ls.idx[0] = k + 2 * (size_t)cap;
@@ -1583,30 +1987,30 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   }
 
   if (nrc) {
-    char* qb = sc + 256 + ent_bytes + (on_device ? 0 : img_bytes) + vrec_bytes + pl_bytes;
+    char* qb = tail + vrec_bytes + pl_bytes;
     A.qbuf = (float4*)qb;
     A.qpix = (uint32_t*)(qb + (size_t)slots * (size_t)pass_cap * 32);
-    A.qcount = (uint32_t*)sc + 8;
+    A.qcount = A.head + kQueryAt;
   }
   float ms = 0.0f, ms_trace = 0.0f, ms_cache = 0.0f;
   int rc;
   if (kind == 0 && g->rec32 && o.record_layout != 48) {
     TetMedium32 m{model ? g->mrec32 : g->rec32, g->keys, g->n, g->max_depth, shapes, g->kidx, g->kbits};
-    rc = nrc ? run_passes<TetMedium32, 1>(m, A, o, spp, npix, sc, entries, pass_cap, st, &ms, &ms_trace, &ms_cache,
+    rc = nrc ? run_passes<TetMedium32, 1>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
                                           !noalloc, &ls)
-             : run_passes<TetMedium32, 0>(m, A, o, spp, npix, sc, entries, pass_cap, st, &ms, &ms_trace, &ms_cache,
+             : run_passes<TetMedium32, 0>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
                                           !noalloc, &ls);
   } else if (kind == 0) {
     if (o.record_layout == 32) return fail(TET_ERR_UNSUPPORTED, "render: this grid has no compact records");
     TetMedium m{model ? g->mrec : g->rec, g->keys, g->n, g->max_depth, shapes, g->kidx, g->kbits};
-    rc = nrc ? run_passes<TetMedium, 1>(m, A, o, spp, npix, sc, entries, pass_cap, st, &ms, &ms_trace, &ms_cache,
+    rc = nrc ? run_passes<TetMedium, 1>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
                                         !noalloc, &ls)
-             : run_passes<TetMedium, 0>(m, A, o, spp, npix, sc, entries, pass_cap, st, &ms, &ms_trace, &ms_cache,
+             : run_passes<TetMedium, 0>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
                                         !noalloc, &ls);
   } else {
     VoxelMedium m{dens->data, dens->n, dens->density_scale};
-    rc = run_passes<VoxelMedium, 0>(m, A, o, spp, npix, sc, entries, pass_cap, st, &ms, &ms_trace, &ms_cache,
-                                    !noalloc);
+    rc = run_passes<VoxelMedium, 0>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
+                                    !noalloc, &ls);
   }
   if (rc) return rc;
   if (noalloc) return TET_OK;
@@ -1632,23 +2036,23 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     TV_HIP(hipEventElapsedTime(&tms, t0, t1));
     ms += tms;
   }
-  unsigned long long hs[6] = {0, 0, 0, 0, 0, 0};
-  TV_HIP(hipMemcpyAsync(hs, A.stats, sizeof(hs), hipMemcpyDeviceToHost, st));
+  HostStats hs;
+  TV_HIP(hs.fetch(A.head, st));
   if (!on_device) TV_HIP(hipMemcpyAsync(out_rgb, A.out, img_bytes, hipMemcpyDeviceToHost, st));
   TV_HIP(hipStreamSynchronize(st));
   if (stats) {
-    stats->tet_steps = (int64_t)hs[0];
-    stats->null_collisions = (int64_t)hs[1];
-    stats->real_collisions = (int64_t)hs[2];
-    stats->escapes = (int64_t)hs[3];
-    stats->truncated = (int64_t)hs[4];
+    stats->tet_steps = hs.sum(0);
+    stats->null_collisions = hs.sum(1);
+    stats->real_collisions = hs.sum(2);
+    stats->escapes = hs.sum(3);
+    stats->truncated = hs.sum(4);
     stats->ms = ms;
     stats->trace_ms = ms_trace;
     stats->cache_ms = ms_cache;
-    stats->cache_queries = (int64_t)hs[5];
+    stats->cache_queries = hs.sum(5);
     stats->cache_records = records;
     stats->cache_loss = loss;
-    stats->light_rays_queued = ls.queued;
+    stats->light_rays_queued = hs.sum(6);
   }
   return TET_OK;
 }
@@ -1675,7 +2079,6 @@ int trace_training_paths(const tet_grid* g, const tet_camera* cam, const tet_med
   set_scene(A, cam, medm, light);
   set_ext(A.ex, g, o);
   A.spp = 1;
-  A.per_item = 1;
   A.max_bounces = o.max_bounces;
   A.transmittance = o.transmittance;
   A.max_steps = (uint32_t)std::min<int64_t>(o.max_steps_per_path, 0x7FFFFFFF);
@@ -1689,27 +2092,39 @@ int trace_training_paths(const tet_grid* g, const tet_camera* cam, const tet_med
   A.rec_vertices = kv;
   A.vrec = vrec;
   A.path_l = path_l;
-  size_t ent_bytes = (size_t)n_paths * sizeof(RayEntry);
-  char* sc = (char*)dev_alloc(256 + ent_bytes);
+  char* sc = (char*)dev_alloc(kHeadBytes + (size_t)n_paths * sizeof(RayEntry) + 32 * (size_t)band_size_of((uint64_t)n_paths));
   if (!sc) return fail(TET_ERR_OUT_OF_MEMORY, "training paths: scratch");
   struct Free {
     void* p;
     ~Free() { dev_free(p); }
-  } fr_{sc};
-  A.counter = (uint32_t*)sc;
-  A.stats = (unsigned long long*)(sc + 64);
-  RayEntry* entries = (RayEntry*)(sc + 256);
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, (uint32_t*)sc, 64);
+  };
+  Free fr_{sc};
+  A.head = (uint32_t*)sc;
+  A.entries = (RayEntry*)(sc + kHeadBytes);
+  A.list = (uint32_t*)(A.entries + n_paths);
+  zero_stats(A.head, st);
+  LightSort ls;  // (unsorted: few rays)
+  memset(&ls, 0, sizeof(ls));
+  Free fq_{nullptr};
+  if (o.max_steps_per_path >= 0x7FFFFFFF && terms_fit(n_paths, o.max_bounces)) {
+    size_light_queue(A, n_paths, o);
+    const size_t qb = (size_t)A.lq_chunk * A.lq_chunks * sizeof(LightRec);
+    fq_.p = dev_alloc(qb + (size_t)n_paths * (size_t)o.max_bounces * 32);
+    if (!fq_.p) return fail(TET_ERR_OUT_OF_MEMORY, "training paths: light-ray queue");
+    A.defer = 1;
+    A.lq = (LightRec*)fq_.p;
+    A.terms = (float4*)((char*)fq_.p + qb);
+  }
   float ms = 0.0f, ms_trace = 0.0f, ms_cache = 0.0f;
   int rc;
   const bool model = g->model != 0;
   if (g->rec32 && o.record_layout != 48) {
     TetMedium32 m{model ? g->mrec32 : g->rec32, g->keys, g->n, g->max_depth, shapes, g->kidx, g->kbits};
-    rc = run_passes<TetMedium32, 2>(m, A, o, 1, 0, sc, entries, 1, st, &ms, &ms_trace, &ms_cache);
+    rc = run_passes<TetMedium32, 2>(m, A, o, 1, 0, 1, st, &ms, &ms_trace, &ms_cache, true, &ls);
   } else {
     if (o.record_layout == 32) return fail(TET_ERR_UNSUPPORTED, "training paths: this grid has no compact records");
     TetMedium m{model ? g->mrec : g->rec, g->keys, g->n, g->max_depth, shapes, g->kidx, g->kbits};
-    rc = run_passes<TetMedium, 2>(m, A, o, 1, 0, sc, entries, 1, st, &ms, &ms_trace, &ms_cache);
+    rc = run_passes<TetMedium, 2>(m, A, o, 1, 0, 1, st, &ms, &ms_trace, &ms_cache, true, &ls);
   }
   if (rc) return rc;
   TV_HIP(hipStreamSynchronize(st));
@@ -1729,7 +2144,6 @@ int render_grid(const tet_grid* g, const tet_camera* cam, const tet_medium* m, c
 // when the library's code is loaded on it, kept until the process ends).  In
 // host code `scratch` only names the symbol; its device address comes from
 // hipGetSymbolAddress, looked up once per device.
-constexpr size_t kNoAllocBytes = (size_t(64) << 20) + 256;  // counters, then 2^21 entry records
 static __device__ __align__(256) char scratch[kNoAllocBytes];
 constexpr int kMaxDevices = 64;
 
@@ -1787,12 +2201,13 @@ struct BatchState {
   int device = 0;
   int n = 0;
   bool use32 = true;
-  bool ext = false;  // some scene carries channels or a density model
+  bool ext = false;    // some scene carries channels or a density model
+  bool model = false;  // some grid carries a density model
   const uint32_t* shapes = nullptr;
   tet_render_opts o;
   SceneDesc* pinned = nullptr;  // host staging of the scene table (page-locked)
   SceneDesc* table = nullptr;   // device scene table
-  char* scratch = nullptr;      // counters and statistics, then the entry records
+  char* scratch = nullptr;      // counters and statistics, the entry records, their lists
   RenderArgs A;
   uint64_t total_px = 0;
   int grid = 1, bs = 256;
@@ -1840,7 +2255,7 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
   if (!B->shapes) return fail(TET_ERR_DEVICE, "render batch: shape table");
   if (hipGetDevice(&B->device) != hipSuccess) return fail(TET_ERR_DEVICE, "render batch: no device");
   std::vector<SceneDesc> host((size_t)n);
-  uint64_t item = 0, entry = 0, px = 0;
+  uint64_t entry = 0, px = 0;
   for (int i = 0; i < n; i++) {
     SceneDesc& S = host[i];
     memset(&S, 0, sizeof(S));
@@ -1857,8 +2272,6 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
     int64_t tiles_y = (cams[i].height + 7) / 8;
     uint64_t items = (uint64_t)S.tiles_x * (uint64_t)tiles_y * 64ull * (uint64_t)spp[i];
     S.s0 = (uint32_t)o.sample_offset;
-    S.items = (uint32_t)std::min<uint64_t>(items, 0xFFFFFFFFull);
-    S.item0 = (uint32_t)std::min<uint64_t>(item, 0xFFFFFFFFull);
     S.entry0 = entry;
     S.pix0 = px;
     const tet_grid* g = grids[i];
@@ -1866,70 +2279,80 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
     else S.rec = use32 ? (const void*)g->rec32 : (const void*)g->rec;
     set_ext(S.ex, g, o);
     if (o.channels || g->model) B->ext = true;
+    if (g->model) B->model = true;
     S.keys = g->keys;
     S.kidx = g->kidx;
     S.kbits = g->kbits;
     S.n = g->n;
     S.dmax = g->max_depth;
     S.out = outs[i];
-    item += (items + 63) / 64 * 64;
     entry += items;
     px += (uint64_t)cams[i].width * (uint64_t)cams[i].height;
-    if (items >= (1ull << 32) || item >= (1ull << 32) || entry >= (1ull << 32))
+    if (items >= (1ull << 32) || entry >= (1ull << 32))
       return fail(TET_ERR_INVALID_ARG, "render batch: more than 2^32 samples in one batch");
   }
   B->total_px = px;
   B->table = (SceneDesc*)dev_alloc(sizeof(SceneDesc) * (size_t)n);
-  B->scratch = (char*)dev_alloc(256 + (size_t)entry * sizeof(RayEntry));
+  RenderArgs& A = B->A;
+  memset(&A, 0, sizeof(A));
+  const size_t ent_bytes =
+      (kHeadBytes + (size_t)entry * sizeof(RayEntry) + 32 * (size_t)band_size_of(entry) + 255) & ~(size_t)255;
+  size_t lq_bytes = 0;
+  if (o.max_steps_per_path >= 0x7FFFFFFF) {  // light rays queued, walked as queued
+    size_light_queue(A, (int64_t)entry, o);
+    lq_bytes = (size_t)A.lq_chunk * A.lq_chunks * sizeof(LightRec);
+  }
+  B->scratch = (char*)dev_alloc(ent_bytes + lq_bytes);
   if (hipHostMalloc((void**)&B->pinned, sizeof(SceneDesc) * (size_t)n, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     B->pinned = nullptr;
   }
   if (!B->table || !B->scratch || !B->pinned) return fail(TET_ERR_OUT_OF_MEMORY, "render batch: device memory");
   memcpy(B->pinned, host.data(), sizeof(SceneDesc) * (size_t)n);
-  RenderArgs& A = B->A;
-  memset(&A, 0, sizeof(A));
+  A.defer = lq_bytes != 0;
+  A.lq = (LightRec*)(B->scratch + ent_bytes);
   A.max_bounces = o.max_bounces;
   A.transmittance = o.transmittance;
   A.max_steps = (uint32_t)std::min<int64_t>(o.max_steps_per_path, 0x7FFFFFFF);
-  A.per_item = 1;
-  A.items = (uint32_t)item;
-  A.range_size = (uint32_t)(((item + 7) / 8 + 63) / 64 * 64);
-  A.batch = 64;  // a wave's batch stays within one scene (scenes' items are padded to 64)
+  A.batch = 64;
   A.event_wait = o.event_wait ? o.event_wait : 32;
-  A.accumulate = 1;
-  A.counter = (uint32_t*)B->scratch;
-  A.stats = (unsigned long long*)(B->scratch + 64);
-  A.entries = (const RayEntry*)(B->scratch + 256);
+  A.head = (uint32_t*)B->scratch;
+  A.entries = (RayEntry*)(B->scratch + kHeadBytes);
+  A.list = (uint32_t*)(A.entries + entry);
+  A.band_size = band_size_of(entry);
+  A.chunk_blocks = chunk_blocks_of(entry);
   A.scenes = B->table;
   A.nscenes = n;
   A.total_entries = entry;
   B->bs = o.block_size ? o.block_size : 256;
   int bpc = o.blocks_per_cu ? o.blocks_per_cu : 8;
-  B->grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)cu_count() * bpc, ((int64_t)item + B->bs - 1) / B->bs));
+  B->grid = (int)std::max<int64_t>(1, std::min<int64_t>((int64_t)cu_count() * bpc, ((int64_t)entry + B->bs - 1) / B->bs));
   return TET_OK;
 }
 
 // The frame's kernels (no host synchronisation, no memset: capturable).
 static int batch_enqueue(const BatchState* B, hipStream_t st) {
   const RenderArgs& A = B->A;
-  RayEntry* entries = (RayEntry*)(B->scratch + 256);
-  unsigned pblocks = (unsigned)((B->total_px + 255) / 256);
-  unsigned eblocks = (unsigned)((A.total_entries + 255) / 256);
-  hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, (uint32_t*)B->scratch, 64);
-  hipLaunchKernelGGL(k_batch_images, dim3(pblocks), dim3(256), 0, st, (const SceneDesc*)B->table, B->n, B->total_px, 1);
+  hipLaunchKernelGGL(k_zero_u32, dim3((kPassWords + 255) / 256), dim3(256), 0, st, A.head, kPassWords);
+  zero_stats(A.head, st);
   if (B->use32) {
     TetMedium32 m{nullptr, nullptr, 0, 0, B->shapes, nullptr, 0};
-    hipLaunchKernelGGL(k_raygen_batch<TetMedium32>, dim3(eblocks), dim3(256), 0, st, A, m, entries);
+    launch_first<TetMedium32, true>(A, m, B->model, st);
     if (B->ext) hipLaunchKernelGGL((k_render<TetMedium32, 5, 0, true, true>), dim3((unsigned)B->grid), dim3(B->bs), 0, st, A, m);
     else hipLaunchKernelGGL((k_render<TetMedium32, 5, 0, true>), dim3((unsigned)B->grid), dim3(B->bs), 0, st, A, m);
   } else {
     TetMedium m{nullptr, nullptr, 0, 0, B->shapes, nullptr, 0};
-    hipLaunchKernelGGL(k_raygen_batch<TetMedium>, dim3(eblocks), dim3(256), 0, st, A, m, entries);
+    launch_first<TetMedium, true>(A, m, B->model, st);
     if (B->ext) hipLaunchKernelGGL((k_render<TetMedium, 5, 0, true, true>), dim3((unsigned)B->grid), dim3(B->bs), 0, st, A, m);
     else hipLaunchKernelGGL((k_render<TetMedium, 5, 0, true>), dim3((unsigned)B->grid), dim3(B->bs), 0, st, A, m);
   }
-  hipLaunchKernelGGL(k_batch_images, dim3(pblocks), dim3(256), 0, st, (const SceneDesc*)B->table, B->n, B->total_px, 0);
+  const dim3 px_grid((unsigned)((B->total_px + 255) / 256));
+  hipLaunchKernelGGL(k_resolve_batch, px_grid, dim3(256), 0, st, A, B->total_px);
+  if (A.defer) {
+    if (B->use32) launch_light<TetMedium32, true>(A, TetMedium32{nullptr, nullptr, 0, 0, B->shapes, nullptr, 0}, B->model, nullptr, 0, st);
+    else launch_light<TetMedium, true>(A, TetMedium{nullptr, nullptr, 0, 0, B->shapes, nullptr, 0}, B->model, nullptr, 0, st);
+    hipLaunchKernelGGL(k_scale_batch, px_grid, dim3(256), 0, st, A, B->total_px);
+  }
   TV_HIP(hipGetLastError());
   return TET_OK;
 }
@@ -1957,18 +2380,18 @@ static int batch_run(BatchState* B, const uint64_t* seeds, hipStream_t st, tet_r
     return rc;
   }
   TV_HIP(hipEventRecord(e1, st));
-  unsigned long long hs[6] = {0, 0, 0, 0, 0, 0};
-  TV_HIP(hipMemcpyAsync(hs, B->A.stats, sizeof(hs), hipMemcpyDeviceToHost, st));
+  HostStats hs;
+  TV_HIP(hs.fetch(B->A.head, st));
   TV_HIP(hipStreamSynchronize(st));
   float ms = 0.0f;
   TV_HIP(hipEventElapsedTime(&ms, e0, e1));
   if (stats) {
     memset(stats, 0, sizeof(*stats));
-    stats->tet_steps = (int64_t)hs[0];
-    stats->null_collisions = (int64_t)hs[1];
-    stats->real_collisions = (int64_t)hs[2];
-    stats->escapes = (int64_t)hs[3];
-    stats->truncated = (int64_t)hs[4];
+    stats->tet_steps = hs.sum(0);
+    stats->null_collisions = hs.sum(1);
+    stats->real_collisions = hs.sum(2);
+    stats->escapes = hs.sum(3);
+    stats->truncated = hs.sum(4);
     stats->ms = ms;
     stats->trace_ms = ms;
   }

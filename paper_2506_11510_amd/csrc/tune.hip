@@ -158,7 +158,7 @@ int autotune(const tet_grid* g, const tet_camera* cam, const tet_medium* med, co
     }
   }
   // candidate values per option (record layouts only those the grid has)
-  std::vector<std::vector<int32_t>> cand = {{4, 5, 6}, {16, 32, 48}, {32, 64, 128}, {128, 256}, {48}};
+  std::vector<std::vector<int32_t>> cand = {{4, 5}, {16, 32, 48}, {32, 64, 128}, {128, 256}, {48}};
   if (g->rec32) cand[4] = {32, 48};
   tet_render_opts cur = base;
   if (!cur.waves_per_simd) cur.waves_per_simd = 5;
