@@ -315,9 +315,9 @@ __device__ inline int64_t locate_point(const uint64_t* __restrict__ keys, const 
 // face is never crossed), and 0 for all 9 when a dot product is too small
 // for exit_face's bounds (|dir_N . d| < 2^-40, or NaN, or d = 0), which makes every
 // step of the segment take its general path.
-// Entry k of the block's lane i is at k * kTabRow + i: a lane's reads stay in
-// its own bank whichever entry it reads.
-constexpr int kTabRow = 256;  // lanes (the largest block)
+// Each wave has a table of its own, entry k of lane i at k * kTabRow + i: a
+// lane's reads stay in its own bank whichever entry it reads.
+constexpr int kTabRow = 64;
 constexpr int kTabDot = 9, kTabDen = 18, kTabRows = 27;
 
 struct SegDirs {
@@ -742,6 +742,8 @@ __device__ inline void add_stats(const RenderArgs& A, const uint32_t (&v)[N]) {
   }
 }
 
+constexpr uint32_t kFirstBlock = 64;
+
 // Camera rays and their walk to the first real collision, one thread per
 // entry record in record order: the samples of a pixel are neighbouring
 // lanes, which walk the same tets, so a wave reads a few record lines per step
@@ -755,16 +757,16 @@ __device__ inline void add_stats(const RenderArgs& A, const uint32_t (&v)[N]) {
 // 2.8 of 5 resident waves per SIMD on average).  A block lists its colliding samples with one atomic on its
 // band's count.  MODEL: the grid carries a density model.
 template <class Med, bool BATCH, bool MODEL>
-__global__ __launch_bounds__(256) void k_first(RenderArgs A, Med med) {
-  __shared__ float s_tab[Med::kTabled ? kTabRows * kTabRow : 1];
-  __shared__ uint32_t s_n[4], s_base;
-  float* tab = s_tab + threadIdx.x;
+__global__ __launch_bounds__(kFirstBlock) void k_first(RenderArgs A, Med med) {
+  __shared__ float s_tab[Med::kTabled ? kTabRows * kFirstBlock : 1];
+  float* tab = s_tab + (threadIdx.x >> 6) * (kTabRows * kTabRow) + (threadIdx.x & 63u);
   const int lane = __lane_id();
   // the first blocks trace the training paths that go with an image
   const bool with = !BATCH && blockIdx.x < A.train_blocks, train = with || (!BATCH && A.train);
   const uint32_t blk = blockIdx.x - (with ? 0u : A.train_blocks);
-  const uint32_t band = with ? 0u : blk & 7u, j = blk >> 3, g = A.chunk_blocks;
-  const uint64_t e = (with ? (uint64_t)blk : ((uint64_t)(j / g) * 8u + band) * g + j % g) * 256u + threadIdx.x;
+  const uint32_t band = with ? 0u : blk & 7u, j = blk >> 3, g = A.chunk_blocks, round = j / g;
+  const uint32_t turn = (band + ((round * 0x9E3779B9u) >> 29)) & 7u;  // (a row of the image may hold a multiple of 8 chunks)
+  const uint64_t e = (with ? (uint64_t)blk : ((uint64_t)round * 8u + turn) * g + j % g) * kFirstBlock + threadIdx.x;
   const uint64_t total = BATCH ? A.total_entries : (with ? A.train_items : (uint64_t)A.slots * (uint64_t)A.pass_spp);
   RayEntry* const entries = A.entries + (with ? A.train_ent0 : 0u);
   uint32_t n_stat[5] = {0, 0, 0, 0, 0};  // steps, null collisions, real collisions, escapes, truncated
@@ -877,17 +879,13 @@ __global__ __launch_bounds__(256) void k_first(RenderArgs A, Med med) {
     }
   }
   const unsigned long long m = __ballot(hit);
-  if (lane == 0) s_n[threadIdx.x >> 6] = (uint32_t)__popcll(m);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t n = s_n[0] + s_n[1] + s_n[2] + s_n[3];
-    s_base = n ? atomicAdd(A.head + kCountAt + (with ? kTrainList : (int)band) * kLine, n) : 0u;
-  }
-  __syncthreads();
-  if (hit) {
-    uint32_t at = s_base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
-    for (uint32_t w = 0; w < (threadIdx.x >> 6); w++) at += s_n[w];
-    A.list[(with ? (uint64_t)A.train_list0 : (uint64_t)band * A.band_size) + at] = (uint32_t)e;
+  if (m) {
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(A.head + kCountAt + (with ? kTrainList : (int)band) * kLine, (uint32_t)__popcll(m));
+    base = __shfl(base, 0);
+    if (hit)
+      A.list[(with ? (uint64_t)A.train_list0 : (uint64_t)band * A.band_size) + base +
+             (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)e;
   }
   add_stats(A, n_stat);
 }
@@ -904,11 +902,11 @@ __global__ __launch_bounds__(256) void k_first(RenderArgs A, Med med) {
 // (the plain variant carries none of that code).
 template <class Med, int W, int NRC, bool BATCH = false, bool EXT = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) void k_render(RenderArgs A, Med med) {
-  __shared__ float s_tab[Med::kTabled ? kTabRows * kTabRow : 1];
+  __shared__ float s_tab[Med::kTabled ? kTabRows * 256 : 1];
   // per wave: its queue chunk's first record, records used, light rays queued
   // (volatile: different lanes of the wave read and write them in turn)
   __shared__ volatile uint32_t s_lq[4][3];
-  float* tab = s_tab + threadIdx.x;
+  float* tab = s_tab + (threadIdx.x >> 6) * (kTabRows * kTabRow) + (threadIdx.x & 63u);
   const int lane = __lane_id();
   int mode = M_FETCH;
   uint32_t pix = 0, ent = 0;  // ent: the sample's entry record
@@ -1371,14 +1369,15 @@ template <class Med, bool BATCH, bool EXT>
 __global__ __launch_bounds__(256) void k_light(RenderArgs A, Med med, const uint32_t* __restrict__ order,
                                                uint32_t n_sorted, SegDirs sun) {
   constexpr bool SHARED = !BATCH;  // one direction for all rays
-  __shared__ float s_tab[Med::kTabled ? (SHARED ? 9 : kTabRows) * kTabRow : 1];
+  constexpr int ROWS = SHARED ? 9 : kTabRows;
+  __shared__ float s_tab[Med::kTabled ? ROWS * 256 : 1];
   __shared__ float s_dir[18];
   if (SHARED && threadIdx.x < 9) {
     s_dir[threadIdx.x] = sun.r[threadIdx.x];
     s_dir[9 + threadIdx.x] = sun.d[threadIdx.x];
   }
   __syncthreads();
-  float* tab = s_tab + threadIdx.x;
+  float* tab = s_tab + (threadIdx.x >> 6) * (ROWS * kTabRow) + (threadIdx.x & 63u);
   const uint32_t n = order ? n_sorted : min(A.head[kChunkAt], A.lq_chunks) * A.lq_chunk;
   uint32_t total = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
@@ -1550,7 +1549,7 @@ static int cu_count() {
 constexpr int64_t kMaxEntriesPerPass = 1ll << 25;  // 1 GiB of entry records
 // tet_render_noalloc's fixed scratch: counters, 2^21 entry records, their lists
 constexpr int64_t kNoAllocEntries = 1ll << 21;
-constexpr int64_t kListSlack = 8 * 64 * 256;  // the lists' last, incomplete round of chunks
+constexpr int64_t kListSlack = 8 * 16384;  // the lists' last, incomplete round of chunks
 constexpr size_t kNoAllocBytes = (size_t)kNoAllocEntries * sizeof(RayEntry) + (size_t)(kNoAllocEntries + kListSlack) * 4 + kHeadBytes + 256;
 // Sort buffers of the deferred light rays (keys and positions, both ways)
 // and the sort's own scratch.
@@ -1615,24 +1614,25 @@ static void size_light_queue(RenderArgs& A, int64_t samples, const tet_render_op
 
 // The eight lists of ne entry records: blocks per chunk (at least 16 chunks
 // per list where there are blocks enough) and records per list.
+constexpr uint32_t kMostChunk = 16384;  // entry records
 static uint32_t chunk_blocks_of(uint64_t ne) {
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(64, (ne + 255) / 256 / 128));
+  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(kMostChunk, ne / 128) / kFirstBlock);
 }
 static uint32_t band_size_of(uint64_t ne) {
-  const uint64_t g = chunk_blocks_of(ne), chunks = ((ne + 255) / 256 + g - 1) / g;
-  return (uint32_t)((chunks + 7) / 8 * g * 256);
+  const uint64_t g = chunk_blocks_of(ne) * (uint64_t)kFirstBlock, chunks = (ne + g - 1) / g;
+  return (uint32_t)((chunks + 7) / 8 * g);
 }
 
 template <class Med, bool BATCH>
 static void launch_first(const RenderArgs& P, const Med& med, bool model, hipStream_t st) {
-  const unsigned grid = P.train_blocks + 8u * (P.band_size / 256u);
+  const unsigned grid = P.train_blocks + 8u * (P.band_size / kFirstBlock);
   if constexpr (!std::is_same<Med, VoxelMedium>::value) {
     if (model) {
-      hipLaunchKernelGGL((k_first<Med, BATCH, true>), dim3(grid), dim3(256), 0, st, P, med);
+      hipLaunchKernelGGL((k_first<Med, BATCH, true>), dim3(grid), dim3(kFirstBlock), 0, st, P, med);
       return;
     }
   }
-  hipLaunchKernelGGL((k_first<Med, BATCH, false>), dim3(grid), dim3(256), 0, st, P, med);
+  hipLaunchKernelGGL((k_first<Med, BATCH, false>), dim3(grid), dim3(kFirstBlock), 0, st, P, med);
 }
 
 // The tracing kernel at an occupancy target.  Five waves per SIMD fit beside
@@ -1698,7 +1698,7 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
     P.chunk_blocks = chunk_blocks_of(ne);
     hipLaunchKernelGGL(k_zero_u32, dim3((kPassWords + 255) / 256), dim3(256), 0, st, A.head, kPassWords);
     if (timed) TV_HIP(hipEventRecord(t0, st));
-    P.train_blocks = (P.train_items + 255) / 256;
+    P.train_blocks = (P.train_items + kFirstBlock - 1) / kFirstBlock;
     P.train_blocks = (P.train_blocks + 7) / 8 * 8;
     launch_first<Med, false>(P, med, A.ex.model != 0, st);
     int64_t grid = (int64_t)cu_count() * bpc;
