@@ -292,8 +292,8 @@ __device__ __attribute__((noinline)) float exp_neg(float x) {
 
 // (cos, sin)(2 pi u) for u in [0, 1): quadrant q = round(4u), w = u - q/4
 // (exact), theta = 2 pi w in FP64 (|theta| <= pi/4), Taylor polynomials
-// through degree 18 / 17 (truncation < 1e-19), rotated by q.
-__device__ __attribute__((noinline)) void sincos_2pi(float u, float& c, float& s) {
+// through degree 18 / 17 (truncation < 1e-19), rotated by q; unrounded.
+__device__ inline void sincos_2pi_f64(float u, double& c, double& s) {
   const int q = (int)(u * 4.0f + 0.5f);
   const float w = u - (float)q * 0.25f;
   const double th = (double)w * 6.283185307179586;
@@ -317,10 +317,18 @@ __device__ __attribute__((noinline)) void sincos_2pi(float u, float& c, float& s
   pc = pc * z + 1.0 / 24.0;
   pc = pc * z - 0.5;
   pc = pc * z + 1.0;
-  const float sn = (float)(th * ps), cs = (float)pc;
+  const double sn = th * ps;
   const int r = q & 3;
-  c = r == 0 ? cs : (r == 1 ? 0.0f - sn : (r == 2 ? 0.0f - cs : sn));
-  s = r == 0 ? sn : (r == 1 ? cs : (r == 2 ? 0.0f - sn : 0.0f - cs));
+  c = r == 0 ? pc : (r == 1 ? 0.0 - sn : (r == 2 ? 0.0 - pc : sn));
+  s = r == 0 ? sn : (r == 1 ? pc : (r == 2 ? 0.0 - sn : 0.0 - pc));
+}
+
+// The same rounded once.
+__device__ __attribute__((noinline)) void sincos_2pi(float u, float& c, float& s) {
+  double cd, sd;
+  sincos_2pi_f64(u, cd, sd);
+  c = (float)cd;
+  s = (float)sd;
 }
 
 // Henyey-Greenstein density of the cosine mu between successive propagation

@@ -39,12 +39,15 @@ __device__ inline f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
 __device__ inline bf16x8 as_bf(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ inline u32x4 as_u4(bf16x8 v) { return __builtin_bit_cast(u32x4, v); }
 
-// bfloat16 bits of a finite x, rounded to nearest, ties to even.
-__device__ inline uint32_t bf16_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+// Two finite values as bfloat16, rounded to nearest, ties to even (the
+// first in the low half): one instruction.
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+__device__ inline uint32_t pack2(float a, float b) {
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-__device__ inline uint32_t pack2(float a, float b) { return bf16_rne(a) | (bf16_rne(b) << 16); }
+__device__ inline uint32_t bf16_rne(float x) { return pack2(x, 0.0f) & 0xFFFFu; }
 __device__ inline bool bf16_positive(uint16_t h) { return __uint_as_float((uint32_t)h << 16) > 0.0f; }
 
 __host__ __device__ constexpr int kmap(int ks, int g, int e) { return 32 * ks + 16 * (e >> 2) + 4 * g + (e & 3); }
@@ -94,30 +97,60 @@ __global__ void k_nrc_pack(const float* __restrict__ P, char* __restrict__ net) 
 }
 
 // ---------------------------------------------------------------- encoding
-// Features 8c..8c+7 (c = 0..11) of one sample: sin / cos (2^k pi p_a) for
-// c < 9 (axis c / 3, k = 4 (c % 3) .. +3), then d and the normalised
-// extinction, then zeros.  2^k p is exact, and so is its reduction modulo 2,
-// r; sin / cos (pi r) = sin / cos (2 pi (r / 2)).
-__device__ inline bf16x8 feat_chunk(int c, float px, float py, float pz, float dx, float dy, float dz, float sigma,
-                                    double lref) {
-  u32x4 v = {0u, 0u, 0u, 0u};
-  if (c < 9) {
-    float x = c < 3 ? px : (c < 6 ? py : pz);
-    int k0 = 4 * (c % 3);
+// Features 8c..8c+7 of one sample, c < 9: sin / cos (2^k pi p_a), axis
+// a = c / 3, k = 4 (c % 3) .. +3.  2^k p is exact, and so is its reduction
+// modulo 2, r; sin / cos (pi r) = sin / cos (2 pi (r / 2)) in FP64 for the
+// first k, by angle doubling for the other three (each doubles the absolute
+// error of ~1e-16, so the FP32 roundings are those of the direct series but
+// within 1e-15 of a tie; 9 series per 64 samples and lane instead of 48).
+__device__ inline bf16x8 feat_waves(int c, float px, float py, float pz) {
+  const float x = c < 3 ? px : (c < 6 ? py : pz);
+  const float y = ldexpf(x, 4 * (c % 3));
+  const float r = y - 2.0f * floorf(y * 0.5f);
+  double cs, sn;
+  sincos_2pi_f64(r * 0.5f, cs, sn);
+  u32x4 v;
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      float y = ldexpf(x, k0 + j);
-      float r = y - 2.0f * floorf(y * 0.5f);
-      float cs, sn;
-      sincos_2pi(r * 0.5f, cs, sn);
-      v[j] = pack2(sn, cs);
-    }
-  } else if (c == 9) {
-    float sn = (float)(log1p((double)sigma) / lref);
-    v[0] = pack2(dx, dy);
-    v[1] = pack2(dz, sn);
+  for (int j = 0; j < 4; j++) {
+    v[j] = pack2((float)sn, (float)cs);
+    const double s2 = 2.0 * (sn * cs);
+    cs = 1.0 - 2.0 * (sn * sn);
+    sn = s2;
   }
   return as_bf(v);
+}
+
+// The normalised extinction of one sample.
+__device__ inline float feat_sigma(float sigma, double lref) { return (float)(log1p((double)sigma) / lref); }
+
+__device__ inline float shfl_f(float x, int lane) { return __shfl(x, lane, 64); }
+
+// The layer-0 operand of 64 samples, lane l given sample l: column block cb,
+// row r of the operand is sample 16 cb + r, and lane group g holds the chunks
+// 4 ks + g.  Chunk 8 of column block g is made by lane group g, chunk 9 (d and
+// the normalised extinction) by each sample's own lane, so no lane idles.
+__device__ inline void feat_operand(float px, float py, float pz, float dx, float dy, float dz, float sn, int lane,
+                                    bf16x8 (&X)[4][3]) {
+  const int r = lane & 15, g = lane >> 4;
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  const u32x4 last = as_u4(feat_waves(8, px, py, pz));  // of the lane's own sample
+  const uint32_t w0 = pack2(dx, dy), w1 = pack2(dz, sn);
+#pragma unroll
+  for (int cb = 0; cb < 4; cb++) {
+    const int from = 16 * cb + r;
+    const float x = shfl_f(px, from), y = shfl_f(py, from), z = shfl_f(pz, from);
+    X[cb][0] = feat_waves(g, x, y, z);
+    X[cb][1] = feat_waves(4 + g, x, y, z);
+    u32x4 v = zero;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+      const uint32_t a = (uint32_t)__shfl((int)last[j], from, 64);
+      const uint32_t b = j == 0 ? (uint32_t)__shfl((int)w0, from, 64) : (j == 1 ? (uint32_t)__shfl((int)w1, from, 64) : 0u);
+      v[j] = g == 0 ? a : (g == 1 ? b : 0u);
+    }
+    X[cb][2] = as_bf(v);
+    __builtin_amdgcn_sched_barrier(0);  // one block at a time: four at once take 252 registers
+  }
 }
 
 __device__ inline bf16x8 feat_chunk_mem(const float* f, int c) {
@@ -203,9 +236,13 @@ struct NrcQueryArgs {
 };
 
 // Mode 0: network outputs at explicit points.  Mode 1: a render pass's
-// queries; each adds beta * max(y, 0) to its pixel.
+// queries; each adds beta * max(y, 0) to its pixel.  Bound by the encoding's
+// VALU work, not by its 152 matrix products per 64 queries (2,432 cycles):
+// 300,007 points took 82 us with a series per sine/cosine pair and integer
+// bfloat16 rounding, 30 us with 9 series per lane, angle doubling and the
+// packed conversion, at the 4 waves per SIMD that the weights' LDS allows.
 template <int MODE>
-__global__ __launch_bounds__(256) void k_nrc_query(NrcQueryArgs Q) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_nrc_query(NrcQueryArgs Q) {
   __shared__ u32x4 s_frag[kNrcFwdFrags * 64];
   __shared__ float s_bias[kNrcBias];
   {
@@ -220,40 +257,20 @@ __global__ __launch_bounds__(256) void k_nrc_query(NrcQueryArgs Q) {
   const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
   const int64_t count = MODE == 1 ? (int64_t)min((uint64_t)*Q.qcount, (uint64_t)Q.count) : Q.count;
   for (int64_t base = wave * 64; base < count; base += nwaves * 64) {
-    float p[4][3], d[4][3], sg[4], beta[4];
-    bool valid[4];
-    bool any = false;
-#pragma unroll
-    for (int cb = 0; cb < 4; cb++) {
-      int64_t n = base + 16 * cb + r;
-      valid[cb] = n < count;
-      float4 a = make_float4(0, 0, 0, 0), b = a;
-      if (valid[cb]) {
-        if (MODE == 0) {
-          a = make_float4(Q.pos[3 * n], Q.pos[3 * n + 1], Q.pos[3 * n + 2], Q.sigma[n]);
-          b = make_float4(Q.dir[3 * n], Q.dir[3 * n + 1], Q.dir[3 * n + 2], 1.0f);
-        } else {
-          a = Q.q[2 * n];
-          b = Q.q[2 * n + 1];
-        }
+    // lane l holds sample base + l
+    const int64_t own = base + lane;
+    float4 a = make_float4(0, 0, 0, 0), b = a;
+    if (own < count) {
+      if (MODE == 0) {
+        a = make_float4(Q.pos[3 * own], Q.pos[3 * own + 1], Q.pos[3 * own + 2], Q.sigma[own]);
+        b = make_float4(Q.dir[3 * own], Q.dir[3 * own + 1], Q.dir[3 * own + 2], 1.0f);
+      } else {
+        a = Q.q[2 * own];
+        b = Q.q[2 * own + 1];
       }
-      p[cb][0] = a.x;
-      p[cb][1] = a.y;
-      p[cb][2] = a.z;
-      sg[cb] = a.w;
-      d[cb][0] = b.x;
-      d[cb][1] = b.y;
-      d[cb][2] = b.z;
-      beta[cb] = b.w;
-      any = any || valid[cb];
     }
-    if (!__any(any)) continue;
     bf16x8 X[4][3];
-#pragma unroll
-    for (int cb = 0; cb < 4; cb++)
-#pragma unroll
-      for (int ks = 0; ks < 3; ks++)
-        X[cb][ks] = feat_chunk(4 * ks + g, p[cb][0], p[cb][1], p[cb][2], d[cb][0], d[cb][1], d[cb][2], sg[cb], Q.lref);
+    feat_operand(a.x, a.y, a.z, b.x, b.y, b.z, feat_sigma(a.w, Q.lref), lane, X);
     f32x4 acc[4][4];
     bf16x8 H[4][2];
     layer_fwd<3>(s_frag + kF0 * 64, s_bias, X, acc, lane);
@@ -265,21 +282,28 @@ __global__ __launch_bounds__(256) void k_nrc_query(NrcQueryArgs Q) {
     }
     f32x4 o[4];
     out_fwd(s_frag + kF4 * 64, s_bias + 256, H, o, lane);
-    if (g == 0) {
+    // outputs of sample 16 cb + r sit in lane r's o[cb]: to the sample's lane
+    float y[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+      float v = 0.0f;
 #pragma unroll
       for (int cb = 0; cb < 4; cb++) {
-        if (!valid[cb]) continue;
-        int64_t n = base + 16 * cb + r;
-        if (MODE == 0) {
-          Q.y[3 * n] = o[cb][0];
-          Q.y[3 * n + 1] = o[cb][1];
-          Q.y[3 * n + 2] = o[cb][2];
-        } else {
-          float* px = Q.out + 3 * (size_t)Q.qpix[n];
-          atomicAdd(px, beta[cb] * fmaxf(o[cb][0], 0.0f));
-          atomicAdd(px + 1, beta[cb] * fmaxf(o[cb][1], 0.0f));
-          atomicAdd(px + 2, beta[cb] * fmaxf(o[cb][2], 0.0f));
-        }
+        const float t = shfl_f(o[cb][i], r);
+        v = g == cb ? t : v;
+      }
+      y[i] = v;
+    }
+    if (own < count) {
+      if (MODE == 0) {
+        Q.y[3 * own] = y[0];
+        Q.y[3 * own + 1] = y[1];
+        Q.y[3 * own + 2] = y[2];
+      } else {
+        float* px = Q.out + 3 * (size_t)Q.qpix[own];
+        atomicAdd(px, b.w * fmaxf(y[0], 0.0f));
+        atomicAdd(px + 1, b.w * fmaxf(y[1], 0.0f));
+        atomicAdd(px + 2, b.w * fmaxf(y[2], 0.0f));
       }
     }
   }
@@ -408,6 +432,11 @@ __global__ __launch_bounds__(64) void k_nrc_train(NrcTrainArgs T) {
   // ---- inputs
   bf16x8 X[4][3];
   bool valid[4];
+  if (!T.feats) {
+    const int64_t own = min(base + lane, (int64_t)T.count - 1);
+    feat_operand(T.pos[3 * own], T.pos[3 * own + 1], T.pos[3 * own + 2], T.dir[3 * own], T.dir[3 * own + 1],
+                 T.dir[3 * own + 2], feat_sigma(T.sigma[own], T.lref), lane, X);
+  }
 #pragma unroll
   for (int cb = 0; cb < 4; cb++) {
     int64_t n = base + 16 * cb + r;
@@ -420,9 +449,6 @@ __global__ __launch_bounds__(64) void k_nrc_train(NrcTrainArgs T) {
         X[cb][ks] = as_bf(z);
       } else if (T.feats) {
         X[cb][ks] = feat_chunk_mem(T.feats + (size_t)kNrcIn * n, c);
-      } else {
-        X[cb][ks] = feat_chunk(c, T.pos[3 * n], T.pos[3 * n + 1], T.pos[3 * n + 2], T.dir[3 * n], T.dir[3 * n + 1],
-                               T.dir[3 * n + 2], T.sigma[n], T.lref);
       }
       u32x4 v = as_u4(X[cb][ks]);
 #pragma unroll
