@@ -50,6 +50,6 @@ def test_encoding_edges(cache):
     _, d, s = points(len(pos), 2)
     s[::7] = 0.0
     y = n.infer(pos, d, s).cpu().numpy().astype(np.float64)
-    ref = np.array([oracle.nrc_eval_point(P, pos[i], d[i], float(s[i]), 20.0) for i in range(len(pos))], np.float64)
+    ref = oracle.mlp_forward(P.astype(np.float64), oracle.nrc_encode(pos, d, s, 20.0).astype(np.float64), bf16=True)
     e = np.abs(y - ref) / np.sqrt((ref ** 2).mean())
     assert e.max() <= 2.0 ** -6 and (e <= 1e-4).mean() >= 0.95
