@@ -92,3 +92,37 @@ def test_reciprocal_rule_equals_general_way(kind, scale):
     assert (kind == "tiny") or taken.mean() > 0.25  # the rule is worth having
     assert (f2[taken] == face[taken]).all()
     assert (t2[taken].view(np.uint32) == te[taken].view(np.uint32)).all()
+
+
+@pytest.mark.parametrize("kind", ["random", "axes", "diagonals", "grazing", "tiny"])
+def test_voxel_rule_equals_division_of_every_axis(kind):
+    """The voxel walk's form of the rule: the axis with the smallest rounded
+    distance (plane - o) / d, the lowest axis on ties, and that distance."""
+    rng = np.random.default_rng(9)
+    k, n = 300000, 64
+    cell = rng.integers(0, n, (k, 3))
+    o = ((cell + rng.random((k, 3))) / n).astype(F)
+    o[: k // 3] = (cell[: k // 3] / n).astype(F)  # on voxel faces, edges and corners
+    d = directions(kind, k, rng)
+    num = ((cell + (d > 0)) / F(n)).astype(F) - o
+    td9 = dots(d)
+    tiny = (d == 0).all(axis=1) | ((td9 != 0) & ~((td9 <= -F(2.0 ** -40)) | (td9 >= F(2.0 ** -40)))).any(axis=1)
+    with np.errstate(all="ignore"):
+        tf = (num / d).astype(F)
+        best, bt = np.full(k, -1), np.zeros(k, F)
+        for a in range(3):
+            better = (d[:, a] != 0) & ((best < 0) | (tf[:, a] < bt))
+            best, bt = np.where(better, a, best), np.where(better, tf[:, a], bt)
+        r = np.where(tiny[:, None], F(0), np.where(d == 0, F(np.nan), F(1) / d)).astype(F)
+        q = (num * r).astype(F)
+        b = np.fmin(np.fmin(q[:, 0], q[:, 1]), q[:, 2])
+        m = q <= fma(np.abs(b), np.full_like(b, 2.0 ** -20), b)[:, None]
+        taken = (m.sum(axis=1) <= 1) & (b > F(2.0 ** -40))
+        axis = np.where(m[:, 2], 2, np.where(m[:, 1], 1, 0))
+        at = np.arange(k)
+        q1 = fma(fma(-b, d[at, axis], num[at, axis]), r[at, axis], b)
+        te = fma(fma(-q1, d[at, axis], num[at, axis]), r[at, axis], q1)
+    assert not taken[tiny].any() and not taken[best < 0].any()
+    assert (kind == "tiny") or taken.mean() > 0.25
+    assert (axis[taken] == best[taken]).all()
+    assert (te[taken].view(np.uint32) == bt[taken].view(np.uint32)).all()
