@@ -114,8 +114,8 @@ typedef struct {
                                  tet grids 6 and 8 mean 5, what the on-chip memory of a CU allows) */
   int32_t record_layout;      /* tet records walked: 32 (compact), 48, or 0 = compact when the grid has them */
   int32_t batch_items;        /* paths a wave takes at a time, at most (0 = default 64; batches always take 64) */
-  int32_t event_wait;         /* lanes of a wave that wait for an event before events run (0 = default: 32;
-                                 48 when collecting training paths) */
+  int32_t event_wait;         /* lanes of a wave that wait for an event before events run (0 = default: 48;
+                                 32 with channels or a density model) */
   const tet_nrc* nrc;         /* radiance cache: NULL = plain estimator; else paths stop at the cache's
                                  truncate_bounce-th real vertex and add throughput x cache (tet grids only) */
   int32_t nrc_train;          /* with a cache: the same launch also traces the cache's training paths of

@@ -761,7 +761,7 @@ __global__ __launch_bounds__(256) void k_scale_batch(RenderArgs A, uint64_t tota
 }
 
 enum { M_TRACK = 0, M_SHADOW = 1, M_COLLIDE = 2, M_SCATTER = 3, M_ESCAPE = 4, M_FINISH = 5, M_FETCH = 6,
-       M_DONE = 7 };
+       M_DONE = 7, M_PARK = 8 };
 
 constexpr uint32_t kMinTake = 16;  // paths a wave takes at least
 // Adds each lane's v[0..n) to the block's statistics slot: wave reductions,
@@ -1134,10 +1134,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
       // wave refills its batch with one atomic, first from this block's band
       // (blocks are dealt to the 8 XCDs round-robin, so an XCD's L2 serves
       // one band of the image), then from the others.
+      // A wave with training paths takes no others until they end: they are
+      // the longest, and among image paths each of their events would wait
+      // for the wave's others (cache frame of 16 K training paths: 2.34 ms
+      // mixed, 2.30 ms apart).
+      const bool hold = NRC == 1 && nlists == kLists && __ballot(trainp && mode <= M_ESCAPE);
+      if (NRC == 1 && !hold && mode == M_PARK) mode = M_FETCH;
       bool need = mode == M_FETCH;
       unsigned long long m = __ballot(need);
       if (m) {
-        while (bnext >= bend && tried < nlists) {
+        while (bnext >= bend && tried < (hold ? 1 : nlists)) {
           const uint32_t n = A.head[kCountAt + range * kLine];
           const uint32_t take = min(A.batch, max(kMinTake, n / (range == kTrainList ? 8 * list_waves : list_waves)));
           uint32_t base = 0;
@@ -1193,7 +1199,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
           }
           bnext = min(bnext + (uint32_t)__popcll(m), bend);
         } else if (need) {
-          mode = M_DONE;
+          mode = hold ? M_PARK : M_DONE;
         }
       }
       if (mode == M_COLLIDE && (NRC != 1 || trainp || (int32_t)bounce + 1 != A.truncate)) start_light();
@@ -1714,6 +1720,13 @@ static void launch_first(const RenderArgs& P, const Med& med, bool model, hipStr
   hipLaunchKernelGGL((k_first<Med, BATCH, false>), dim3(grid), dim3(kFirstBlock), 0, st, P, med);
 }
 
+// Lanes that wait for an event before the wave handles events: an event
+// section costs about twenty walk steps, so it is shared by most of the wave
+// (48 against 32: cloud frame 37.9 -> 36.7 ms, plume frame 30.1 -> 29.2 ms);
+// with channels or a density model more paths end in events (48: emissive
+// frame 3.71 -> 3.83 ms).
+static int default_event_wait(const ExtArgs& X) { return X.model || X.ch_t || X.ch_a || X.ch_g ? 32 : 48; }
+
 // The tracing kernel at an occupancy target.  Five waves per SIMD fit beside
 // the segments' tables (27 KB of LDS per 256 lanes), so on tet grids 6 and 8
 // mean 5.
@@ -1979,7 +1992,7 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   A.slots = (uint32_t)slots;
   A.tiles_x = tiles_x;
   A.batch = o.batch_items ? (uint32_t)o.batch_items : 64u;
-  A.event_wait = o.event_wait ? o.event_wait : 32;
+  A.event_wait = o.event_wait ? o.event_wait : default_event_wait(A.ex);
   if (nrc) {
     A.nrc = nrc;
     A.truncate = nrc->opts.truncate_bounce;
@@ -2158,7 +2171,7 @@ int trace_training_paths(const tet_grid* g, const tet_camera* cam, const tet_med
   A.slots = (uint32_t)n_paths;
   A.tiles_x = (cam->width + 7) / 8;
   A.batch = o.batch_items ? (uint32_t)o.batch_items : 64u;
-  A.event_wait = o.event_wait ? o.event_wait : 48;
+  A.event_wait = o.event_wait ? o.event_wait : default_event_wait(A.ex);
   A.train = 1;
   A.npix = (uint32_t)((int64_t)cam->width * cam->height);
   A.rec_vertices = kv;
@@ -2400,7 +2413,7 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
   A.transmittance = o.transmittance;
   A.max_steps = (uint32_t)std::min<int64_t>(o.max_steps_per_path, 0x7FFFFFFF);
   A.batch = 64;
-  A.event_wait = o.event_wait ? o.event_wait : 32;
+  A.event_wait = o.event_wait ? o.event_wait : (B->ext ? 32 : 48);
   A.head = (uint32_t*)B->scratch;
   A.entries = (RayEntry*)(B->scratch + kHeadBytes);
   A.list = (uint32_t*)(A.entries + entry);
