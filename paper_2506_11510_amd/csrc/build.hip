@@ -1325,38 +1325,6 @@ __device__ inline void root_verts(int r, int32_t v[4][3]) {
 
 __device__ inline int isgn(int64_t x) { return (x > 0) - (x < 0); }
 
-// Bisection step of the perturbed-point descent for a compile-time tag K:
-// the point is 3 * face centroid (q3, below 2^22) plus epsilon * outward
-// normal.
-template <int K>
-__device__ inline void descend_perturbed(int32_t v[4][3], uint64_t& h, uint32_t& cls, const uint32_t* __restrict__ shapes,
-                                         const int32_t q3[3], const int nout[3]) {
-  const uint32_t w = shapes[cls];
-  int32_t z[3], u[3];
-  shape_bisector<K>(v, w, z, u);
-  int32_t side = 0, pert = 0;
-#pragma unroll
-  for (int i = 0; i < 3; i++) {
-    side += __mul24(u[i], q3[i] - 3 * z[i]);
-    pert += __mul24(u[i], nout[i]);
-  }
-  bool first = side != 0 ? side > 0 : pert > 0;
-  cls = first ? (w >> 8) & 255u : (w >> 16) & 255u;
-  if (first) {
-#pragma unroll
-    for (int i = 0; i < 3; i++) v[K][i] = z[i];
-    h = 2 * h;
-  } else {
-#pragma unroll
-    for (int j = 0; j < K; j++)
-#pragma unroll
-      for (int i = 0; i < 3; i++) v[j][i] = v[j + 1][i];
-#pragma unroll
-    for (int i = 0; i < 3; i++) v[K][i] = z[i];
-    h = 2 * h + 1;
-  }
-}
-
 // Outward unit normal of the face (a, b, c) opposite vertex o and its
 // lattice offset; returns false when the normal is not one of the 18
 // orientations.
@@ -1562,8 +1530,7 @@ __global__ __launch_bounds__(kRecordsBlock) void k_records(int64_t n, const uint
 __global__ void k_links(const uint32_t* __restrict__ items, const uint32_t* __restrict__ item_count, int64_t item_cap,
                         int64_t n,
                         const uint64_t* __restrict__ verts, const uint64_t* __restrict__ keys,
-                        const uint32_t* __restrict__ kidx, int kbits, int dmax, const uint32_t* __restrict__ shapes,
-                        TetRec* __restrict__ rec, TetRec32* __restrict__ rec32, int* __restrict__ err) {
+                        const uint32_t* __restrict__ kidx, int kbits, int dmax, TetRec* __restrict__ rec, TetRec32* __restrict__ rec32, int* __restrict__ err) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= min((int64_t)*item_count, item_cap)) return;
   const uint32_t it = items[s];
@@ -1586,15 +1553,12 @@ __global__ void k_links(const uint32_t* __restrict__ items, const uint32_t* __re
   if (root < 0) {
     atomicOr(err, 4);
   } else {
-    int32_t w[4][3], q3i[3] = {(int32_t)q3[0], (int32_t)q3[1], (int32_t)q3[2]};
-    root_verts(root, w);
-    uint64_t h = 8 + root;
-    uint32_t cls = shapes[kShapeWords + root];
-    for (int d = 0; d < dmax; d += 3) {
-      descend_perturbed<3>(w, h, cls, shapes, q3i, un);
-      if (d + 1 < dmax) descend_perturbed<2>(w, h, cls, shapes, q3i, un);
-      if (d + 2 < dmax) descend_perturbed<1>(w, h, cls, shapes, q3i, un);
-    }
+    // the point as one integer per axis: 8 * (3 * centroid) + normal
+    int32_t F[3];
+#pragma unroll
+    for (int a = 0; a < 3; a++) F[a] = 8 * (int32_t)q3[a] + un[a];
+    const int32_t hi = max(max(F[0], F[1]), F[2]), lo = min(min(F[0], F[1]), F[2]);
+    const uint64_t h = fold_path<true>(hi, F[0] + F[1] + F[2] - hi - lo, lo, 24 * kLatS, dmax, 8 + (uint64_t)root);
     const int64_t nb = search_keys_idx(keys, kidx, kbits, h << (60 - dmax));
     // back face: the neighbour's vertex that is not on face f
     const int i0 = f == 0 ? 1 : 0, i1 = f <= 1 ? 2 : 1, i2 = f <= 2 ? 3 : 2;
@@ -2486,7 +2450,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
                      scale, o.majorant_mode, g->rec, g->rec32, items.as<uint32_t>(), item_cap, d_items,
                      d_flag + 2);
   hipLaunchKernelGGL(k_links, dim3(nblocks(item_cap, 128)), dim3(128), 0, st, items.as<uint32_t>(), d_items, item_cap,
-                     cur, g->verts, g->keys, g->kidx, g->kbits, g->max_depth, shapes, g->rec, g->rec32, d_flag + 2);
+                     cur, g->verts, g->keys, g->kidx, g->kbits, g->max_depth, g->rec, g->rec32, d_flag + 2);
   int ferr = 0;
   he = hipMemcpyAsync(&ferr, d_flag + 2, 4, hipMemcpyDeviceToHost, st);
   if (he == hipSuccess) he = hipEventRecord(e1, st);

@@ -273,8 +273,9 @@ __device__ inline void descend_point(int32_t v[4][3], uint64_t& h, uint32_t& cls
 }
 
 // Tet containing p: the Kuhn root whose axis order sorts p's coordinates in
-// descending order, exact bisection-plane descent to the grid's depth, then
-// the last tet whose depth-first key is <= the key reached.
+// descending order, bisections down to the grid's depth (folded coordinates;
+// bisected vertices where those would not be exact), then the last tet whose
+// depth-first key is <= the key reached.
 __device__ inline int64_t locate_point(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ kidx, int kbits,
                                        int dmax, const uint32_t* __restrict__ shapes, float3 p) {
   const float c[3] = {p.x, p.y, p.z};
@@ -286,6 +287,16 @@ __device__ inline int64_t locate_point(const uint64_t* __restrict__ keys, const 
   else if (c[2] >= c[0] && c[0] >= c[1]) r = 4;
   else if (c[2] >= c[1] && c[1] >= c[0]) r = 5;
   if (r < 0) return -1;
+  const double P[3] = {(double)p.x * (double)kLatS, (double)p.y * (double)kLatS, (double)p.z * (double)kLatS};
+  // Coordinates that are 0 or at least 2^-29 are multiples of 2^-32 lattice
+  // units: then both ways of descending are exact in FP64 and agree.  The
+  // points on the cube's surface that paths enter at nearly always are.
+  if ((c[0] == 0.0f || c[0] >= 0x1p-29f) && (c[1] == 0.0f || c[1] >= 0x1p-29f) && (c[2] == 0.0f || c[2] >= 0x1p-29f)) {
+    const double hi = fmax(fmax(P[0], P[1]), P[2]), lo = fmin(fmin(P[0], P[1]), P[2]);
+    const double mid = fmax(fmin(P[0], P[1]), fmin(fmax(P[0], P[1]), P[2]));
+    return search_keys_idx(keys, kidx, kbits,
+                           fold_path<false>(hi, mid, lo, (double)kLatS, dmax, 8 + (uint64_t)r) << (60 - dmax));
+  }
   const int p0 = (r < 2) ? 0 : (r < 4 ? 1 : 2);
   const int p1 = (r == 0 || r == 5) ? 1 : ((r == 1 || r == 3) ? 2 : 0);
   int32_t v[4][3];
@@ -296,7 +307,6 @@ __device__ inline int64_t locate_point(const uint64_t* __restrict__ keys, const 
     v[2][a] = (a == p0 || a == p1) ? kLatS : 0;
     v[3][a] = kLatS;
   }
-  double P[3] = {(double)p.x * (double)kLatS, (double)p.y * (double)kLatS, (double)p.z * (double)kLatS};
   uint64_t h = 8 + (uint64_t)r;
   uint32_t cls = shapes[kShapeWords + r];
   for (int d = 0; d < dmax; d += 3) {
