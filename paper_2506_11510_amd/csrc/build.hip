@@ -110,48 +110,62 @@ __device__ inline void box_stats(const Pyramid& P, const int32_t lo[3], const in
     l = min(l, (int)__builtin_ctz((uint32_t)r1[a]));
   }
   int64_t m = (int64_t)P.n >> l;
+  const int32_t i0 = r0[0] >> l, i1 = r1[0] >> l, j0 = r0[1] >> l, j1 = r1[1] >> l;
+  int32_t i = i0, j = j0, k = r0[2] >> l;
+  const int64_t cells = (int64_t)(i1 - i0) * (j1 - j0) * ((r1[2] >> l) - k);
   double s = 0.0;
   float a = 0.0f, b = 0.0f;
-  bool first = true;
-  int64_t cells = 0;
-  for (int32_t k = r0[2] >> l; k < (r1[2] >> l); k++)
-    for (int32_t j = r0[1] >> l; j < (r1[1] >> l); j++)
-      for (int32_t i = r0[0] >> l; i < (r1[0] >> l); i++) {
-        int64_t o = i + m * (j + m * (int64_t)k);
-        float cmn, cmx;
-        double cs;
-        if (P.bmap && l < kBrickBits) {  // sparse levels 0..2: inside the cell's brick, zero without one
-          const int sb = kBrickBits - l;
-          const int32_t br = P.bmap[(i >> sb) + (int64_t)P.nb * ((j >> sb) + (int64_t)P.nb * (k >> sb))];
-          if (br < 0) {
-            cmn = cmx = 0.0f;
-            cs = 0.0;
-          } else {
-            const int32_t mk = (1 << sb) - 1;
-            const int64_t li = (int64_t)br * (1 << (3 * sb)) + ((i & mk) + ((j & mk) << sb) + ((k & mk) << (2 * sb)));
-            if (l == 0) {
-              cmn = cmx = P.bval[li];
-              cs = (double)cmn;
-            } else {
-              cmn = P.bmn[l][li];
-              cmx = P.bmx[l][li];
-              cs = P.bsum[l][li];
-            }
-          }
-        } else if (l == 0) {
-          cmn = cmx = P.dens[o];
-          cs = (double)cmn;
+  for (int64_t done = 0; done < cells; done += 4) {
+    float cmn[4], cmx[4];
+    double cs[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int64_t o = i + m * (j + m * (int64_t)k);
+      if (P.bmap && l < kBrickBits) {  // sparse levels 0..2: inside the cell's brick, zero without one
+        const int sb = kBrickBits - l;
+        const int32_t br = P.bmap[(i >> sb) + (int64_t)P.nb * ((j >> sb) + (int64_t)P.nb * (k >> sb))];
+        if (br < 0) {
+          cmn[q] = cmx[q] = 0.0f;
+          cs[q] = 0.0;
         } else {
-          cmn = P.mn[l][o];
-          cmx = P.mx[l][o];
-          cs = P.sum[l][o];
+          const int32_t mk = (1 << sb) - 1;
+          const int64_t li = (int64_t)br * (1 << (3 * sb)) + ((i & mk) + ((j & mk) << sb) + ((k & mk) << (2 * sb)));
+          if (l == 0) {
+            cmn[q] = cmx[q] = P.bval[li];
+            cs[q] = (double)cmn[q];
+          } else {
+            cmn[q] = P.bmn[l][li];
+            cmx[q] = P.bmx[l][li];
+            cs[q] = P.bsum[l][li];
+          }
         }
-        if (first || cmn < a) a = cmn;
-        if (first || cmx > b) b = cmx;
-        first = false;
-        s = s + cs;
-        cells++;
+      } else if (l == 0) {
+        cmn[q] = cmx[q] = P.dens[o];
+        cs[q] = (double)cmn[q];
+      } else {
+        cmn[q] = P.mn[l][o];
+        cmx[q] = P.mx[l][o];
+        cs[q] = P.sum[l][o];
       }
+      if (done + q + 1 < cells) {  // (past the last cell: that cell again, not added)
+        if (++i == i1) {
+          i = i0;
+          if (++j == j1) {
+            j = j0;
+            k++;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      if (done + q >= cells) break;
+      const bool first = done + q == 0;
+      if (first || cmn[q] < a) a = cmn[q];
+      if (first || cmx[q] > b) b = cmx[q];
+      s = s + cs[q];
+    }
+  }
   mn = a;
   mx = b;
   sum = s;
