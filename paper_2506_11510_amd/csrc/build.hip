@@ -39,39 +39,47 @@
 namespace tv {
 
 // ---------------------------------------------------------------- pyramid
-__global__ void k_pyramid_level(const float* __restrict__ dens, const float* __restrict__ cmn,
-                                const float* __restrict__ cmx, const double* __restrict__ csum, int32_t m,
-                                float* __restrict__ mn, float* __restrict__ mx, double* __restrict__ sum) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t total = (int64_t)m * m * m;
-  if (idx >= total) return;
+// Cell idx of a level of m^3 cells from the 8 below it.
+__device__ inline PyrCell parent_cell(const float* __restrict__ dens, const PyrCell* __restrict__ child, int32_t m,
+                                      int64_t idx) {
   int64_t i = idx % m, j = (idx / m) % m, k = idx / ((int64_t)m * m);
   int64_t pm = 2 * (int64_t)m;
-  float lo[8], hi[8];
-  double s[8];
+  PyrCell x[8];
 #pragma unroll
   for (int q = 0; q < 8; q++) {
     int64_t c = (2 * i + (q & 1)) + pm * ((2 * j + ((q >> 1) & 1)) + pm * (2 * k + ((q >> 2) & 1)));
-    if (dens) {
-      float v = dens[c];
-      lo[q] = v;
-      hi[q] = v;
-      s[q] = (double)v;
-    } else {
-      lo[q] = cmn[c];
-      hi[q] = cmx[c];
-      s[q] = csum[c];
-    }
+    if (dens) x[q].mn = x[q].mx = dens[c], x[q].sum = (double)x[q].mn;
+    else x[q] = child[c];
   }
-  float a = lo[0], b = hi[0];
+  float a = x[0].mn, b = x[0].mx;
 #pragma unroll
   for (int q = 1; q < 8; q++) {
-    a = lo[q] < a ? lo[q] : a;
-    b = hi[q] > b ? hi[q] : b;
+    a = x[q].mn < a ? x[q].mn : a;
+    b = x[q].mx > b ? x[q].mx : b;
   }
-  mn[idx] = a;
-  mx[idx] = b;
-  sum[idx] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+  return {a, b,
+          ((x[0].sum + x[1].sum) + (x[2].sum + x[3].sum)) + ((x[4].sum + x[5].sum) + (x[6].sum + x[7].sum))};
+}
+
+// One level; dens for level 1 of a dense volume, else NULL.
+__global__ void k_pyramid_level(const float* __restrict__ dens, const PyrCell* __restrict__ child, int32_t m,
+                                PyrCell* __restrict__ out) {
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (idx < (int64_t)m * m * m) out[idx] = parent_cell(dens, child, m, idx);
+}
+
+// The levels of at most kTopCells^3 cells, up to the one cell, from the
+// level of (2m)^3 below them: one block, a level at a time (as launches of
+// their own they took 5 us each).
+constexpr int kTopCells = 16;
+__global__ __launch_bounds__(1024) void k_pyramid_top(const PyrCell* child, int32_t m, PyrCell* cells) {
+  for (; m >= 1; m >>= 1) {
+    PyrCell* out = cells + level_offset(__builtin_ctz(m));
+    for (int idx = threadIdx.x; idx < m * m * m; idx += 1024) out[idx] = parent_cell(nullptr, child, m, idx);
+    child = out;
+    __threadfence_block();
+    __syncthreads();
+  }
 }
 
 __global__ void k_check_density(const float* __restrict__ d, int64_t n, int* __restrict__ bad) {
@@ -113,11 +121,11 @@ __device__ inline void box_stats(const Pyramid& P, const int32_t lo[3], const in
   const int32_t i0 = r0[0] >> l, i1 = r1[0] >> l, j0 = r0[1] >> l, j1 = r1[1] >> l;
   int32_t i = i0, j = j0, k = r0[2] >> l;
   const int64_t cells = (int64_t)(i1 - i0) * (j1 - j0) * ((r1[2] >> l) - k);
+  const PyrCell* lev = P.cells + level_offset(P.L - l);
   double s = 0.0;
   float a = 0.0f, b = 0.0f;
   for (int64_t done = 0; done < cells; done += 4) {
-    float cmn[4], cmx[4];
-    double cs[4];
+    PyrCell c[4];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
       const int64_t o = i + m * (j + m * (int64_t)k);
@@ -125,27 +133,22 @@ __device__ inline void box_stats(const Pyramid& P, const int32_t lo[3], const in
         const int sb = kBrickBits - l;
         const int32_t br = P.bmap[(i >> sb) + (int64_t)P.nb * ((j >> sb) + (int64_t)P.nb * (k >> sb))];
         if (br < 0) {
-          cmn[q] = cmx[q] = 0.0f;
-          cs[q] = 0.0;
+          c[q] = {0.0f, 0.0f, 0.0};
         } else {
           const int32_t mk = (1 << sb) - 1;
-          const int64_t li = (int64_t)br * (1 << (3 * sb)) + ((i & mk) + ((j & mk) << sb) + ((k & mk) << (2 * sb)));
+          const int32_t li = (i & mk) + ((j & mk) << sb) + ((k & mk) << (2 * sb));
           if (l == 0) {
-            cmn[q] = cmx[q] = P.bval[li];
-            cs[q] = (double)cmn[q];
+            const float v = P.bval[(int64_t)br * 512 + li];
+            c[q] = {v, v, (double)v};
           } else {
-            cmn[q] = P.bmn[l][li];
-            cmx[q] = P.bmx[l][li];
-            cs[q] = P.bsum[l][li];
+            c[q] = P.bcells[(int64_t)br * kBrickCells + (l == 1 ? li : 64 + li)];
           }
         }
       } else if (l == 0) {
-        cmn[q] = cmx[q] = P.dens[o];
-        cs[q] = (double)cmn[q];
+        const float v = P.dens[o];
+        c[q] = {v, v, (double)v};
       } else {
-        cmn[q] = P.mn[l][o];
-        cmx[q] = P.mx[l][o];
-        cs[q] = P.sum[l][o];
+        c[q] = lev[o];
       }
       if (done + q + 1 < cells) {  // (past the last cell: that cell again, not added)
         if (++i == i1) {
@@ -161,9 +164,9 @@ __device__ inline void box_stats(const Pyramid& P, const int32_t lo[3], const in
     for (int q = 0; q < 4; q++) {
       if (done + q >= cells) break;
       const bool first = done + q == 0;
-      if (first || cmn[q] < a) a = cmn[q];
-      if (first || cmx[q] > b) b = cmx[q];
-      s = s + cs[q];
+      if (first || c[q].mn < a) a = c[q].mn;
+      if (first || c[q].mx > b) b = c[q].mx;
+      s = s + c[q].sum;
     }
   }
   mn = a;
@@ -1792,26 +1795,31 @@ struct Leaves {
   }
 };
 
-// Min / max / FP64-sum pyramid of an n^3 grid (n = 2^L) on the device,
-// levels 1..L in lv; false when out of memory.
+// Levels l0..L, each from the one below (level 1 from the voxels d).
+static void pyramid_levels(const float* d, int32_t n, int L, int l0, PyrCell* cells, hipStream_t st) {
+  for (int l = l0; l <= L; l++) {
+    const int32_t m = n >> l;
+    const PyrCell* child = l == 1 ? nullptr : cells + level_offset(L - l + 1);
+    if (l > 1 && m <= kTopCells) {
+      hipLaunchKernelGGL(k_pyramid_top, dim3(1), dim3(1024), 0, st, child, m, cells);
+      return;
+    }
+    hipLaunchKernelGGL(k_pyramid_level, dim3(nblocks((int64_t)m * m * m, 256)), dim3(256), 0, st, l == 1 ? d : nullptr,
+                       child, m, cells + level_offset(L - l));
+  }
+}
+
+// Min / max / FP64-sum pyramid of an n^3 grid (n = 2^L) on the device, its
+// levels in lv; false when out of memory.
 static bool make_pyramid(const float* d, int32_t n, int L, Pyramid& P, std::vector<Buf>& lv, hipStream_t st) {
   memset(&P, 0, sizeof(P));
   P.dens = d;
   P.n = n;
   P.L = L;
-  lv = std::vector<Buf>(3 * (L + 1));
-  for (int l = 1; l <= L; l++) {
-    int64_t m = (int64_t)n >> l, cells = m * m * m;
-    if (!lv[3 * l].ensure(cells * 4) || !lv[3 * l + 1].ensure(cells * 4) || !lv[3 * l + 2].ensure(cells * 8))
-      return false;
-    P.mn[l] = lv[3 * l].as<float>();
-    P.mx[l] = lv[3 * l + 1].as<float>();
-    P.sum[l] = lv[3 * l + 2].as<double>();
-    hipLaunchKernelGGL(k_pyramid_level, dim3(nblocks(cells, 256)), dim3(256), 0, st, l == 1 ? d : nullptr,
-                       l == 1 ? nullptr : P.mn[l - 1], l == 1 ? nullptr : P.mx[l - 1],
-                       l == 1 ? nullptr : P.sum[l - 1], (int32_t)m, (float*)P.mn[l], (float*)P.mx[l],
-                       (double*)P.sum[l]);
-  }
+  lv = std::vector<Buf>(1);
+  if (!lv[0].ensure((size_t)level_offset(L) * sizeof(PyrCell))) return false;
+  P.cells = lv[0].as<PyrCell>();
+  pyramid_levels(d, n, L, 1, lv[0].as<PyrCell>(), st);
   return true;
 }
 
@@ -1833,81 +1841,25 @@ __global__ void k_brick_map(const int32_t* __restrict__ coords, int64_t nbricks,
 // its level-3 cell in the dense level-3 arrays; children combined as in
 // k_pyramid_level.
 __global__ __launch_bounds__(64) void k_brick_levels(const int32_t* __restrict__ coords, const float* __restrict__ val,
-                                                     int32_t nb, float* __restrict__ mn1, float* __restrict__ mx1,
-                                                     double* __restrict__ s1, float* __restrict__ mn2,
-                                                     float* __restrict__ mx2, double* __restrict__ s2,
-                                                     float* __restrict__ mn3, float* __restrict__ mx3,
-                                                     double* __restrict__ s3) {
-  __shared__ float lmn[64], lmx[64];
-  __shared__ double lsum[64];
+                                                     int32_t nb, PyrCell* __restrict__ bcells,
+                                                     PyrCell* __restrict__ level3) {
+  __shared__ PyrCell cell[64], cell2[8];
   const int64_t b = blockIdx.x;
   const int t = threadIdx.x;
-  auto combine = [](const float* lo, const float* hi, const double* s, float& a, float& c, double& sum) {
-    a = lo[0];
-    c = hi[0];
-    for (int q = 1; q < 8; q++) {
-      a = lo[q] < a ? lo[q] : a;
-      c = hi[q] > c ? hi[q] : c;
-    }
-    sum = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
-  };
-  {  // level 1: cell (i, j, k) of 4^3 from voxels (2i + a, 2j + b, 2k + c) of 8^3
-    const int i = t & 3, j = (t >> 2) & 3, k = t >> 4;
-    float lo[8], hi[8];
-    double s[8];
-    for (int q = 0; q < 8; q++) {
-      const float v = val[b * 512 + (2 * i + (q & 1)) + 8 * ((2 * j + ((q >> 1) & 1)) + 8 * (2 * k + ((q >> 2) & 1)))];
-      lo[q] = v;
-      hi[q] = v;
-      s[q] = (double)v;
-    }
-    float a, c;
-    double sum;
-    combine(lo, hi, s, a, c, sum);
-    mn1[b * 64 + t] = a;
-    mx1[b * 64 + t] = c;
-    s1[b * 64 + t] = sum;
-    lmn[t] = a;
-    lmx[t] = c;
-    lsum[t] = sum;
-  }
+  // level 1: cell of 4^3 from the voxels of 8^3
+  cell[t] = parent_cell(val + b * 512, nullptr, 4, t);
+  bcells[b * kBrickCells + t] = cell[t];
   __syncthreads();
-  float a2 = 0.0f, c2 = 0.0f;
-  double sum2 = 0.0;
   if (t < 8) {  // level 2: cell of 2^3 from level-1 cells of 4^3
-    const int i = t & 1, j = (t >> 1) & 1, k = t >> 2;
-    float lo[8], hi[8];
-    double s[8];
-    for (int q = 0; q < 8; q++) {
-      const int c = (2 * i + (q & 1)) + 4 * ((2 * j + ((q >> 1) & 1)) + 4 * (2 * k + ((q >> 2) & 1)));
-      lo[q] = lmn[c];
-      hi[q] = lmx[c];
-      s[q] = lsum[c];
-    }
-    combine(lo, hi, s, a2, c2, sum2);
-    mn2[b * 8 + t] = a2;
-    mx2[b * 8 + t] = c2;
-    s2[b * 8 + t] = sum2;
-  }
-  __syncthreads();
-  if (t < 8) {
-    lmn[t] = a2;
-    lmx[t] = c2;
-    lsum[t] = sum2;
+    cell2[t] = parent_cell(nullptr, cell, 2, t);
+    bcells[b * kBrickCells + 64 + t] = cell2[t];
   }
   __syncthreads();
   const int32_t bx = coords[3 * b], by = coords[3 * b + 1], bz = coords[3 * b + 2];
-  if (t == 0 && bx >= 0 && by >= 0 && bz >= 0 && bx < nb && by < nb && bz < nb) {
-    // level 3: the brick's own cell (child order q = x + 2y + 4z); bricks
-    // out of range are reported by k_brick_map and skipped here
-    float a, c;
-    double sum;
-    combine(lmn, lmx, lsum, a, c, sum);
-    const int64_t o = bx + (int64_t)nb * (by + (int64_t)nb * bz);
-    mn3[o] = a;
-    mx3[o] = c;
-    s3[o] = sum;
-  }
+  // level 3: the brick's own cell; bricks out of range are reported by
+  // k_brick_map and skipped here
+  if (t == 0 && bx >= 0 && by >= 0 && bz >= 0 && bx < nb && by < nb && bz < nb)
+    level3[bx + (int64_t)nb * (by + (int64_t)nb * bz)] = parent_cell(nullptr, cell2, 1, 0);
 }
 
 // Pyramid of a sparse volume (n >= 8): brick map, per-brick levels 1-2,
@@ -1921,45 +1873,25 @@ static bool make_sparse_pyramid(const int32_t* coords, const float* val, int64_t
   const int32_t nb = n >> kBrickBits;
   P.nb = nb;
   const int64_t nbc = (int64_t)nb * nb * nb;
-  lv = std::vector<Buf>(3 * (L + 1) + 1);
-  Buf& map = lv[3 * (L + 1)];
-  if (!map.ensure(nbc * 4)) return false;
-  hipLaunchKernelGGL(k_fill_u32, dim3(nblocks(nbc, 256)), dim3(256), 0, st, map.as<uint32_t>(), nbc, 0xFFFFFFFFu);
-  if (nbricks > 0)
-    hipLaunchKernelGGL(k_brick_map, dim3(nblocks(nbricks, 256)), dim3(256), 0, st, coords, nbricks, nb,
-                       map.as<int32_t>(), d_bad);
+  lv = std::vector<Buf>(3);
+  Buf &cells = lv[0], &bcells = lv[1], &map = lv[2];
+  if (!map.ensure(nbc * 4) || !bcells.ensure((size_t)std::max<int64_t>(nbricks, 1) * kBrickCells * sizeof(PyrCell)) ||
+      !cells.ensure((size_t)level_offset(L - 2) * sizeof(PyrCell)))
+    return false;
   P.bmap = map.as<int32_t>();
   P.bval = val;
-  const int64_t nbr = std::max<int64_t>(nbricks, 1);
-  for (int l = 1; l <= 2; l++) {  // per-brick levels
-    const int64_t cells = nbr * (l == 1 ? 64 : 8);
-    if (!lv[3 * l].ensure(cells * 4) || !lv[3 * l + 1].ensure(cells * 4) || !lv[3 * l + 2].ensure(cells * 8))
-      return false;
-    P.bmn[l] = lv[3 * l].as<float>();
-    P.bmx[l] = lv[3 * l + 1].as<float>();
-    P.bsum[l] = lv[3 * l + 2].as<double>();
+  P.bcells = bcells.as<PyrCell>();
+  P.cells = cells.as<PyrCell>();
+  PyrCell* level3 = cells.as<PyrCell>() + level_offset(L - 3);
+  hipLaunchKernelGGL(k_fill_u32, dim3(nblocks(nbc, 256)), dim3(256), 0, st, map.as<uint32_t>(), nbc, 0xFFFFFFFFu);
+  if (hipMemsetAsync(level3, 0, nbc * sizeof(PyrCell), st) != hipSuccess) return false;
+  if (nbricks > 0) {
+    hipLaunchKernelGGL(k_brick_map, dim3(nblocks(nbricks, 256)), dim3(256), 0, st, coords, nbricks, nb,
+                       map.as<int32_t>(), d_bad);
+    hipLaunchKernelGGL(k_brick_levels, dim3((unsigned)nbricks), dim3(64), 0, st, coords, val, nb, bcells.as<PyrCell>(),
+                       level3);
   }
-  for (int l = 3; l <= L; l++) {
-    const int64_t m = (int64_t)n >> l, cells = m * m * m;
-    if (!lv[3 * l].ensure(cells * 4) || !lv[3 * l + 1].ensure(cells * 4) || !lv[3 * l + 2].ensure(cells * 8))
-      return false;
-    P.mn[l] = lv[3 * l].as<float>();
-    P.mx[l] = lv[3 * l + 1].as<float>();
-    P.sum[l] = lv[3 * l + 2].as<double>();
-    if (l == 3) {
-      if (hipMemsetAsync(lv[9].p, 0, cells * 4, st) != hipSuccess ||
-          hipMemsetAsync(lv[10].p, 0, cells * 4, st) != hipSuccess ||
-          hipMemsetAsync(lv[11].p, 0, cells * 8, st) != hipSuccess)
-        return false;
-      if (nbricks > 0)
-        hipLaunchKernelGGL(k_brick_levels, dim3((unsigned)nbricks), dim3(64), 0, st, coords, val, nb,
-                           (float*)P.bmn[1], (float*)P.bmx[1], (double*)P.bsum[1], (float*)P.bmn[2], (float*)P.bmx[2],
-                           (double*)P.bsum[2], (float*)P.mn[3], (float*)P.mx[3], (double*)P.sum[3]);
-    } else {
-      hipLaunchKernelGGL(k_pyramid_level, dim3(nblocks(cells, 256)), dim3(256), 0, st, nullptr, P.mn[l - 1],
-                         P.mx[l - 1], P.sum[l - 1], (int32_t)m, (float*)P.mn[l], (float*)P.mx[l], (double*)P.sum[l]);
-    }
-  }
+  pyramid_levels(nullptr, n, L, 4, cells.as<PyrCell>(), st);
   return true;
 }
 

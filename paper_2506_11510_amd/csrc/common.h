@@ -15,7 +15,6 @@ constexpr int kLatBits = 20;
 constexpr int32_t kLatS = 1 << kLatBits;
 constexpr uint32_t kBoundary = 0xFFFFFFFFu;
 constexpr uint64_t kEmptyKey = ~0ull;  // never a packed vertex (coords <= 2^20 < 2^21 - 1)
-constexpr int kMaxLevels = 13;          // pyramid levels for n <= 4096
 
 // Traversal record of one tet: everything a walk step reads, 48 bytes,
 // fetched as three 16-byte loads.
@@ -77,23 +76,28 @@ __host__ __device__ inline int dir_code(const int un[3]) {
 // Density pyramid: level 0 is the input volume; levels 1..L hold per cell
 // min, max (FP32) and the FP64 sum of its 8 children combined as
 // ((c000 + c100) + (c010 + c110)) + ((c001 + c101) + (c011 + c111)).
+struct PyrCell {  // statistics of a cell's voxels
+  float mn, mx;
+  double sum;
+};
 struct Pyramid {
   const float* dens;
   int32_t n, L;
-  const float* mn[kMaxLevels];
-  const float* mx[kMaxLevels];
-  const double* sum[kMaxLevels];
+  const PyrCell* cells;  // level l at level_offset(L - l)
   // sparse volume (zero outside 8^3 bricks; dens and levels 1, 2 unused):
   // brick index at each brick position (nb^3, -1 = empty), and per brick
-  // its 512 voxels (bval) and its level-1 (64 cells) and level-2 (8 cells)
-  // statistics; levels >= 3 are dense as above
+  // its 512 voxels (bval) and its 64 level-1 and 8 level-2 cells; levels
+  // >= 3 are dense as above
   const int32_t* bmap;
   int32_t nb;
   const float* bval;
-  const float* bmn[3];
-  const float* bmx[3];
-  const double* bsum[3];
+  const PyrCell* bcells;
 };
+constexpr int kBrickCells = 64 + 8;
+// Cells of the t coarsest levels, (8^t - 1) / 7 (the bits 001001..., 3t of them).
+__host__ __device__ inline int64_t level_offset(int t) {
+  return (int64_t)(0x1249249249249249ull & ((1ull << (3 * t)) - 1));
+}
 constexpr int kBrickBits = 3;  // sparse bricks of 8^3 voxels
 
 // Camera quantities of the camera criterion, FP64.
