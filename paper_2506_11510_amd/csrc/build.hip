@@ -373,20 +373,18 @@ __device__ inline void cell_mark(uint32_t* cells, uint64_t z, bool coarse) {
   }
 }
 
-// True when the box of v touches a marked cell (or spans more than 64 cells).
+// True when the box of v touches a marked cell, or spans more than two cells
+// along an axis: such leaves are few, and a loop over up to 64 cells, one
+// load after another, kept their waves waiting 40 us.
 __device__ inline bool cells_touched(const uint32_t* __restrict__ cells, const uint64_t v[4]) {
   int32_t lo[3], hi[3];
   tet_box(v, lo, hi);
   const int x0 = cell_of(lo[0]), x1 = cell_of(hi[0]), y0 = cell_of(lo[1]), y1 = cell_of(hi[1]);
   const int z0 = cell_of(lo[2]), z1 = cell_of(hi[2]);
-  if ((x1 - x0 + 1) * (y1 - y0 + 1) * (z1 - z0 + 1) > 64) return true;
-  for (int z = z0; z <= z1; z++)
-    for (int y = y0; y <= y1; y++)
-      for (int x = x0; x <= x1; x++) {
-        const int idx = (z * 64 + y) * 64 + x;
-        if (!((cells[idx >> 5] >> (idx & 31)) & 1u)) return true;
-      }
-  return false;
+  if (x1 - x0 > 1 || y1 - y0 > 1 || z1 - z0 > 1) return true;
+  const uint64_t* rows = reinterpret_cast<const uint64_t*>(cells);  // the 64 cells along x
+  const uint64_t all = rows[z0 * 64 + y0] & rows[z0 * 64 + y1] & rows[z1 * 64 + y0] & rows[z1 * 64 + y1];
+  return (~all & (1ull << x0 | 1ull << x1)) != 0;
 }
 
 // Tail rounds: every leaf that splits is listed.  The list positions come
@@ -450,22 +448,6 @@ __global__ void k_chunk_boxes(int64_t n, int64_t c0, int64_t c1, const uint64_t*
   }
 }
 
-// True when the chunk's box may hold a marked cell.
-__device__ inline bool chunk_touched(const uint32_t* __restrict__ cells, const uint32_t* __restrict__ box,
-                                     int64_t c) {
-  const uint32_t x0 = box[8 * c], y0 = box[8 * c + 1], z0 = box[8 * c + 2];
-  const uint32_t x1 = box[8 * c + 4], y1 = box[8 * c + 5], z1 = box[8 * c + 6];
-  if (x0 > x1) return false;  // empty
-  if ((x1 - x0 + 1) * (y1 - y0 + 1) * (z1 - z0 + 1) > 64) return true;
-  for (uint32_t z = z0; z <= z1; z++)
-    for (uint32_t y = y0; y <= y1; y++)
-      for (uint32_t x = x0; x <= x1; x++) {
-        const uint32_t idx = (z * 64 + y) * 64 + x;
-        if (!((cells[idx >> 5] >> (idx & 31)) & 1u)) return true;
-      }
-  return false;
-}
-
 // Leaves whose want predicate is settled: split only when forced.
 __global__ void k_mark(int64_t n, const uint64_t* __restrict__ verts, uint8_t* __restrict__ flags,
                        uint32_t* __restrict__ cnt, const uint64_t* __restrict__ vset, uint64_t vmask,
@@ -488,98 +470,69 @@ __global__ void k_mark(int64_t n, const uint64_t* __restrict__ verts, uint8_t* _
   if (slist) list_split(split, (uint32_t)i, splitc, list0, slist);
 }
 
-// Tail rounds: k_mark over chunks, kTailChunks per block, with the cell
-// map staged in LDS.  A chunk of the main part whose box holds no marked
-// cell is skipped whole: its leaves are all checked (flag bit 1; the tail
-// starts after a compacting round, which checks every leaf), so none can
-// split.  Chunks holding appended leaves are always read.  Each half-wave
-// tests one chunk's box, a cell per lane (boxes of more than 64 cells count
-// as touched).
-constexpr int kTailChunks = 8;
-
+// Tail rounds: k_mark over chunks, one per wave.  A chunk of the main part
+// whose box holds no marked cell is skipped whole: its leaves are all checked
+// (flag bit 1; the tail starts after a compacting round, which checks every
+// leaf), so none can split.  Chunks holding appended leaves are always read.
+// A cell of the box per lane (boxes of more than 64 cells count as touched),
+// the 8^3 regions first when the last split was a tail round's, which keeps
+// the coarse map; then four leaves per lane, their loads issued together.
+// Latency bound: a wave waits for some eight loads in turn.  (As blocks of
+// eight chunks read one after the other, with the map staged in LDS, a round
+// of few splits took 50 us on 2.8 M leaves and 0.1 M new; now 13.)
 __device__ inline bool cell_marked(const uint32_t* m, uint32_t x, uint32_t y, uint32_t z) {
   const uint32_t idx = (z * 64 + y) * 64 + x;
   return !((m[idx >> 5] >> (idx & 31)) & 1u);
 }
 
-__global__ __launch_bounds__(kChunk) void k_mark_tail(int64_t n, int64_t nmain, const uint64_t* __restrict__ verts,
-                                                      uint8_t* __restrict__ flags, const uint64_t* __restrict__ vset,
-                                                      uint64_t vmask, const uint64_t* __restrict__ nset,
-                                                      uint64_t nmask, const uint32_t* __restrict__ cells,
-                                                      const uint32_t* __restrict__ box, uint32_t* splitc,
-                                                      uint32_t list0, uint32_t* __restrict__ slist, int coarse) {
-  static_assert(kChunk == 256 && kTailChunks == 8, "two chunks per wave of the block");
-  __shared__ uint4 smap4[kCellWords / 4];
-  __shared__ int stouch[kTailChunks];
-  // coarse test first (when the last split was a tail round's, which keeps
-  // the coarse map): a block none of whose chunks meets a marked 8^3 region
-  // stages nothing
-  if (coarse) {
-    const int lane = __lane_id(), k = 2 * (threadIdx.x >> 6) + (lane >> 5), j = lane & 31;
-    const int64_t c = (int64_t)blockIdx.x * kTailChunks + k;
-    bool hit = false;
-    if (c * kChunk < n) {
-      if (c >= nmain / kChunk) {
-        hit = true;
-      } else {
-        const uint32_t x0 = box[8 * c] >> 3, y0 = box[8 * c + 1] >> 3, z0 = box[8 * c + 2] >> 3;
-        const uint32_t nx = (box[8 * c + 4] >> 3) - x0 + 1, ny = (box[8 * c + 5] >> 3) - y0 + 1;
-        const uint32_t nz = (box[8 * c + 6] >> 3) - z0 + 1;
-        for (uint32_t q = j; q < nx * ny * nz; q += 32) {
-          const uint32_t cidx = ((z0 + q / (nx * ny)) * 8 + (y0 + (q / nx) % ny)) * 8 + (x0 + q % nx);
-          hit = hit || !((cells[kCellWords + (cidx >> 5)] >> (cidx & 31)) & 1u);
-        }
+__global__ __launch_bounds__(256) void k_mark_tail(int64_t n, int64_t nmain, const uint64_t* __restrict__ verts,
+                                                   uint8_t* __restrict__ flags, const uint64_t* __restrict__ vset,
+                                                   uint64_t vmask, const uint64_t* __restrict__ nset,
+                                                   uint64_t nmask, const uint32_t* __restrict__ cells,
+                                                   const uint32_t* __restrict__ box, uint32_t* splitc,
+                                                   uint32_t list0, uint32_t* __restrict__ slist, int coarse) {
+  const int lane = __lane_id();
+  const int64_t c = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (c * kChunk >= n) return;
+  if (c < nmain / kChunk) {
+    const uint32_t x0 = box[8 * c], y0 = box[8 * c + 1], z0 = box[8 * c + 2];
+    const uint32_t x1 = box[8 * c + 4], y1 = box[8 * c + 5], z1 = box[8 * c + 6];
+    if (coarse) {
+      const uint32_t nx = (x1 >> 3) - (x0 >> 3) + 1, ny = (y1 >> 3) - (y0 >> 3) + 1, nz = (z1 >> 3) - (z0 >> 3) + 1;
+      bool hit = false;
+      for (uint32_t q = lane; q < nx * ny * nz; q += 64) {
+        const uint32_t cidx = (((z0 >> 3) + q / (nx * ny)) * 8 + ((y0 >> 3) + (q / nx) % ny)) * 8 + ((x0 >> 3) + q % nx);
+        hit = hit || !((cells[kCellWords + (cidx >> 5)] >> (cidx & 31)) & 1u);
       }
+      if (!__any(hit)) return;
     }
-    if (!__syncthreads_or(hit)) return;
+    const uint32_t nx = x1 - x0 + 1, ny = y1 - y0 + 1, q = lane;
+    const uint32_t cnt = nx * ny * (z1 - z0 + 1);
+    if (!__any(cnt > 64 || (q < cnt && cell_marked(cells, x0 + q % nx, y0 + (q / nx) % ny, z0 + q / (nx * ny))))) return;
   }
-  const uint4* c4 = reinterpret_cast<const uint4*>(cells);
-  for (int w = threadIdx.x; w < kCellWords / 4; w += kChunk) smap4[w] = c4[w];
-  __syncthreads();
-  const uint32_t* smap = reinterpret_cast<const uint32_t*>(smap4);
-  {
-    const int lane = __lane_id(), k = 2 * (threadIdx.x >> 6) + (lane >> 5), j = lane & 31;
-    const int64_t c = (int64_t)blockIdx.x * kTailChunks + k;
-    bool hit = false, all = false;
-    if (c * kChunk < n) {
-      if (c >= nmain / kChunk) {
-        all = true;
-      } else {
-        const uint32_t x0 = box[8 * c], y0 = box[8 * c + 1], z0 = box[8 * c + 2];
-        const uint32_t nx = box[8 * c + 4] - x0 + 1, ny = box[8 * c + 5] - y0 + 1, nz = box[8 * c + 6] - z0 + 1;
-        const uint32_t cnt = nx * ny * nz;
-        if (cnt > 64) all = true;
-        for (uint32_t q = j; q < cnt && q < 64; q += 32)
-          hit = hit || cell_marked(smap, x0 + q % nx, y0 + (q / nx) % ny, z0 + q / (nx * ny));
-      }
-    }
-    const unsigned long long m = __ballot(hit || all);
-    if (j == 0) stouch[k] = ((m >> (lane & 32)) & 0xFFFFFFFFull) != 0;
+  constexpr int kPer = kChunk / 64;
+  uint8_t fl[kPer];
+  uint64_t v[kPer][4];
+  bool split[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; k++) {
+    const int64_t i = c * kChunk + 64 * k + lane;
+    fl[k] = i < n ? flags[i] : 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) v[k][j] = verts[4 * min(i, n - 1) + j];
   }
-  __syncthreads();
-  for (int k = 0; k < kTailChunks; k++) {
-    if (!stouch[k]) continue;
-    const int64_t i = ((int64_t)blockIdx.x * kTailChunks + k) * kChunk + threadIdx.x;
-    bool split = false;
-    if (i < n) {
-      const uint8_t fl = flags[i];
-      if (fl & 1) {
-        uint64_t v[4] = {verts[4 * i], verts[4 * i + 1], verts[4 * i + 2], verts[4 * i + 3]};
-        if (fl & 2) {
-          uint32_t cb[6];
-          cell_box(v, cb);
-          bool t = (cb[3] - cb[0] + 1) * (cb[4] - cb[1] + 1) * (cb[5] - cb[2] + 1) > 64;
-          for (uint32_t z = cb[2]; z <= cb[5] && !t; z++)
-            for (uint32_t y = cb[1]; y <= cb[4] && !t; y++)
-              for (uint32_t x = cb[0]; x <= cb[3] && !t; x++) t = cell_marked(smap, x, y, z);
-          split = t && hanging(v, nset, nmask);
-        } else {
-          split = hanging(v, vset, vmask);
-          if (!split) flags[i] = fl | 2;
-        }
-      }
+#pragma unroll
+  for (int k = 0; k < kPer; k++)
+    split[k] = (fl[k] & 1) && (!(fl[k] & 2) || cells_touched(cells, v[k]));
+#pragma unroll
+  for (int k = 0; k < kPer; k++) {
+    const int64_t i = c * kChunk + 64 * k + lane;
+    const bool checked = fl[k] & 2;
+    if (split[k]) {
+      split[k] = hanging(v[k], checked ? nset : vset, checked ? nmask : vmask);
+      if (!split[k] && !checked) flags[i] = fl[k] | 2;
     }
-    list_split(split, (uint32_t)i, splitc, list0, slist);
+    list_split(split[k], (uint32_t)i, splitc, list0, slist);
   }
 }
 
@@ -2208,7 +2161,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
                          dense_last ? nullptr : (const uint32_t*)(ns.as<uint64_t>() + nscap), d_splitc, splitc,
                          nullptr);
     else
-      hipLaunchKernelGGL(k_mark_tail, dim3(nblocks(cur, kChunk * kTailChunks)), dim3(kChunk), 0, st, cur, nmain,
+      hipLaunchKernelGGL(k_mark_tail, dim3(nblocks(cur, 256 / 64 * kChunk)), dim3(256), 0, st, cur, nmain,
                          A.verts.as<uint64_t>(), A.flags.as<uint8_t>(), vs.as<uint64_t>(), vcap - 1,
                          ns.as<uint64_t>(), nscap - 1, (const uint32_t*)(ns.as<uint64_t>() + nscap),
                          cbox.as<uint32_t>(), d_splitc, splitc, cntb.as<uint32_t>(), (int)(cur > nmain));
