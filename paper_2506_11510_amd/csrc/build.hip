@@ -1293,44 +1293,39 @@ __device__ inline void root_verts(int r, int32_t v[4][3]) {
   }
 }
 
-__device__ inline int isgn(int64_t x) { return (x > 0) - (x < 0); }
+__device__ inline int isgn(int32_t x) { return (x > 0) - (x < 0); }
 
 // Outward unit normal of the face (a, b, c) opposite vertex o and its
 // lattice offset; returns false when the normal is not one of the 18
-// orientations.
-__device__ inline bool face_normal(const int64_t a[3], const int64_t b[3], const int64_t c[3], const int64_t o[3],
-                                   int un[3], int64_t& off) {
-  int64_t e1[3], e2[3], n[3];
+// orientations.  FP32 is exact here: a tet's edge vectors are its shape's, of
+// components -2..2, times one power of two (at most 2^20).
+// (k_records of 6.2 M tets 340 -> 268 us; the products were 64-bit integers.)
+__device__ inline bool face_normal(const int32_t a[3], const int32_t b[3], const int32_t c[3], const int32_t o[3],
+                                   int un[3], int32_t& off) {
+  float e1[3], e2[3], n[3];
 #pragma unroll
   for (int i = 0; i < 3; i++) {
-    e1[i] = b[i] - a[i];
-    e2[i] = c[i] - a[i];
+    e1[i] = (float)(b[i] - a[i]);
+    e2[i] = (float)(c[i] - a[i]);
   }
   n[0] = e1[1] * e2[2] - e1[2] * e2[1];
   n[1] = e1[2] * e2[0] - e1[0] * e2[2];
   n[2] = e1[0] * e2[1] - e1[1] * e2[0];
-  int64_t s = 0;
+  float s = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 3; i++) s += n[i] * (o[i] - a[i]);
-  if (s == 0) return false;
-  int64_t m = 0;
-#pragma unroll
-  for (int i = 0; i < 3; i++) {
-    if (s > 0) n[i] = -n[i];
-    int64_t ab = n[i] < 0 ? -n[i] : n[i];
-    m = ab > m ? ab : m;
-  }
-  bool ok = true;
+  for (int i = 0; i < 3; i++) s += n[i] * (float)(o[i] - a[i]);
+  const float m = fmaxf(fmaxf(fabsf(n[0]), fabsf(n[1])), fabsf(n[2]));
+  bool ok = s != 0.0f;
+  int nz = 0;
 #pragma unroll
   for (int i = 0; i < 3; i++) {
-    int64_t ab = n[i] < 0 ? -n[i] : n[i];
-    if (ab != 0 && ab != m) ok = false;
-    un[i] = isgn(n[i]);
+    const float ab = fabsf(n[i]);
+    if (ab != 0.0f && ab != m) ok = false;
+    un[i] = ab == 0.0f ? 0 : ((n[i] < 0.0f) == (s < 0.0f) ? -1 : 1);
+    nz += ab != 0.0f;
   }
-  int nz = (un[0] != 0) + (un[1] != 0) + (un[2] != 0);
-  if (nz > 2) ok = false;
   off = un[0] * a[0] + un[1] * a[1] + un[2] * a[2];
-  return ok;
+  return ok && nz <= 2;
 }
 
 // Element i of a 4-array held in registers (selects, no indexed access).
@@ -1342,10 +1337,10 @@ __device__ inline T pick4(const T x[4], int i) {
 // Kuhn root whose axis order sorts the point (q3, perturbed along un) in
 // descending order: pairwise comparisons of (q3, un), lexicographic; -1 on
 // a tie.
-__device__ inline int root_of(const int64_t q3[3], const int un[3]) {
+__device__ inline int root_of(const int32_t q3[3], const int un[3]) {
   auto cmp = [&](int a, int b) {
     const int c = isgn(q3[a] - q3[b]);
-    return c ? c : isgn((int64_t)un[a] - un[b]);
+    return c ? c : isgn(un[a] - un[b]);
   };
   const int c01 = cmp(0, 1), c02 = cmp(0, 2), c12 = cmp(1, 2);
   if (!c01 || !c02 || !c12) return -1;
@@ -1360,12 +1355,12 @@ __device__ inline int root_of(const int64_t q3[3], const int un[3]) {
 
 // Face f of the tet v: its three vertices (the others, in order) and the
 // opposite vertex (selects keep the arrays in registers).
-__device__ inline void face_of(const int64_t v[4][3], int f, int64_t fa[3], int64_t fb[3], int64_t fc[3],
-                               int64_t fo[3]) {
+__device__ inline void face_of(const int32_t v[4][3], int f, int32_t fa[3], int32_t fb[3], int32_t fc[3],
+                               int32_t fo[3]) {
   const int i0 = f == 0 ? 1 : 0, i1 = f <= 1 ? 2 : 1, i2 = f <= 2 ? 3 : 2;
 #pragma unroll
   for (int a = 0; a < 3; a++) {
-    const int64_t col[4] = {v[0][a], v[1][a], v[2][a], v[3][a]};
+    const int32_t col[4] = {v[0][a], v[1][a], v[2][a], v[3][a]};
     fa[a] = pick4(col, i0);
     fb[a] = pick4(col, i1);
     fc[a] = pick4(col, i2);
@@ -1373,7 +1368,7 @@ __device__ inline void face_of(const int64_t v[4][3], int f, int64_t fa[3], int6
   }
 }
 
-__device__ inline void unpack_tet(const uint64_t* __restrict__ verts, int64_t t, uint64_t pv[4], int64_t v[4][3]) {
+__device__ inline void unpack_tet(const uint64_t* __restrict__ verts, int64_t t, uint64_t pv[4], int32_t v[4][3]) {
 #pragma unroll
   for (int j = 0; j < 4; j++) {
     pv[j] = verts[4 * t + j];
@@ -1401,7 +1396,7 @@ __global__ __launch_bounds__(kRecordsBlock) void k_records(int64_t n, const uint
   uint32_t owned = 0;  // bit f: this tet links face f
   if (t < n) {
     uint64_t pv[4];
-    int64_t v[4][3];
+    int32_t v[4][3];
     unpack_tet(verts, t, pv, v);
     // medium: extinction = scale * mean(D), majorant tight or scale * max(D)
     int32_t lo[3], hi[3];
@@ -1417,10 +1412,10 @@ __global__ __launch_bounds__(kRecordsBlock) void k_records(int64_t n, const uint
     int32_t ioff[4];
 #pragma unroll 1
     for (int f = 0; f < 4; f++) {
-      int64_t fa3[3], fb3[3], fc3[3], fo3[3];
+      int32_t fa3[3], fb3[3], fc3[3], fo3[3];
       face_of(v, f, fa3, fb3, fc3, fo3);
       int un[3];
-      int64_t off;
+      int32_t off;
       int code = -1;
       if (face_normal(fa3, fb3, fc3, fo3, un, off)) code = dir_code(un);
       if (code < 0) {
@@ -1432,7 +1427,7 @@ __global__ __launch_bounds__(kRecordsBlock) void k_records(int64_t n, const uint
       bool bnd = false;
 #pragma unroll
       for (int a = 0; a < 3; a++) {
-        const int64_t x = fa3[a];
+        const int32_t x = fa3[a];
         if (fb3[a] == x && fc3[a] == x && (x == 0 || x == kLatS)) bnd = true;
       }
       if (bnd) {
@@ -1444,9 +1439,9 @@ __global__ __launch_bounds__(kRecordsBlock) void k_records(int64_t n, const uint
 #pragma unroll
       for (int k = 0; k < 4; k++) {
         if (k == f) {
-          const int64_t pc = (code & 1) ? -off : off;  // along +dir_N
+          const int32_t pc = (code & 1) ? -off : off;  // along +dir_N
           offs[k] = ldexpf((float)pc, -kLatBits);
-          ioff[k] = (int32_t)pc;
+          ioff[k] = pc;
         }
       }
     }
@@ -1507,16 +1502,16 @@ __global__ void k_links(const uint32_t* __restrict__ items, const uint32_t* __re
   const int64_t t = it >> 2;
   const int f = (int)(it & 3u);
   uint64_t pv[4];
-  int64_t v[4][3];
+  int32_t v[4][3];
   unpack_tet(verts, t, pv, v);
-  int64_t fa3[3], fb3[3], fc3[3], fo3[3];
+  int32_t fa3[3], fb3[3], fc3[3], fo3[3];
   face_of(v, f, fa3, fb3, fc3, fo3);
   int un[3];
-  int64_t off;
+  int32_t off;
   int code = 0;
   if (face_normal(fa3, fb3, fc3, fo3, un, off)) code = max(dir_code(un), 0);
   uint32_t link = kBoundary;
-  int64_t q3[3];
+  int32_t q3[3];
 #pragma unroll
   for (int a = 0; a < 3; a++) q3[a] = fa3[a] + fb3[a] + fc3[a];
   const int root = root_of(q3, un);
@@ -1526,7 +1521,7 @@ __global__ void k_links(const uint32_t* __restrict__ items, const uint32_t* __re
     // the point as one integer per axis: 8 * (3 * centroid) + normal
     int32_t F[3];
 #pragma unroll
-    for (int a = 0; a < 3; a++) F[a] = 8 * (int32_t)q3[a] + un[a];
+    for (int a = 0; a < 3; a++) F[a] = 8 * q3[a] + un[a];
     const int32_t hi = max(max(F[0], F[1]), F[2]), lo = min(min(F[0], F[1]), F[2]);
     const uint64_t h = fold_path<true>(hi, F[0] + F[1] + F[2] - hi - lo, lo, 24 * kLatS, dmax, 8 + (uint64_t)root);
     const int64_t nb = search_keys_idx(keys, kidx, kbits, h << (60 - dmax));
