@@ -751,6 +751,7 @@ __global__ void k_merge(int64_t nmain, int64_t m, int64_t total, const uint64_t*
 // Exclusive scan of n uint32 values, 1024 per block (256 threads x 4).
 constexpr int kScanThreads = 256, kScanItems = 4, kScanBlock = kScanThreads * kScanItems;
 
+template <int THREADS = kScanThreads>
 __device__ inline uint32_t block_exclusive(uint32_t x, uint32_t* wsum, uint32_t* total) {
   int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   uint32_t inc = x;
@@ -762,7 +763,7 @@ __device__ inline uint32_t block_exclusive(uint32_t x, uint32_t* wsum, uint32_t*
   if (lane == 63) wsum[wid] = inc;
   __syncthreads();
   uint32_t pre = 0, tot = 0;
-  for (int w = 0; w < kScanThreads / 64; w++) {
+  for (int w = 0; w < THREADS / 64; w++) {
     if (w < wid) pre += wsum[w];
     tot += wsum[w];
   }
@@ -1108,6 +1109,7 @@ __global__ void k_seed_write(int64_t n, const uint64_t* __restrict__ ids, const 
 // probes the whole vertex set (flag bit 1 is never set here), and the last
 // split leaves the list of its new leaves for the rounds that follow.
 constexpr uint32_t kBarrierSpins = 1u << 24;  // about a second of s_sleep per barrier
+constexpr int kSmallThreads = 1024;
 constexpr int64_t kSmallCap = 1 << 21;         // leaves the cooperative rounds may reach
 constexpr int64_t kAppendRatio = 16;           // tail rounds: fewer than leaves / 16 splits
 
@@ -1123,23 +1125,39 @@ struct SmallRounds {
   uint64_t vmask;
   uint32_t* vcount;
   uint32_t* state;  // out: [0] leaves, [1] rounds, [2] splits of the last round, [3] converged;
-                    // [4] barrier arrivals (zero at launch), [5] nonzero: a barrier timed out
+                    // [5] nonzero: a barrier timed out
+  uint32_t* bar;    // grid barrier (kBarWords)
   int64_t cur0, cap;
 };
 
-// Grid barrier number k (1, 2, ...): every block adds one arrival, then waits
-// until k * gridDim.x arrivals are in.  The wait is bounded; on time-out the
-// error word is set and every block leaves the kernel at its next check.
-__device__ inline bool grid_barrier(uint32_t* arrivals, uint32_t* err, uint32_t k, int* s_ok) {
+// Grid barrier number k (1, 2, ...) of kBarLines lines of 128 bytes, zero at
+// launch.  A block arrives at one of kBarSlots counters, the last of a slot at
+// the common one, and the last there opens every slot's flag, which the
+// slot's blocks poll: on one address the arrivals and polls of 128 blocks
+// serialised (2.5 us more a barrier; a build of 6.2 M tets, with some 40
+// barriers, 5.03 -> 4.93 ms).  The wait is bounded; on time-out
+// the error word is set and every block leaves the kernel at its next check.
+constexpr int kBarSlots = 8, kBarLines = 2 * kBarSlots + 1, kBarWords = 32 * kBarLines;
+
+__device__ inline bool grid_barrier(uint32_t* bar, uint32_t* err, uint32_t k, int* s_ok) {
   __syncthreads();
   if (threadIdx.x == 0) {
+    const uint32_t slot = blockIdx.x % kBarSlots, slots = min((uint32_t)kBarSlots, gridDim.x);
+    const uint32_t members = (gridDim.x - slot + kBarSlots - 1) / kBarSlots;
+    uint32_t* flag = bar + 32 * (kBarSlots + 1);
     __threadfence();
-    atomicAdd(arrivals, 1u);
-    const uint32_t target = k * gridDim.x;
+    if (atomicAdd(&bar[32 * (1 + slot)], 1u) + 1 == k * members) {
+      __threadfence();
+      if (atomicAdd(&bar[0], 1u) + 1 == k * slots) {
+        __threadfence();
+        for (uint32_t s = 0; s < slots; s++)
+          __hip_atomic_store(&flag[32 * s], k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
     int ok = 1;
     // relaxed polling (an acquiring load would invalidate this XCD's L2 on
     // every poll, under the blocks still working); one fence after the wait
-    for (uint32_t spin = 0; __hip_atomic_load(arrivals, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target;
+    for (uint32_t spin = 0; __hip_atomic_load(&flag[32 * slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < k;
          spin++) {
       if (spin >= kBarrierSpins) {
         atomicOr(err, 1u);
@@ -1156,22 +1174,22 @@ __device__ inline bool grid_barrier(uint32_t* arrivals, uint32_t* err, uint32_t 
   return *s_ok != 0;
 }
 
-__global__ __launch_bounds__(256) void k_small_rounds(SmallRounds S, Pyramid P, CamCrit cc, WantParams wp) {
-  __shared__ uint32_t ws[kScanThreads / 64];
+__global__ __launch_bounds__(kSmallThreads) void k_small_rounds(SmallRounds S, Pyramid P, CamCrit cc, WantParams wp) {
+  __shared__ uint32_t ws[kSmallThreads / 64];
   __shared__ int s_ok;
   const int64_t nb = gridDim.x, b = blockIdx.x;
   uint32_t nbar = 0, last = 0, rounds = 0, conv = 0;
   int src = 0;
   int64_t cur = S.cur0;
   while (cur <= S.cap / 2) {
-    const int64_t chunk = ((cur + nb - 1) / nb + 255) / 256 * 256;
+    const int64_t chunk = ((cur + nb - 1) / nb + kSmallThreads - 1) / kSmallThreads * kSmallThreads;
     const int64_t lo = b * chunk, hi = min(cur, lo + chunk);
     const uint64_t* ids = S.ids[src];
     const uint64_t* verts = S.verts[src];
     uint8_t* flags = S.flags[src];
     // mark
     uint32_t part = 0;
-    for (int64_t base = lo; base < hi; base += 256) {
+    for (int64_t base = lo; base < hi; base += kSmallThreads) {
       const int64_t i = base + threadIdx.x;
       if (i < hi) {
         uint64_t v[4] = {verts[4 * i], verts[4 * i + 1], verts[4 * i + 2], verts[4 * i + 3]};
@@ -1187,19 +1205,19 @@ __global__ __launch_bounds__(256) void k_small_rounds(SmallRounds S, Pyramid P, 
       }
     }
     uint32_t btot;
-    block_exclusive(part, ws, &btot);
+    block_exclusive<kSmallThreads>(part, ws, &btot);
     if (threadIdx.x == 0) S.bsum[b] = btot;
-    if (!grid_barrier(&S.state[4], &S.state[5], ++nbar, &s_ok)) return;
+    if (!grid_barrier(S.bar, &S.state[5], ++nbar, &s_ok)) return;
     // output offset of this block and the new leaf count
     uint32_t pre = 0, tot = 0;
-    for (int64_t k = threadIdx.x; k < nb; k += 256) {
+    for (int64_t k = threadIdx.x; k < nb; k += kSmallThreads) {
       const uint32_t x = S.bsum[k];
       tot += x;
       if (k < b) pre += x;
     }
     uint32_t bpre, btot2;
-    block_exclusive(pre, ws, &bpre);
-    block_exclusive(tot, ws, &btot2);
+    block_exclusive<kSmallThreads>(pre, ws, &bpre);
+    block_exclusive<kSmallThreads>(tot, ws, &btot2);
     pre = bpre;
     tot = btot2;
     if ((int64_t)tot == cur) {
@@ -1208,11 +1226,11 @@ __global__ __launch_bounds__(256) void k_small_rounds(SmallRounds S, Pyramid P, 
     }
     // split
     uint32_t carry = pre;
-    for (int64_t base = lo; base < hi; base += 256) {
+    for (int64_t base = lo; base < hi; base += kSmallThreads) {
       const int64_t i = base + threadIdx.x;
       const uint32_t x = i < hi ? S.cnt[i] : 0u;
       uint32_t t;
-      const uint32_t ex = block_exclusive(x, ws, &t);
+      const uint32_t ex = block_exclusive<kSmallThreads>(x, ws, &t);
       bool added = false;
       if (i < hi)
         added = split_one(i, (int64_t)carry + ex, x != 1u, ids, verts, flags, S.chain[src], S.ids[src ^ 1],
@@ -1221,7 +1239,7 @@ __global__ __launch_bounds__(256) void k_small_rounds(SmallRounds S, Pyramid P, 
       block_count(added, S.vcount);
       carry += t;
     }
-    if (!grid_barrier(&S.state[4], &S.state[5], ++nbar, &s_ok)) return;
+    if (!grid_barrier(S.bar, &S.state[5], ++nbar, &s_ok)) return;
     last = (uint32_t)(tot - cur);
     cur = tot;
     src ^= 1;
@@ -1983,8 +2001,8 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
   // [2] finalize error, [3] listed faces, [4] scan total, [5] running count of marked splits,
   // [6, 6 + kCountSlots) vertex count slots, [24, 30) small-round state
   Buf misc;
-  if (!misc.ensure(128)) return fail(TET_ERR_OUT_OF_MEMORY, "leb_build: scratch");
-  TV_HIP(hipMemsetAsync(misc.p, 0, 128, st));
+  if (!misc.ensure(128 + kBarWords * 4)) return fail(TET_ERR_OUT_OF_MEMORY, "leb_build: scratch");
+  TV_HIP(hipMemsetAsync(misc.p, 0, 128 + kBarWords * 4, st));
   int* d_flag = misc.as<int>();
   uint32_t* d_total = misc.as<uint32_t>() + 4;
   uint32_t* d_splitc = misc.as<uint32_t>() + 5;
@@ -2020,11 +2038,12 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
   TV_HIP(hipGetDevice(&dev));
   TV_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
   TV_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  TV_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(k_small_rounds), 256, 0));
+  TV_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(k_small_rounds), kSmallThreads, 0));
   const int64_t small_cap = std::min<int64_t>(kSmallCap, o.max_tets);
   const bool small = !prev && !o.host_rounds && coop && occ > 0 && ncu > 0 && small_cap >= 12;
-  // half the CUs: the rounds are small, and every block adds an arrival to
-  // each grid barrier (128 blocks measured best on 256 CUs)
+  // half the CUs: every block takes part in each grid barrier (a build of
+  // 6.2 M tets: 64 blocks 5.03 ms, 128 4.93, 256 5.07), with 1024 threads
+  // each, for the later rounds' latencies (256 threads: 160 us more)
   const int small_blocks = std::max(1, ncu / 2);
 
   uint32_t* hbuf = nullptr;
@@ -2128,12 +2147,13 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
     S.vmask = vcap - 1;
     S.vcount = d_vcount;
     S.state = misc.as<uint32_t>() + 24;
+    S.bar = misc.as<uint32_t>() + 32;
     S.cur0 = cur;
     S.cap = small_cap;
     void* args[] = {&S, &P, &cc, &wp};
     // a refused cooperative launch (its blocks could not all be resident)
     // changed nothing: the host-driven rounds below then do all the work
-    if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_small_rounds), dim3(small_blocks), dim3(256), args,
+    if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_small_rounds), dim3(small_blocks), dim3(kSmallThreads), args,
                                    0, st) != hipSuccess) {
       (void)hipGetLastError();
     } else {
