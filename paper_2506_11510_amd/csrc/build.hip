@@ -1892,7 +1892,7 @@ static int64_t scan_u32(const uint32_t* in, int64_t n, uint32_t* out, Buf& bsum,
 // already the result.
 static int seed_from_grid(const tet_grid* prev, const Pyramid& P, const CamCrit& cc, const WantParams& wp,
                           Leaves& A, Buf& wk, Buf& vs, uint64_t* vcap, Buf& bsum, uint32_t* d_total,
-                          uint32_t* d_count, uint32_t* d_vcount, uint32_t* hbuf, hipStream_t st, int64_t* cur,
+                          uint32_t* d_count, uint32_t* d_vcount, hipStream_t st, int64_t* cur,
                           int64_t* nwork, bool allow_same, bool* unchanged) {
   const int64_t n = prev->n;
   const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
@@ -1912,9 +1912,9 @@ static int seed_from_grid(const tet_grid* prev, const Pyramid& P, const CamCrit&
     TV_HIP(hipMemsetAsync(d_count, 0, 4, st));
     hipLaunchKernelGGL(k_chain_diff, dim3(nblocks(n, 256)), dim3(256), 0, st, n,
                        (const uint64_t*)bits.as<uint64_t>(), (const uint64_t*)prev->chain, d_count);
-    TV_HIP(hipMemcpyAsync(hbuf, d_count, 4, hipMemcpyDeviceToHost, st));
-    TV_HIP(hipStreamSynchronize(st));
-    if (hbuf[0] == 0) {
+    uint32_t diff = 0;
+    TV_HIP(fetch(&diff, d_count, 4, st));
+    if (diff == 0) {
       *unchanged = true;
       return TET_OK;
     }
@@ -1923,9 +1923,9 @@ static int seed_from_grid(const tet_grid* prev, const Pyramid& P, const CamCrit&
                      bits.as<uint64_t>(), first.as<uint32_t>());
   if (scan_u32(first.as<uint32_t>(), n, pos.as<uint32_t>(), bsum, d_total, st))
     return fail(TET_ERR_OUT_OF_MEMORY, "leb_update: seed scan");
-  TV_HIP(hipMemcpyAsync(hbuf, d_total, 4, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));
-  const int64_t m = hbuf[0];
+  uint32_t count = 0;
+  TV_HIP(fetch(&count, d_total, 4, st));
+  const int64_t m = count;
   if (m < 6 || m > n) return fail(TET_ERR_INTERNAL, "leb_update: bad seed size");
   if (!A.ensure(std::max<int64_t>(m, 1 << 16)) || !wk.ensure((size_t)m * 4))
     return fail(TET_ERR_OUT_OF_MEMORY, "leb_update: seed leaves");
@@ -1942,10 +1942,9 @@ static int seed_from_grid(const tet_grid* prev, const Pyramid& P, const CamCrit&
                      A.verts.as<uint64_t>(), A.flags.as<uint8_t>(), A.chain.as<uint64_t>(), wk.as<uint32_t>(), d_count,
                      vs.as<uint64_t>(), cap - 1, d_vcount);
   TV_HIP(hipGetLastError());
-  TV_HIP(hipMemcpyAsync(hbuf, d_count, 4, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));  // before the scratch returns to the pool
+  TV_HIP(fetch(&count, d_count, 4, st));  // (before the scratch returns to the pool)
   *cur = m;
-  *nwork = hbuf[0];
+  *nwork = count;
   *vcap = cap;
   return TET_OK;
 }
@@ -2017,8 +2016,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
          : !make_pyramid(d_dens, n, L, P, lv, st))
     return fail(TET_ERR_OUT_OF_MEMORY, "leb_build: pyramid");
   int flag = 0;
-  TV_HIP(hipMemcpyAsync(&flag, d_flag, 4, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));
+  TV_HIP(fetch(&flag, d_flag, 4, st));
   if (flag & 6) return fail(TET_ERR_INVALID_ARG, "leb_build_sparse: brick coordinates out of range or listed twice");
   if (flag) return fail(TET_ERR_NUMERIC, "leb_build: density has NaN, infinite or negative values");
 
@@ -2046,12 +2044,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
   // each, for the later rounds' latencies (256 threads: 160 us more)
   const int small_blocks = std::max(1, ncu / 2);
 
-  uint32_t* hbuf = nullptr;
-  TV_HIP(hipHostMalloc((void**)&hbuf, 128, hipHostMallocDefault));
-  struct HostFree {
-    uint32_t* p;
-    ~HostFree() { if (p) (void)hipHostFree(p); }
-  } hf{hbuf};
+  uint32_t hbuf[32];
   Leaves A, B;
   int64_t cur = 6, nwork = 6;
   Buf vs, vs_old, cntb, offb, bsum, ns, wk;  // ns: vertices made by the last split pass; wk: its new leaves
@@ -2060,7 +2053,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
     // the seed from the previous grid's tree
     bool same = false;
     if (int rc = seed_from_grid(prev, P, cc, wp, A, wk, vs, &vcap, bsum, d_total, misc.as<uint32_t>() + 31,
-                                d_vcount, hbuf, st, &cur, &nwork, prev->majorant_mode == o.majorant_mode, &same))
+                                d_vcount, st, &cur, &nwork, prev->majorant_mode == o.majorant_mode, &same))
       return rc;
     if (same) {  // the previous tree is the result; its tets take the new volume's extinction
       hipLaunchKernelGGL(k_refresh_medium, dim3(nblocks(prev->n, 256)), dim3(256), 0, st, prev->n, prev->verts, P,
@@ -2157,8 +2150,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
                                    0, st) != hipSuccess) {
       (void)hipGetLastError();
     } else {
-      TV_HIP(hipMemcpyAsync(hbuf + 24, S.state, 24, hipMemcpyDeviceToHost, st));
-      TV_HIP(hipStreamSynchronize(st));
+      TV_HIP(fetch(hbuf + 24, S.state, 24, st));
       if (hbuf[29]) return fail(TET_ERR_INTERNAL, "leb_build: grid barrier of the small rounds timed out");
       cur = hbuf[24];
       rounds = (int)hbuf[25];
@@ -2186,8 +2178,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
                        cc, wp, vs.as<uint64_t>(), vcap - 1, d_splitc, splitc, nmain < 0 ? nullptr : cntb.as<uint32_t>());
     if (nmain < 0 && scan_u32(cntb.as<uint32_t>(), cur, offb.as<uint32_t>(), bsum, d_total, st))
       return fail(TET_ERR_OUT_OF_MEMORY, "leb_build: scan");
-    TV_HIP(hipMemcpyAsync(hbuf, d_total, (2 + kCountSlots) * 4, hipMemcpyDeviceToHost, st));
-    TV_HIP(hipStreamSynchronize(st));
+    TV_HIP(fetch(hbuf, d_total, (2 + kCountSlots) * 4, st));
     const int64_t total = nmain < 0 ? (int64_t)hbuf[0] : cur + (int64_t)(hbuf[1] - splitc);
     uint64_t vcount = 0;
     for (int k = 0; k < kCountSlots; k++) vcount += hbuf[2 + k];
@@ -2328,9 +2319,8 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
   cbox.release();
   if (he == hipSuccess) {
     hipLaunchKernelGGL(k_keys, dim3(nblocks(cur, 1024)), dim3(1024), 0, st, cur, g->ids, g->keys, d_flag + 1);
-    he = hipMemcpyAsync(&flag, d_flag + 1, 4, hipMemcpyDeviceToHost, st);
+    he = fetch(&flag, d_flag + 1, 4, st);
   }
-  if (he == hipSuccess) he = hipStreamSynchronize(st);
   if (he != hipSuccess) {
     tet_grid_free(g);
     return fail(TET_ERR_DEVICE, std::string("leb_build: ") + hipGetErrorString(he));
@@ -2366,9 +2356,8 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
   hipLaunchKernelGGL(k_links, dim3(nblocks(item_cap, 128)), dim3(128), 0, st, items.as<uint32_t>(), d_items, item_cap,
                      cur, g->verts, g->keys, g->kidx, g->kbits, g->max_depth, g->rec, g->rec32, d_flag + 2);
   int ferr = 0;
-  he = hipMemcpyAsync(&ferr, d_flag + 2, 4, hipMemcpyDeviceToHost, st);
-  if (he == hipSuccess) he = hipEventRecord(e1, st);
-  if (he == hipSuccess) he = hipStreamSynchronize(st);
+  he = hipEventRecord(e1, st);
+  if (he == hipSuccess) he = fetch(&ferr, d_flag + 2, 4, st);
   if (he != hipSuccess) {
     tet_grid_free(g);
     return fail(TET_ERR_DEVICE, std::string("leb_build: ") + hipGetErrorString(he));
@@ -2465,8 +2454,7 @@ int grid_set_channels(tet_grid* g, const tet_channels* ch, hipStream_t st) {
     hipLaunchKernelGGL(k_check_channel, dim3(nblocks(nvox, 256)), dim3(256), 0, st, d[k], nvox, k, flag.as<int>());
   }
   int bad = 0;
-  TV_HIP(hipMemcpyAsync(&bad, flag.p, 4, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));
+  TV_HIP(fetch(&bad, flag.p, 4, st));
   if (bad)
     return fail(TET_ERR_NUMERIC, "tet_grid_set_channels: temperature < 0 or not finite, albedo outside [0, 1] or g "
                                  "outside (-1, 1)");
@@ -2692,8 +2680,7 @@ int grid_set_density_model(tet_grid* g, const tet_density* dens, int32_t model, 
   TV_HIP(hipMemsetAsync(flag.p, 0, 4, st));
   hipLaunchKernelGGL(k_check_density, dim3(nblocks(nvox, 256)), dim3(256), 0, st, d, nvox, flag.as<int>());
   int bad = 0;
-  TV_HIP(hipMemcpyAsync(&bad, flag.p, 4, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));
+  TV_HIP(fetch(&bad, flag.p, 4, st));
   if (bad) return fail(TET_ERR_NUMERIC, "tet_grid_set_density_model: density values must be finite and >= 0");
   own.maj = (float*)dev_alloc((size_t)g->n * 4);
   own.rec = (TetRec*)dev_alloc((size_t)g->n * sizeof(TetRec));

@@ -429,6 +429,8 @@ int fail(int status, const std::string& msg);
 // Device-memory cache: blocks freed by the library are kept for reuse.
 void* dev_alloc(size_t bytes);
 void dev_free(void* p);
+// Copies bytes from the device once the stream's work is done (synchronises).
+hipError_t fetch(void* dst, const void* src, size_t bytes, hipStream_t st);
 
 #define TV_HIP(call)                                                                       \
   do {                                                                                     \

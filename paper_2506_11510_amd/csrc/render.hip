@@ -1683,8 +1683,7 @@ static int walk_light_queue(const Med& med, const RenderArgs& P, bool model, Lig
     return TET_OK;
   }
   uint32_t n = 0;
-  TV_HIP(hipMemcpyAsync(&n, P.head + kChunkAt, 4, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));
+  TV_HIP(fetch(&n, P.head + kChunkAt, 4, st));
   n = std::min(n, P.lq_chunks) * P.lq_chunk;
   if (!n) return TET_OK;
   hipLaunchKernelGGL(k_light_keys<BATCH>, dim3((n + 255) / 256), dim3(256), 0, st, P, n, ls.keys[0], ls.idx[0], ls.bits);
@@ -1759,17 +1758,35 @@ static void launch_render(const RenderArgs& P, const Med& med, bool ext, int wav
   }
 }
 
+// The statistics' slots on the host, to be summed.
+struct HostStats {
+  uint32_t w[kStatSlots * kLine];
+  hipError_t fetch(const uint32_t* head, hipStream_t st) {
+    return tv::fetch(w, head + kStatAt, sizeof(w), st);
+  }
+  int64_t sum(int q) const {
+    uint64_t s = 0;
+    for (int k = 0; k < kStatSlots; k++) {
+      uint64_t v;
+      memcpy(&v, w + k * kLine + 2 * q, 8);
+      s += v;
+    }
+    return (int64_t)s;
+  }
+};
+
 template <class Med, int NRC>
 static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, int32_t spp, int64_t npix,
                       int64_t pass_cap, hipStream_t st, float* ms_total, float* ms_trace, float* ms_cache,
-                      bool timed = true, LightSort* ls = nullptr) {
+                      bool timed = true, LightSort* ls = nullptr, HostStats* hs = nullptr) {
   if (A.defer && !ls) return fail(TET_ERR_INTERNAL, "render: light-ray queue without its sort");
   int bs = o.block_size ? o.block_size : 256;
   int bpc = o.blocks_per_cu ? o.blocks_per_cu : 8;
   const bool ext = A.ex.model != 0 || A.ex.ch_t || A.ex.ch_a || A.ex.ch_g;
   // several contributions per pixel: passes, queued light rays, cache queries
   const bool several = pass_cap < spp || A.defer || NRC == 1;
-  // timed: HIP events around the passes, waited for after each pass;
+  // timed: HIP events around the passes, waited for after each pass (after
+  // the last one together with the statistics, hs);
   // untimed: kernel launches on the stream only
   hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr, t0 = nullptr, t1 = nullptr;
   struct Ev {
@@ -1789,6 +1806,14 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
   *ms_total = 0.0f;
   *ms_trace = 0.0f;
   *ms_cache = 0.0f;
+  auto pass_times = [&]() -> int {
+    float ms = 0.0f;
+    TV_HIP(hipEventElapsedTime(&ms, t0, t1));
+    *ms_trace += ms;
+    TV_HIP(hipEventElapsedTime(&ms, t1, e2));
+    *ms_cache += ms;
+    return TET_OK;
+  };
   if (timed) TV_HIP(hipEventRecord(e0, st));
   for (int32_t done = 0; done < spp; done += (int32_t)pass_cap) {
     A.pass_start = A.pass_start + (done ? (int32_t)pass_cap : 0);
@@ -1821,12 +1846,10 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
       if (int rc = nrc_query_pass(A.nrc, A.qbuf, A.qpix, A.qcount, A.out, (int64_t)ne, st)) return rc;
     if (timed) {
       TV_HIP(hipEventRecord(e2, st));
-      TV_HIP(hipEventSynchronize(e2));
-      float ms = 0.0f;
-      TV_HIP(hipEventElapsedTime(&ms, t0, t1));
-      *ms_trace += ms;
-      TV_HIP(hipEventElapsedTime(&ms, t1, e2));
-      *ms_cache += ms;
+      if (done + pass_cap < spp) {  // (the last pass's times: below, with one wait for all)
+        TV_HIP(hipEventSynchronize(e2));
+        if (int rc = pass_times()) return rc;
+      }
     }
   }
   if (several && NRC != 2)
@@ -1835,7 +1858,9 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
   TV_HIP(hipGetLastError());
   if (timed) {
     TV_HIP(hipEventRecord(e1, st));
-    TV_HIP(hipEventSynchronize(e1));
+    if (hs) TV_HIP(hs->fetch(A.head, st));
+    else TV_HIP(hipEventSynchronize(e1));
+    if (int rc = pass_times()) return rc;
     TV_HIP(hipEventElapsedTime(ms_total, e0, e1));
   }
   return TET_OK;
@@ -1850,23 +1875,6 @@ static void zero_stats(uint32_t* head, hipStream_t st) {
   constexpr int n = kStatSlots * kLine;
   hipLaunchKernelGGL(k_zero_u32, dim3((n + 255) / 256), dim3(256), 0, st, head + kStatAt, n);
 }
-
-// The statistics' slots on the host (a stream copy), to be summed once it is complete.
-struct HostStats {
-  uint32_t w[kStatSlots * kLine];
-  hipError_t fetch(const uint32_t* head, hipStream_t st) {
-    return hipMemcpyAsync(w, head + kStatAt, sizeof(w), hipMemcpyDeviceToHost, st);
-  }
-  int64_t sum(int q) const {
-    uint64_t s = 0;
-    for (int k = 0; k < kStatSlots; k++) {
-      uint64_t v;
-      memcpy(&v, w + k * kLine + 2 * q, 8);
-      s += v;
-    }
-    return (int64_t)s;
-  }
-};
 
 static int check_render_opts(const tet_render_opts& o) {
   if (o.max_bounces < 1 || o.transmittance < 0 || o.transmittance > 2 || o.max_steps_per_path < 1 ||
@@ -2087,25 +2095,26 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     A.qcount = A.head + kQueryAt;
   }
   float ms = 0.0f, ms_trace = 0.0f, ms_cache = 0.0f;
+  HostStats hs;
   int rc;
   if (kind == 0 && g->rec32 && o.record_layout != 48) {
     TetMedium32 m{model ? g->mrec32 : g->rec32, g->keys, g->n, g->max_depth, shapes, g->kidx, g->kbits};
     rc = nrc ? run_passes<TetMedium32, 1>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
-                                          !noalloc, &ls)
+                                          !noalloc, &ls, &hs)
              : run_passes<TetMedium32, 0>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
-                                          !noalloc, &ls);
+                                          !noalloc, &ls, &hs);
   } else if (kind == 0) {
     if (o.record_layout == 32) return fail(TET_ERR_UNSUPPORTED, "render: this grid has no compact records");
     TetMedium m{model ? g->mrec : g->rec, g->keys, g->n, g->max_depth, shapes, g->kidx, g->kbits};
     rc = nrc ? run_passes<TetMedium, 1>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
-                                        !noalloc, &ls)
+                                        !noalloc, &ls, &hs)
              : run_passes<TetMedium, 0>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
-                                        !noalloc, &ls);
+                                        !noalloc, &ls, &hs);
   } else {
     VoxelMedium m{dens->data, dens->n, dens->density_scale, 0, 1.0f / (float)dens->n};
     while ((1 << m.sh) < dens->n) m.sh++;
     rc = run_passes<VoxelMedium, 0>(m, A, o, spp, npix, pass_cap, st, &ms, &ms_trace, &ms_cache,
-                                    !noalloc, &ls);
+                                    !noalloc, &ls, &hs);
   }
   if (rc) return rc;
   if (noalloc) return TET_OK;
@@ -2131,10 +2140,10 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     TV_HIP(hipEventElapsedTime(&tms, t0, t1));
     ms += tms;
   }
-  HostStats hs;
-  TV_HIP(hs.fetch(A.head, st));
-  if (!on_device) TV_HIP(hipMemcpyAsync(out_rgb, A.out, img_bytes, hipMemcpyDeviceToHost, st));
-  TV_HIP(hipStreamSynchronize(st));
+  if (!on_device) {
+    TV_HIP(hipMemcpyAsync(out_rgb, A.out, img_bytes, hipMemcpyDeviceToHost, st));
+    TV_HIP(hipStreamSynchronize(st));
+  }
   if (stats) {
     stats->tet_steps = hs.sum(0);
     stats->null_collisions = hs.sum(1);
@@ -2499,7 +2508,6 @@ static int batch_run(BatchState* B, const uint64_t* seeds, hipStream_t st, tet_r
   TV_HIP(hipEventRecord(e1, st));
   HostStats hs;
   TV_HIP(hs.fetch(B->A.head, st));
-  TV_HIP(hipStreamSynchronize(st));
   float ms = 0.0f;
   TV_HIP(hipEventElapsedTime(&ms, e0, e1));
   if (stats) {
