@@ -310,6 +310,21 @@ __global__ void k_vset_seed(const uint64_t* __restrict__ verts, int64_t n, uint6
   const bool added = i < 4 * n && vset_add(tab, mask, verts[i]);
   block_count(added, count);
 }
+// Edges (bits in hanging's order) of a tet of depth d whose midpoints can be
+// vertices while no tet deeper than smax has been split.  Every tet around an
+// edge bisects it at the same depth, if it gets there: by tag (columns 3, 2,
+// 1) and edge, the tet's depth plus
+//   x0x1 2 1 0   x0x2 1 0 2   x0x3 0 2 1   x1x2 2 1 2   x1x3 1 2 1   x2x3 2 2 3
+// The rounds split breadth first, so most new leaves are the deepest yet and
+// have no edge to look up: the lookups are random reads of a table past the
+// caches.  Passes over a 6.2 M tet build: want 900 -> 730 us, mark 430 -> 330.
+__host__ __device__ inline uint32_t edges_upto(int d, int smax) {
+  const int s = smax - d, t = tag_of(d);
+  if (s < 0) return 0u;
+  const uint32_t lv = t == 3 ? 0x3F3F1604u : (t == 2 ? 0x3F3F0B02u : 0x3F1F1501u);  // a byte per s
+  return (lv >> (8 * (s < 3 ? s : 3))) & 0xFFu;
+}
+
 
 // ---------------------------------------------------------------- rounds
 // Leaf flags: bit 0 = the want predicate was false (it depends on the tet
@@ -321,7 +336,8 @@ __global__ void k_vset_seed(const uint64_t* __restrict__ verts, int64_t n, uint6
 // True when a vertex of `tab` sits on one of the tet's 6 edge midpoints;
 // the first probes are issued together, collision chains followed only
 // where the first slot holds another key.
-__device__ inline bool hanging(const uint64_t v[4], const uint64_t* __restrict__ tab, uint64_t mask) {
+__device__ inline bool hanging(const uint64_t v[4], const uint64_t* __restrict__ tab, uint64_t mask,
+                               uint32_t edges = 0x3Fu) {
   uint64_t key[6], h[6], e[6];
   bool on[6];
   int k = 0;
@@ -330,7 +346,7 @@ __device__ inline bool hanging(const uint64_t v[4], const uint64_t* __restrict__
 #pragma unroll
     for (int b = a + 1; b < 4; b++, k++) {
       int32_t x = vx(v[a]) + vx(v[b]), y = vy(v[a]) + vy(v[b]), z = vz(v[a]) + vz(v[b]);
-      on[k] = ((x | y | z) & 1) == 0;  // a midpoint on the lattice
+      on[k] = ((x | y | z) & 1) == 0 && ((edges >> k) & 1u);  // a midpoint on the lattice
       key[k] = pack_vertex(x >> 1, y >> 1, z >> 1);
       h[k] = mix64(key[k]) & mask;
     }
@@ -449,7 +465,8 @@ __global__ void k_chunk_boxes(int64_t n, int64_t c0, int64_t c1, const uint64_t*
 }
 
 // Leaves whose want predicate is settled: split only when forced.
-__global__ void k_mark(int64_t n, const uint64_t* __restrict__ verts, uint8_t* __restrict__ flags,
+__global__ void k_mark(int64_t n, int smax, const uint64_t* __restrict__ ids, const uint64_t* __restrict__ verts,
+                       uint8_t* __restrict__ flags,
                        uint32_t* __restrict__ cnt, const uint64_t* __restrict__ vset, uint64_t vmask,
                        const uint64_t* __restrict__ nset, uint64_t nmask, const uint32_t* __restrict__ cells,
                        uint32_t* splitc, uint32_t list0, uint32_t* __restrict__ slist) {
@@ -461,8 +478,9 @@ __global__ void k_mark(int64_t n, const uint64_t* __restrict__ verts, uint8_t* _
       uint64_t v[4] = {verts[4 * i], verts[4 * i + 1], verts[4 * i + 2], verts[4 * i + 3]};
       // checked leaves: the last pass's new vertices (after a dense pass,
       // nset is the whole vertex set and there is no cell map)
-      if (fl & 2) split = (!cells || cells_touched(cells, v)) && hanging(v, nset, nmask);
-      else split = hanging(v, vset, vmask);
+      const uint32_t edges = edges_upto(id_depth(ids[i]), smax);
+      if (fl & 2) split = (!cells || cells_touched(cells, v)) && hanging(v, nset, nmask, edges);
+      else split = hanging(v, vset, vmask, edges);
       if (!split && !(fl & 2)) flags[i] = fl | 2;
       if (!slist) cnt[i] = split ? 2u : 1u;
     }
@@ -538,7 +556,7 @@ __global__ __launch_bounds__(256) void k_mark_tail(int64_t n, int64_t nmain, con
 
 // The leaves made by the last split pass (a dense list, so the want
 // predicate's FP64 work runs on full waves): wanted, or forced.
-__global__ void k_want(int64_t m, const uint32_t* __restrict__ work, const uint64_t* __restrict__ ids,
+__global__ void k_want(int64_t m, int smax, const uint32_t* __restrict__ work, const uint64_t* __restrict__ ids,
                        const uint64_t* __restrict__ verts, uint8_t* __restrict__ flags, uint32_t* __restrict__ cnt,
                        Pyramid P, CamCrit cc, WantParams wp, const uint64_t* __restrict__ vset, uint64_t vmask,
                        uint32_t* splitc, uint32_t list0, uint32_t* __restrict__ slist) {
@@ -549,11 +567,12 @@ __global__ void k_want(int64_t m, const uint32_t* __restrict__ work, const uint6
     i = work[j];
     uint64_t v[4] = {verts[4 * (size_t)i], verts[4 * (size_t)i + 1], verts[4 * (size_t)i + 2],
                      verts[4 * (size_t)i + 3]};
-    split = want(P, cc, wp, v, ids[i]);
+    const uint64_t id = ids[i];
+    split = want(P, cc, wp, v, id);
     uint8_t nf = 0;
     if (!split) {
       nf = 1;
-      split = hanging(v, vset, vmask);
+      split = hanging(v, vset, vmask, edges_upto(id_depth(id), smax));
       if (!split) nf = 3;
     }
     flags[i] = nf;
@@ -1199,7 +1218,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_rounds(SmallRounds S, P
           if (want(P, cc, wp, v, ids[i])) split = true;
           else flags[i] = 1;
         }
-        if (!split) split = hanging(v, S.vset, S.vmask);
+        if (!split) split = hanging(v, S.vset, S.vmask, edges_upto(id_depth(ids[i]), (int)rounds - 1));
         S.cnt[i] = split ? 2u : 1u;
         part += split ? 2u : 1u;
       }
@@ -2160,9 +2179,11 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
     }
   }
   while (!done) {
+    const int smax = (prev ? prev->max_depth : 0) + rounds - 1;  // a round deepens the tree by one level at most
     if (!cntb.ensure(cur * 4) || !offb.ensure(cur * 4)) return fail(TET_ERR_OUT_OF_MEMORY, "leb_build: counts");
     if (nmain < 0)
-      hipLaunchKernelGGL(k_mark, dim3(nblocks(cur, 256)), dim3(256), 0, st, cur, A.verts.as<uint64_t>(),
+      hipLaunchKernelGGL(k_mark, dim3(nblocks(cur, 256)), dim3(256), 0, st, cur, smax, A.ids.as<uint64_t>(),
+                         A.verts.as<uint64_t>(),
                          A.flags.as<uint8_t>(), cntb.as<uint32_t>(), vs.as<uint64_t>(), vcap - 1,
                          dense_last ? vs.as<uint64_t>() : ns.as<uint64_t>(), dense_last ? vcap - 1 : nscap - 1,
                          dense_last ? nullptr : (const uint32_t*)(ns.as<uint64_t>() + nscap), d_splitc, splitc,
@@ -2173,7 +2194,7 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
                          ns.as<uint64_t>(), nscap - 1, (const uint32_t*)(ns.as<uint64_t>() + nscap),
                          cbox.as<uint32_t>(), d_splitc, splitc, cntb.as<uint32_t>(), (int)(cur > nmain));
     if (nwork > 0)  // a seed from a previous grid may list no wanted leaf
-      hipLaunchKernelGGL(k_want, dim3(nblocks(nwork, 256)), dim3(256), 0, st, nwork, wk.as<uint32_t>(),
+      hipLaunchKernelGGL(k_want, dim3(nblocks(nwork, 256)), dim3(256), 0, st, nwork, smax, wk.as<uint32_t>(),
                        A.ids.as<uint64_t>(), A.verts.as<uint64_t>(), A.flags.as<uint8_t>(), cntb.as<uint32_t>(), P,
                        cc, wp, vs.as<uint64_t>(), vcap - 1, d_splitc, splitc, nmain < 0 ? nullptr : cntb.as<uint32_t>());
     if (nmain < 0 && scan_u32(cntb.as<uint32_t>(), cur, offb.as<uint32_t>(), bsum, d_total, st))
