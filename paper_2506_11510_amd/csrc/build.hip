@@ -895,28 +895,78 @@ __device__ inline int common_depth(uint64_t a, uint64_t b) {
   return max(m - (64 - (int)__builtin_clzll(x)), -1);
 }
 
-__global__ void k_seed_chain(int64_t n, const uint64_t* __restrict__ ids, Pyramid P, CamCrit cc, WantParams wp,
-                             uint64_t* __restrict__ keep, uint64_t* __restrict__ bits) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const uint64_t h = ids[p];
-  const int D = id_depth(h);
-  const int c = p ? common_depth(ids[p - 1], h) : -1;
-  uint64_t v[4];
-  root_vertices((int)(h >> D) - 8, v);
-  uint64_t b = 0;
-  for (int d = 0; d <= D; d++) {
-    const uint64_t a = h >> (D - d);
-    if (d > c && want(P, cc, wp, v, a)) b |= 1ull << d;
-    if (d == D) break;
-    uint64_t c0[4], c1[4];
-    children(a, v, c0, c1);
-    const bool right = (h >> (D - d - 1)) & 1;
-#pragma unroll
-    for (int j = 0; j < 4; j++) v[j] = right ? c1[j] : c0[j];
+// The parent of a tet v, its second child if `right`; k is the parent's tag.
+// The bisected edge's far end is 2 z - near end, which also holds for packed
+// vertices (the fields' carries cancel).
+__device__ inline void parent_vertices(uint64_t v[4], int k, bool right) {
+  const uint64_t z = k == 1 ? v[1] : (k == 2 ? v[2] : v[3]);
+  const uint64_t near = !right || k == 1 ? v[0] : (k == 2 ? v[1] : v[2]), far = 2 * z - near;
+  const uint64_t w0 = v[0], w1 = v[1], w2 = v[2];
+  if (right) {  // (x1..xk, z, ...)
+    v[0] = far;
+    v[1] = w0;
+    if (k >= 2) v[2] = w1;
+    if (k == 3) v[3] = w2;
+  } else {
+    if (k == 1) v[1] = far;
+    if (k == 2) v[2] = far;
+    if (k == 3) v[3] = far;
   }
-  keep[p] = c >= 0 ? (~0ull >> (63 - c)) : 0ull;
-  bits[p] = b;
+}
+
+// A node is evaluated by the first leaf below it: two nodes a leaf on average,
+// but nine or more for some leaf of nearly every wave.  So a wave deals its
+// leaves' nodes to its lanes (a search of the leaves' prefix sums), and each
+// lane makes its node's vertices from the leaf's, going up.  Bound by the
+// loads of want.  (Down from the root, each lane its own leaf's nodes: 357 us
+// on 2.5 M leaves; up, each lane its own: 305; now 201.)
+constexpr int kSeedBlock = 256;
+
+__global__ __launch_bounds__(kSeedBlock) void k_seed_chain(int64_t n, const uint64_t* __restrict__ ids,
+                                                           const uint64_t* __restrict__ verts, Pyramid P, CamCrit cc,
+                                                           WantParams wp, uint64_t* __restrict__ keep,
+                                                           uint64_t* __restrict__ bits) {
+  __shared__ uint64_t s_id[kSeedBlock], s_v[4][kSeedBlock];
+  __shared__ unsigned long long s_bits[kSeedBlock];
+  __shared__ int s_end[kSeedBlock];
+  const int64_t p = (int64_t)blockIdx.x * kSeedBlock + threadIdx.x;
+  const int lane = __lane_id(), w0 = threadIdx.x & ~63;
+  int c = -1, nodes = 0;
+  if (p < n) {
+    const uint64_t h = ids[p];
+    if (p) c = common_depth(ids[p - 1], h);
+    nodes = id_depth(h) - c;
+    s_id[threadIdx.x] = h;
+#pragma unroll
+    for (int j = 0; j < 4; j++) s_v[j][threadIdx.x] = verts[4 * p + j];
+  }
+  int end = nodes;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(end, o, 64);
+    if (lane >= o) end += y;
+  }
+  s_end[threadIdx.x] = end;
+  s_bits[threadIdx.x] = 0;
+  const int total = __shfl(end, 63, 64);
+  __syncthreads();
+  for (int t = lane; t < total; t += 64) {
+    int l = 0;  // the leaf of node t: the first whose nodes end beyond t
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+      if (s_end[w0 + l + o - 1] <= t) l += o;
+    const int up = t - (l ? s_end[w0 + l - 1] : 0);
+    uint64_t a = s_id[w0 + l];
+    uint64_t v[4] = {s_v[0][w0 + l], s_v[1][w0 + l], s_v[2][w0 + l], s_v[3][w0 + l]};
+    const int d = id_depth(a) - up;
+    for (int k = 0; k < up; k++, a >>= 1) parent_vertices(v, tag_of(id_depth(a) - 1), a & 1);
+    if (want(P, cc, wp, v, a)) atomicOr(&s_bits[w0 + l], 1ull << d);
+  }
+  __syncthreads();
+  if (p < n) {
+    keep[p] = c >= 0 ? (~0ull >> (63 - c)) : 0ull;
+    bits[p] = s_bits[threadIdx.x];
+  }
 }
 
 // Transform M -> (M & k) | b of the chain scan; compose(x, y) applies x, then y.
@@ -1920,8 +1970,8 @@ static int seed_from_grid(const tet_grid* prev, const Pyramid& P, const CamCrit&
   if (!keep.ensure(n * 8) || !bits.ensure(n * 8) || !first.ensure(n * 4) || !pos.ensure(n * 4) ||
       !bagg.ensure(nb * sizeof(ChainT)))
     return fail(TET_ERR_OUT_OF_MEMORY, "leb_update: seed");
-  hipLaunchKernelGGL(k_seed_chain, dim3(nblocks(n, 256)), dim3(256), 0, st, n, (const uint64_t*)prev->ids, P, cc, wp,
-                     keep.as<uint64_t>(), bits.as<uint64_t>());
+  hipLaunchKernelGGL(k_seed_chain, dim3(nblocks(n, kSeedBlock)), dim3(kSeedBlock), 0, st, n, (const uint64_t*)prev->ids,
+                     (const uint64_t*)prev->verts, P, cc, wp, keep.as<uint64_t>(), bits.as<uint64_t>());
   hipLaunchKernelGGL(k_chain_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, st, keep.as<uint64_t>(),
                      bits.as<uint64_t>(), n, bagg.as<ChainT>());
   hipLaunchKernelGGL(k_chain_blocks, dim3(1), dim3(kScanThreads), 0, st, bagg.as<ChainT>(), nb);
