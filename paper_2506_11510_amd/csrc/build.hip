@@ -268,13 +268,6 @@ __device__ inline bool vset_add(uint64_t* tab, uint64_t mask, uint64_t key) {
   }
 }
 
-// One atomic per wave for a running count (called by every lane of the
-// wave, in uniform control flow).
-__device__ inline void count_new(bool added, uint32_t* count) {
-  unsigned long long m = __ballot(added);
-  if (m && __lane_id() == (int)__builtin_ctzll(m)) atomicAdd(count, (uint32_t)__popcll(m));
-}
-
 // The vertex count lives in kCountSlots words that the host sums: a block
 // adds its total once, to the slot of its index, so the atomics of a large
 // pass spread over kCountSlots addresses (on one address they serialise).
@@ -404,16 +397,27 @@ __device__ inline bool cells_touched(const uint32_t* __restrict__ cells, const u
 }
 
 // Tail rounds: every leaf that splits is listed.  The list positions come
-// from the running split count (one atomic per wave); list0 is its value at
-// the start of the round.
-__device__ inline void list_split(bool split, uint32_t i, uint32_t* splitc, uint32_t list0, uint32_t* slist) {
-  const unsigned long long m = __ballot(split);
-  if (!m) return;
-  const int lane = __lane_id(), leader = (int)__builtin_ctzll(m);
+// from the running split count; list0 is its value at the start of the round.
+// The additions to that one word take turns (16 ns each), so a wave lists its
+// leaves, N per lane, with one, and a block of k_want with one.
+template <int N>
+__device__ inline void list_splits(const bool (&split)[N], const uint32_t (&i)[N], uint32_t* splitc, uint32_t list0,
+                                   uint32_t* slist) {
+  uint32_t n = 0, at[N];
+  const int lane = __lane_id();
+#pragma unroll
+  for (int k = 0; k < N; k++) {
+    const unsigned long long m = __ballot(split[k]);
+    at[k] = n + (uint32_t)__popcll(m & (lane ? (~0ull >> (64 - lane)) : 0ull));
+    n += (uint32_t)__popcll(m);
+  }
+  if (!n) return;
   uint32_t base = 0;
-  if (lane == leader) base = atomicAdd(splitc, (uint32_t)__popcll(m));
-  base = __shfl(base, leader, 64);
-  if (split) slist[base - list0 + (uint32_t)__popcll(m & (lane ? (~0ull >> (64 - lane)) : 0ull))] = i;
+  if (lane == 0) base = atomicAdd(splitc, n);
+  base = __shfl(base, 0, 64) - list0;
+#pragma unroll
+  for (int k = 0; k < N; k++)
+    if (split[k]) slist[base + at[k]] = i[k];
 }
 
 // Tail rounds keep, per chunk of 256 leaves of the main part, a box of
@@ -468,10 +472,8 @@ __global__ void k_chunk_boxes(int64_t n, int64_t c0, int64_t c1, const uint64_t*
 __global__ void k_mark(int64_t n, int smax, const uint64_t* __restrict__ ids, const uint64_t* __restrict__ verts,
                        uint8_t* __restrict__ flags,
                        uint32_t* __restrict__ cnt, const uint64_t* __restrict__ vset, uint64_t vmask,
-                       const uint64_t* __restrict__ nset, uint64_t nmask, const uint32_t* __restrict__ cells,
-                       uint32_t* splitc, uint32_t list0, uint32_t* __restrict__ slist) {
+                       const uint64_t* __restrict__ nset, uint64_t nmask, const uint32_t* __restrict__ cells) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  bool split = false;
   if (i < n) {
     const uint8_t fl = flags[i];
     if (fl & 1) {  // new leaves (flag 0) are k_want's
@@ -479,13 +481,13 @@ __global__ void k_mark(int64_t n, int smax, const uint64_t* __restrict__ ids, co
       // checked leaves: the last pass's new vertices (after a dense pass,
       // nset is the whole vertex set and there is no cell map)
       const uint32_t edges = edges_upto(id_depth(ids[i]), smax);
+      bool split;
       if (fl & 2) split = (!cells || cells_touched(cells, v)) && hanging(v, nset, nmask, edges);
       else split = hanging(v, vset, vmask, edges);
       if (!split && !(fl & 2)) flags[i] = fl | 2;
-      if (!slist) cnt[i] = split ? 2u : 1u;
+      cnt[i] = split ? 2u : 1u;
     }
   }
-  if (slist) list_split(split, (uint32_t)i, splitc, list0, slist);
 }
 
 // Tail rounds: k_mark over chunks, one per wave.  A chunk of the main part
@@ -532,6 +534,7 @@ __global__ __launch_bounds__(256) void k_mark_tail(int64_t n, int64_t nmain, con
   uint8_t fl[kPer];
   uint64_t v[kPer][4];
   bool split[kPer];
+  uint32_t leaf[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; k++) {
     const int64_t i = c * kChunk + 64 * k + lane;
@@ -550,16 +553,21 @@ __global__ __launch_bounds__(256) void k_mark_tail(int64_t n, int64_t nmain, con
       split[k] = hanging(v[k], checked ? nset : vset, checked ? nmask : vmask);
       if (!split[k] && !checked) flags[i] = fl[k] | 2;
     }
-    list_split(split[k], (uint32_t)i, splitc, list0, slist);
+    leaf[k] = (uint32_t)i;
   }
+  list_splits(split, leaf, splitc, list0, slist);
 }
 
 // The leaves made by the last split pass (a dense list, so the want
 // predicate's FP64 work runs on full waves): wanted, or forced.
-__global__ void k_want(int64_t m, int smax, const uint32_t* __restrict__ work, const uint64_t* __restrict__ ids,
-                       const uint64_t* __restrict__ verts, uint8_t* __restrict__ flags, uint32_t* __restrict__ cnt,
-                       Pyramid P, CamCrit cc, WantParams wp, const uint64_t* __restrict__ vset, uint64_t vmask,
-                       uint32_t* splitc, uint32_t list0, uint32_t* __restrict__ slist) {
+constexpr int kWantBlock = 256;
+
+__global__ __launch_bounds__(kWantBlock) void k_want(int64_t m, int smax, const uint32_t* __restrict__ work,
+                                                     const uint64_t* __restrict__ ids,
+                                                     const uint64_t* __restrict__ verts, uint8_t* __restrict__ flags,
+                                                     uint32_t* __restrict__ cnt, Pyramid P, CamCrit cc, WantParams wp,
+                                                     const uint64_t* __restrict__ vset, uint64_t vmask,
+                                                     uint32_t* splitc, uint32_t list0, uint32_t* __restrict__ slist) {
   int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool split = false;
   uint32_t i = 0;
@@ -578,7 +586,20 @@ __global__ void k_want(int64_t m, int smax, const uint32_t* __restrict__ work, c
     flags[i] = nf;
     if (!slist) cnt[i] = split ? 2u : 1u;
   }
-  if (slist) list_split(split, i, splitc, list0, slist);
+  if (!slist) return;
+  __shared__ uint32_t s_n[kWantBlock / 64], s_base;
+  const int lane = __lane_id(), w = threadIdx.x >> 6;
+  const unsigned long long mk = __ballot(split);
+  if (lane == 0) s_n[w] = (uint32_t)__popcll(mk);
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+  for (int k = 0; k < kWantBlock / 64; k++) {
+    if (k < w) before += s_n[k];
+    all += s_n[k];
+  }
+  if (threadIdx.x == 0 && all) s_base = atomicAdd(splitc, all) - list0;
+  __syncthreads();
+  if (split) slist[s_base + before + (uint32_t)__popcll(mk & (lane ? (~0ull >> (64 - lane)) : 0ull))] = i;
 }
 
 // Maubach children of the tet (id, v): the first child replaces vertex x_k
@@ -1094,12 +1115,15 @@ __global__ void k_refresh_medium(int64_t n, const uint64_t* __restrict__ verts, 
   if (rec32) rec32[t].w[3] = __float_as_uint(sigma);
 }
 
-// Leaves whose chain bits differ from the previous grid's (one atomic per wave).
-__global__ void k_chain_diff(int64_t n, const uint64_t* __restrict__ a, const uint64_t* __restrict__ b,
-                             uint32_t* count) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool d = p < n && a[p] != b[p];
-  count_new(d, count);
+// *diff: set when a leaf's chain bits differ from the previous grid's, by a
+// plain store per block (a count, one addition per wave: 98 us on 2.5 M
+// leaves; now 11).
+constexpr int kDiffBlock = 1024;
+
+__global__ __launch_bounds__(kDiffBlock) void k_chain_diff(int64_t n, const uint64_t* __restrict__ a,
+                                                           const uint64_t* __restrict__ b, uint32_t* diff) {
+  const int64_t p = (int64_t)blockIdx.x * kDiffBlock + threadIdx.x;
+  if (__syncthreads_or(p < n && a[p] != b[p]) && threadIdx.x == 0) *diff = 1u;
 }
 
 // Adds x over the block to slots[blockIdx.x % kCountSlots] (every thread of
@@ -1979,7 +2003,7 @@ static int seed_from_grid(const tet_grid* prev, const Pyramid& P, const CamCrit&
                      bits.as<uint64_t>(), n, bagg.as<ChainT>());
   if (allow_same) {
     TV_HIP(hipMemsetAsync(d_count, 0, 4, st));
-    hipLaunchKernelGGL(k_chain_diff, dim3(nblocks(n, 256)), dim3(256), 0, st, n,
+    hipLaunchKernelGGL(k_chain_diff, dim3(nblocks(n, kDiffBlock)), dim3(kDiffBlock), 0, st, n,
                        (const uint64_t*)bits.as<uint64_t>(), (const uint64_t*)prev->chain, d_count);
     uint32_t diff = 0;
     TV_HIP(fetch(&diff, d_count, 4, st));
@@ -2236,15 +2260,14 @@ static int build_common(const tet_density* dens, const tet_sparse_density* sp, c
                          A.verts.as<uint64_t>(),
                          A.flags.as<uint8_t>(), cntb.as<uint32_t>(), vs.as<uint64_t>(), vcap - 1,
                          dense_last ? vs.as<uint64_t>() : ns.as<uint64_t>(), dense_last ? vcap - 1 : nscap - 1,
-                         dense_last ? nullptr : (const uint32_t*)(ns.as<uint64_t>() + nscap), d_splitc, splitc,
-                         nullptr);
+                         dense_last ? nullptr : (const uint32_t*)(ns.as<uint64_t>() + nscap));
     else
       hipLaunchKernelGGL(k_mark_tail, dim3(nblocks(cur, 256 / 64 * kChunk)), dim3(256), 0, st, cur, nmain,
                          A.verts.as<uint64_t>(), A.flags.as<uint8_t>(), vs.as<uint64_t>(), vcap - 1,
                          ns.as<uint64_t>(), nscap - 1, (const uint32_t*)(ns.as<uint64_t>() + nscap),
                          cbox.as<uint32_t>(), d_splitc, splitc, cntb.as<uint32_t>(), (int)(cur > nmain));
     if (nwork > 0)  // a seed from a previous grid may list no wanted leaf
-      hipLaunchKernelGGL(k_want, dim3(nblocks(nwork, 256)), dim3(256), 0, st, nwork, smax, wk.as<uint32_t>(),
+      hipLaunchKernelGGL(k_want, dim3(nblocks(nwork, kWantBlock)), dim3(kWantBlock), 0, st, nwork, smax, wk.as<uint32_t>(),
                        A.ids.as<uint64_t>(), A.verts.as<uint64_t>(), A.flags.as<uint8_t>(), cntb.as<uint32_t>(), P,
                        cc, wp, vs.as<uint64_t>(), vcap - 1, d_splitc, splitc, nmain < 0 ? nullptr : cntb.as<uint32_t>());
     if (nmain < 0 && scan_u32(cntb.as<uint32_t>(), cur, offb.as<uint32_t>(), bsum, d_total, st))
