@@ -110,10 +110,11 @@ typedef struct {
   int32_t samples_per_item;   /* >= 0; checked only: every sample is scheduled by itself */
   int32_t block_size;         /* threads per block: 64, 128, 192 or 256 (0 = default) */
   int32_t blocks_per_cu;      /* persistent blocks per compute unit (0 = default) */
-  int32_t waves_per_simd;     /* occupancy target of the tracing kernel: 4, 5, 6 or 8 waves (0 = default 5; on
-                                 tet grids 6 and 8 mean 5, what the on-chip memory of a CU allows) */
+  int32_t waves_per_simd;     /* occupancy target of the tracing kernel: 4, 5, 6 or 8 waves (0 = default: 4 on
+                                 tet grids without a radiance cache, else 5; on tet grids 6 and 8 mean 5,
+                                 what the on-chip memory of a CU allows) */
   int32_t record_layout;      /* tet records walked: 32 (compact), 48, or 0 = compact when the grid has them */
-  int32_t batch_items;        /* paths a wave takes at a time, at most (0 = default 64; batches always take 64) */
+  int32_t batch_items;        /* paths a wave takes at a time, at most (0 = default 32; batches always take 64) */
   int32_t event_wait;         /* lanes of a wave that wait for an event before events run (0 = default: 48;
                                  32 with channels or a density model) */
   const tet_nrc* nrc;         /* radiance cache: NULL = plain estimator; else paths stop at the cache's

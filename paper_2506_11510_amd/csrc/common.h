@@ -205,7 +205,7 @@ __device__ inline void shape_bisector(const int32_t v[4][3], uint32_t w, int32_t
 // three bisections are three compares and a few selects (about 30
 // instructions; from the vertices, with the bisection normals from the shape
 // table, they were 150 in 32-bit integers, 240 in FP64): the links of 6.2 M
-// tets 602 -> 345 us, the camera rays of a 16.8 M sample frame 9.93 -> 9.46 ms.
+// tets 602 -> 345 us, the camera rays of a 33.6 M sample frame 9.93 -> 9.46 ms.
 // A point on a plane takes the first child (ABOVE: the second).  Exact when
 // f +- f and s - f are.
 template <bool ABOVE, class T>

@@ -799,8 +799,9 @@ constexpr uint32_t kFirstBlock = 64;
 // that neighbouring rays share an XCD's L2 and every XCD gets its share of
 // the image's dense part (one contiguous eighth each left half the XCDs idle
 // at the end: 17.4 ms on the 33 M rays of the 1024^2 x 32 cloud frame,
-// 2.8 of 5 resident waves per SIMD on average).  A block lists its colliding samples with one atomic on its
-// band's count.  MODEL: the grid carries a density model.
+// 2.8 of 5 resident waves per SIMD on average; dealt, 9.5 ms, at the VALU
+// issue rate).  A block lists its colliding samples with one atomic on its
+// list's count.  MODEL: the grid carries a density model.
 template <class Med, bool BATCH, bool MODEL>
 __global__ __launch_bounds__(kFirstBlock) void k_first(RenderArgs A, Med med) {
   __shared__ float s_tab[Med::kRows * kFirstBlock];
@@ -1141,9 +1142,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(W, 8))) voi
         mode = M_FETCH;
       }
       // idle lanes take consecutive listed paths from the wave's batch; a
-      // wave refills its batch with one atomic, first from this block's band
+      // wave refills its batch with one atomic, first from this block's list
       // (blocks are dealt to the 8 XCDs round-robin, so an XCD's L2 serves
-      // one band of the image), then from the others.
+      // the chunks of the image that its own blocks listed), then from the others.
       // A wave with training paths takes no others until they end: they are
       // the longest, and among image paths each of their events would wait
       // for the wave's others (cache frame of 16 K training paths: 2.34 ms
@@ -1736,9 +1737,18 @@ static void launch_first(const RenderArgs& P, const Med& med, bool model, hipStr
 // frame 3.71 -> 3.83 ms).
 static int default_event_wait(const ExtArgs& X) { return X.model || X.ch_t || X.ch_a || X.ch_g ? 32 : 48; }
 
+// Listed paths a wave takes at a time: few enough that the last ones spread
+// over the waves (with 4 waves per SIMD, against 64 paths at 5: emissive frame
+// 3.53 -> 3.35 ms, linear-model frame 9.25 -> 9.04, cloud frame 36.1 -> 35.6,
+// plume frame 28.2 -> 28.0; thumbnail and cached frame the same).
+constexpr uint32_t kTakeItems = 32;
+
 // The tracing kernel at an occupancy target.  Five waves per SIMD fit beside
 // the segments' tables (27 KB of LDS per 256 lanes), so on tet grids 6 and 8
-// mean 5.
+// mean 5.  The default is 4 without a cache (fewer paths in flight leave each
+// more of the L2: emissive frame 3.41 ms against 3.35, both with 32 paths
+// at a time; the cloud frame 35.7 against 35.6), 5 with one (its kernels have
+// that form only).
 template <class Med, int NRC>
 static void launch_render(const RenderArgs& P, const Med& med, bool ext, int waves, dim3 grid, dim3 block,
                           hipStream_t st) {
@@ -1749,7 +1759,7 @@ static void launch_render(const RenderArgs& P, const Med& med, bool ext, int wav
       case 8: hipLaunchKernelGGL((k_render<Med, 8, NRC>), grid, block, 0, st, P, med); break;
       default: hipLaunchKernelGGL((k_render<Med, 5, NRC>), grid, block, 0, st, P, med); break;
     }
-  } else if (NRC == 0 && waves == 4) {
+  } else if (NRC == 0 && (waves == 4 || waves == 0)) {
     if (ext) hipLaunchKernelGGL((k_render<Med, 4, 0, false, true>), grid, block, 0, st, P, med);
     else hipLaunchKernelGGL((k_render<Med, 4, 0>), grid, block, 0, st, P, med);
   } else {
@@ -2009,7 +2019,7 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   A.seed = seed;
   A.slots = (uint32_t)slots;
   A.tiles_x = tiles_x;
-  A.batch = o.batch_items ? (uint32_t)o.batch_items : 64u;
+  A.batch = o.batch_items ? (uint32_t)o.batch_items : kTakeItems;
   A.event_wait = o.event_wait ? o.event_wait : default_event_wait(A.ex);
   if (nrc) {
     A.nrc = nrc;
