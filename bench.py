@@ -100,10 +100,13 @@ def _counter_rows(d):
 
 def tracing_part(kernel_name: str):
     """Which part of a plain render's tracing a dispatch is: "main" (the
-    persistent tracing kernel), "light" (the queued light rays: their keys,
-    sort and walks), or None."""
+    persistent tracing kernel), "camera" (the camera segments and the sums of
+    the samples), "light" (the queued light rays: their keys, sort and walks),
+    or None."""
     if "k_render<" in kernel_name and ", 0, false, false>" in kernel_name:
         return "main"
+    if "k_first<" in kernel_name or "k_resolve" in kernel_name:
+        return "camera"
     if "k_light" in kernel_name or "rocprim" in kernel_name:
         return "light"
     return None
@@ -113,9 +116,9 @@ def summarize_pmc(fetch_dir, write_dir, out_path, command, workload="the 1024^2 
     """Traffic of the tracing from FETCH_SIZE / WRITE_SIZE runs (KiB per
     dispatch), each scaled by the factor that maps the same counter on a
     plain 1 GiB device copy to its true size; per launch of the tracing
-    kernel, with the dispatches of its queued light rays."""
+    kernel, with the dispatches of its camera segments and queued light rays."""
     def per_kernel(rows, counter):
-        parts, copies = {"main": [], "light": []}, []
+        parts, copies = {"main": [], "camera": [], "light": []}, []
         for r in rows:
             if r["Counter_Name"] != counter:
                 continue
@@ -129,8 +132,8 @@ def summarize_pmc(fetch_dir, write_dir, out_path, command, workload="the 1024^2 
     fp, fc = per_kernel(_counter_rows(fetch_dir), "FETCH_SIZE")
     wp, wc = per_kernel(_counter_rows(write_dir), "WRITE_SIZE")
     ft, wt = fp["main"], wp["main"]
-    f_kib = (sum(ft) + sum(fp["light"])) / len(ft)
-    w_kib = (sum(wt) + sum(wp["light"])) / len(wt)
+    f_kib = (sum(ft) + sum(fp["camera"]) + sum(fp["light"])) / len(ft)
+    w_kib = (sum(wt) + sum(wp["camera"]) + sum(wp["light"])) / len(wt)
     f_fac = (COPY_BYTES / 1024) / max(fc)
     w_fac = (COPY_BYTES / 1024) / max(wc)
     traffic = (f_kib * f_fac + w_kib * w_fac) * 1024
@@ -145,6 +148,8 @@ def summarize_pmc(fetch_dir, write_dir, out_path, command, workload="the 1024^2 
         f.write(f"dispatches = {len(ft)}\n")
         f.write(f"fetch_kib_per_launch = {f_kib:.1f}\n")
         f.write(f"write_kib_per_launch = {w_kib:.1f}\n")
+        f.write(f"fetch_kib_per_launch_camera_segments = {sum(fp['camera']) / len(ft):.1f}\n")
+        f.write(f"write_kib_per_launch_camera_segments = {sum(wp['camera']) / len(wt):.1f}\n")
         f.write(f"fetch_kib_per_launch_light_rays = {sum(fp['light']) / len(ft):.1f}\n")
         f.write(f"write_kib_per_launch_light_rays = {sum(wp['light']) / len(wt):.1f}\n")
         f.write(f"copy_fetch_kib = {max(fc):.1f}\n")
@@ -157,7 +162,7 @@ def summarize_pmc(fetch_dir, write_dir, out_path, command, workload="the 1024^2 
 
 def summarize_counters(pmc_dir, out_path, command, steps_per_launch: float = 0.0):
     """Every counter collected on the tracing, per launch of the tracing
-    kernel (with the dispatches of its queued light rays), with the L2 hit
+    kernel (with its camera segments and queued light rays), with the L2 hit
     rate and VALU instructions per tet step."""
     rows = [r for r in _counter_rows(pmc_dir) if tracing_part(r["Kernel_Name"])]
     acc, cnt = {}, {}
@@ -168,7 +173,7 @@ def summarize_counters(pmc_dir, out_path, command, steps_per_launch: float = 0.0
             cnt[k] = cnt.get(k, 0) + 1
     avg = {k: acc[k] / cnt[k] for k in acc if cnt.get(k)}
     with open(out_path, "w") as f:
-        f.write("# rocprofv3 counters of the tracing (k_render<TetMedium32> and the walks of its queued light rays),"
+        f.write("# rocprofv3 counters of the tracing (k_render<TetMedium32>, its camera segments and queued light rays),"
                 " per launch\n")
         f.write(f"# command: {command}\n")
         f.write(f"source_hash = {kernel_source_hash()}\n")
@@ -202,14 +207,17 @@ def summarize_trace(trace_dir, out_path, command):
                     f"{float(r['Percentage']):>6.2f}  {r['Name'][:110]}\n")
         main = [r for r in rows if tracing_part(r["Name"]) == "main"]
         light = [r for r in rows if tracing_part(r["Name"]) == "light"]
+        camera = [r for r in rows if tracing_part(r["Name"]) == "camera"]
         if main:
             launches = sum(int(r["Calls"]) for r in main)
             t_main = sum(float(r["TotalDurationNs"]) for r in main) / 1e6
             t_light = sum(float(r["TotalDurationNs"]) for r in light) / 1e6
+            t_camera = sum(float(r["TotalDurationNs"]) for r in camera) / 1e6
             f.write(f"tracing_launches = {launches}\n")
             f.write(f"tracing_kernel_ms_per_launch = {t_main / launches:.3f}\n")
+            f.write(f"camera_segments_ms_per_launch = {t_camera / launches:.3f}  (with the sums of the samples)\n")
             f.write(f"queued_light_rays_ms_per_launch = {t_light / launches:.3f}  (keys, sort, walks)\n")
-            f.write(f"tracing_ms_per_launch = {(t_main + t_light) / launches:.3f}\n")
+            f.write(f"tracing_ms_per_launch = {(t_main + t_camera + t_light) / launches:.3f}\n")
     print(open(out_path).read())
 
 
@@ -833,7 +841,7 @@ def main():
                                                       "light_rays_queued")},
         "image_mean": float(img.mean()),
         "roofline": {"bound": "hbm",
-                     "kernel": "k_render<TetMedium%s, %d, 0, false, false> + queued light rays (k_light, sort)"
+                     "kernel": "k_render<TetMedium%s, %d, 0, false, false> + camera segments (k_first) + queued light rays (k_light, sort)"
                                % ("32" if sc["render"]["record_layout"] == 32 else "", sc["render"]["waves_per_simd"]),
                      "achieved": round(achieved, 2),
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
