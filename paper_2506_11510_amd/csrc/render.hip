@@ -51,6 +51,7 @@
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "nrc.h"
+#include "plan.h"
 
 namespace tv {
 
@@ -786,8 +787,6 @@ __device__ inline void add_stats(const RenderArgs& A, const uint32_t (&v)[N]) {
     if (__lane_id() == 0 && x) atomicAdd(stat_slot(A) + q, x);
   }
 }
-
-constexpr uint32_t kFirstBlock = 64;
 
 // Camera rays and their walk to the first real collision, one thread per
 // entry record in record order: the samples of a pixel are neighbouring
@@ -1625,7 +1624,7 @@ static int cu_count() {
 constexpr int64_t kMaxEntriesPerPass = 1ll << 25;  // 1 GiB of entry records
 // tet_render_noalloc's fixed scratch: counters, 2^21 entry records, their lists
 constexpr int64_t kNoAllocEntries = 1ll << 21;
-constexpr int64_t kListSlack = 8 * 16384;  // the lists' last, incomplete round of chunks
+constexpr int64_t kListSlack = 8 * kMostChunk;  // the lists' last, incomplete round of chunks
 constexpr size_t kNoAllocBytes = (size_t)kNoAllocEntries * sizeof(RayEntry) + (size_t)(kNoAllocEntries + kListSlack) * 4 + kHeadBytes + 256;
 // Sort buffers of the deferred light rays (keys and positions, both ways)
 // and the sort's own scratch.
@@ -1707,15 +1706,12 @@ static void size_light_queue(RenderArgs& A, int64_t samples, const tet_render_op
   A.lq_chunks = (uint32_t)(std::min<int64_t>(1ll << 26, samples * 4) / A.lq_chunk + waves);
 }
 
-// The eight lists of ne entry records: blocks per chunk (at least 16 chunks
-// per list where there are blocks enough) and records per list.
-constexpr uint32_t kMostChunk = 16384;  // entry records
-static uint32_t chunk_blocks_of(uint64_t ne) {
-  return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(kMostChunk, ne / 128) / kFirstBlock);
-}
-static uint32_t band_size_of(uint64_t ne) {
-  const uint64_t g = chunk_blocks_of(ne) * (uint64_t)kFirstBlock, chunks = (ne + g - 1) / g;
-  return (uint32_t)((chunks + 7) / 8 * g);
+// The lists of a call, laid out once for its largest pass; returns their words.
+static size_t set_lists(RenderArgs& A, uint64_t most) {
+  const ListPlan p = list_plan(most);
+  A.chunk_blocks = p.chunk_blocks;
+  A.band_size = p.band_size;
+  return (size_t)p.words();
 }
 
 template <class Med, bool BATCH>
@@ -1831,8 +1827,7 @@ static int run_passes(const Med& med, RenderArgs& A, const tet_render_opts& o, i
     RenderArgs P = A;
     P.train_items = (NRC == 1 && done == 0) ? A.train_items : 0u;  // training paths ride the first pass
     const uint64_t ne = (uint64_t)A.slots * (uint64_t)P.pass_spp;
-    P.band_size = band_size_of(ne);
-    P.chunk_blocks = chunk_blocks_of(ne);
+    if (ne > 8 * (uint64_t)P.band_size) return fail(TET_ERR_INTERNAL, "render: lists too small for the pass");
     hipLaunchKernelGGL(k_zero_u32, dim3((kPassWords + 255) / 256), dim3(256), 0, st, A.head, kPassWords);
     if (timed) TV_HIP(hipEventRecord(t0, st));
     P.train_blocks = (P.train_items + kFirstBlock - 1) / kFirstBlock;
@@ -2038,7 +2033,7 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
   // paths) and their lists, image when the output is on the host,
   // training-path records
   size_t img_bytes = (size_t)npix * 3 * sizeof(float);
-  size_t n_ent = (size_t)slots * (size_t)pass_cap, list0 = 8 * (size_t)band_size_of(n_ent);
+  size_t n_ent = (size_t)slots * (size_t)pass_cap, list0 = set_lists(A, n_ent);
   size_t ent_bytes = kHeadBytes + (n_ent + (size_t)n_train) * sizeof(RayEntry) + (list0 + (size_t)n_train) * 4;
   ent_bytes = (ent_bytes + 255) & ~(size_t)255;
   size_t vrec_bytes = (size_t)n_train * (size_t)kv * 48, pl_bytes = (size_t)n_train * 16;
@@ -2206,7 +2201,8 @@ int trace_training_paths(const tet_grid* g, const tet_camera* cam, const tet_med
   A.rec_vertices = kv;
   A.vrec = vrec;
   A.path_l = path_l;
-  char* sc = (char*)dev_alloc(kHeadBytes + (size_t)n_paths * sizeof(RayEntry) + 32 * (size_t)band_size_of((uint64_t)n_paths));
+  const size_t list_words = set_lists(A, (uint64_t)n_paths);
+  char* sc = (char*)dev_alloc(kHeadBytes + (size_t)n_paths * sizeof(RayEntry) + 4 * list_words);
   if (!sc) return fail(TET_ERR_OUT_OF_MEMORY, "training paths: scratch");
   struct Free {
     void* p;
@@ -2411,7 +2407,7 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
   RenderArgs& A = B->A;
   memset(&A, 0, sizeof(A));
   const size_t ent_bytes =
-      (kHeadBytes + (size_t)entry * sizeof(RayEntry) + 32 * (size_t)band_size_of(entry) + 255) & ~(size_t)255;
+      (kHeadBytes + (size_t)entry * sizeof(RayEntry) + 4 * set_lists(A, entry) + 255) & ~(size_t)255;
   size_t lq_bytes = 0;
   size_t sort_bytes = 0;
   if (o.max_steps_per_path >= 0x7FFFFFFF) {  // light rays queued
@@ -2446,8 +2442,6 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
   A.head = (uint32_t*)B->scratch;
   A.entries = (RayEntry*)(B->scratch + kHeadBytes);
   A.list = (uint32_t*)(A.entries + entry);
-  A.band_size = band_size_of(entry);
-  A.chunk_blocks = chunk_blocks_of(entry);
   A.scenes = B->table;
   A.nscenes = n;
   A.total_entries = entry;

@@ -1,0 +1,58 @@
+"""The sizes of a render's scratch (csrc/plan.h, compiled for the CPU): what a
+pass can write has room in what the call reserved."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2506_11510_amd", "csrc")
+SHIM = """
+#include "plan.h"
+extern "C" void list_plan(uint64_t most, uint64_t* out) {
+  const tv::ListPlan p = tv::list_plan(most);
+  out[0] = p.chunk_blocks; out[1] = p.band_size; out[2] = p.words();
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "plan.so"), str(d / "shim.cpp")],
+                   check=True)
+    return ctypes.CDLL(str(d / "plan.so"))
+
+
+def lists(plan, most):
+    out = (ctypes.c_uint64 * 3)()
+    plan.list_plan(ctypes.c_uint64(most), out)
+    return list(out)
+
+
+def dealt(ne, chunk_blocks):
+    """The most entry records of ne that one of the eight lists can be dealt:
+    a chunk of every round of eight, the last one perhaps cut."""
+    g = 64 * chunk_blocks
+    full, rest = divmod(ne, 8 * g)
+    return full * g + min(rest, g)
+
+
+@pytest.mark.parametrize("w,h", [(8, 8), (24, 20), (64, 64), (96, 80), (192, 120), (144, 120), (192, 192), (251, 187),
+                                 (640, 360), (1024, 1024)])
+def test_every_pass_fits_the_lists_of_the_largest(plan, w, h):
+    """A call of several passes reserves its lists for the largest; the last
+    pass may have any smaller number of samples."""
+    slots = ((w + 7) // 8) * ((h + 7) // 8) * 64
+    caps = {c for c in (1, 2, 3, 5, 18, 30, 48, 95, 127, 272, 511, (1 << 21) // slots, (1 << 25) // slots) if 1 <= c * slots <= 1 << 25}
+    for cap in caps:
+        chunk, band, words = lists(plan, slots * cap)
+        assert words == 8 * band and words >= slots * cap and words <= slots * cap + 8 * 64 * chunk
+        for last in {1, cap, cap - 1, cap // 2, *range(max(1, cap - 40), cap + 1)} - {0}:
+            assert dealt(slots * last, chunk) <= band, (cap, last)
+
+
+def test_a_shorter_passes_own_plan_does_not_fit(plan):
+    """Why a call has one plan: 64 x 64 pixels, passes of 272 and 271 samples."""
+    assert lists(plan, 4096 * 271)[2] > lists(plan, 4096 * 272)[2]
