@@ -102,10 +102,14 @@ typedef struct {
                                  (and above) the light rays of a render's passes are queued and walked
                                  together after each pass (a light walk then runs on its own, bounded by
                                  the tet count; the estimate is the same unless a path takes more than
-                                 2^31 - 1 steps), in single renders sorted by where they start (column of
-                                 the grid along the light, then depth); their terms reach the pixels apart
-                                 from the rest of their samples (FP32 sums in another order).  A full
-                                 queue leaves the rest to the tracing lanes */
+                                 2^31 - 1 steps), on large grids sorted by where they start (column of the
+                                 grid along the light, then depth).  With analytic light on a tet grid of
+                                 constant extinctions, tet_render adds their terms to the pixels one by
+                                 one, in an order that differs from call to call (FP32 rounding); a smaller
+                                 value, or any other kind of render, sums them with their samples in path
+                                 order, so that equal calls give equal bits (radiance caches apart, whose
+                                 queries are added to the pixels in any order).  A full queue leaves the
+                                 rest to the tracing lanes */
   int32_t sample_offset;      /* render samples [offset, offset + spp) */
   int32_t samples_per_item;   /* >= 0; checked only: every sample is scheduled by itself */
   int32_t block_size;         /* threads per block: 64, 128, 192 or 256 (0 = default) */
@@ -246,7 +250,9 @@ int tet_render(const tet_grid* grid, const tet_camera* camera, const tet_medium*
  * device; one sample of every pixel must fit the array (2^21 entry
  * records: images of up to 2^21 pixels once rounded up to 8 x 8 tiles, e.g.
  * 2048 x 1024), else TET_ERR_CAPACITY; a frame takes as many passes as its
- * samples and a light ray for each need (about 2^20 samples a pass).  Every call on a device shares its array: calls that
+ * samples and 1.25 light rays for each need (about 2^20 samples a pass; images
+ * of more than about 10^6 pixels queue no light rays, and take 2^21 samples a
+ * pass).  Every call on a device shares its array: calls that
  * overlap on one device race (serialise them, e.g. on one stream). */
 int tet_render_noalloc(const tet_grid* grid, const tet_camera* camera, const tet_medium* medium,
                        const tet_light* light, int32_t spp, uint64_t seed, const tet_render_opts* opts,

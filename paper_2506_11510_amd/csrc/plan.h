@@ -30,4 +30,35 @@ inline ListPlan list_plan(uint64_t most) {
   return p;
 }
 
+// Samples per pixel of a pass whose records, lists and light-ray queue share
+// `bytes` of fixed scratch (at most `most`), with room for 1.25 light rays per
+// sample; 0: not even one sample per pixel, the light rays are better walked by
+// their own lanes.  A queue that fills leaves its paths to a second launch, as
+// long as a whole one of lanes that walk their own (4.2 M samples of a 256^3
+// cloud at 1.1 light rays each: room for 1.15 per sample 24.7 ms, no queue
+// 16.9 ms; 3.7 M samples, room for 1.47: 9.2 ms, no queue 13.2 ms).
+inline int64_t queued_pass(int64_t slots, int64_t most, int64_t bytes) {
+  const int64_t fit = bytes / (slots * (32 + 4 + 40));
+  return std::min(most, fit);
+}
+
+// The light-ray queue of a pass of `samples` samples traced by at most `waves`
+// waves, which take it a chunk at a time: at most 4 rays per sample and 2^26 in
+// all, and one more chunk for each wave (its last is partly used).
+struct QueuePlan {
+  uint32_t chunk, chunks;  // records per chunk, chunks
+  int64_t waves;
+  uint32_t records() const { return chunk * chunks; }
+  // Rays that find room however the waves share the chunks.
+  int64_t sure() const { return ((int64_t)chunks - waves) * chunk; }
+};
+
+inline QueuePlan queue_plan(int64_t samples, int64_t waves) {
+  QueuePlan p;
+  p.chunk = samples < (1 << 20) ? 64u : 256u;
+  p.waves = std::min<int64_t>(waves, (samples + 63) / 64 + 4);
+  p.chunks = (uint32_t)(std::min<int64_t>(1ll << 26, samples * 4) / p.chunk + p.waves);
+  return p;
+}
+
 }  // namespace tv

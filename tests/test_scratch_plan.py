@@ -13,6 +13,7 @@ extern "C" void list_plan(uint64_t most, uint64_t* out) {
   const tv::ListPlan p = tv::list_plan(most);
   out[0] = p.chunk_blocks; out[1] = p.band_size; out[2] = p.words();
 }
+extern "C" int64_t queued_pass(int64_t slots, int64_t most, int64_t bytes) { return tv::queued_pass(slots, most, bytes); }
 """
 
 
@@ -56,3 +57,14 @@ def test_every_pass_fits_the_lists_of_the_largest(plan, w, h):
 def test_a_shorter_passes_own_plan_does_not_fit(plan):
     """Why a call has one plan: 64 x 64 pixels, passes of 272 and 271 samples."""
     assert lists(plan, 4096 * 271)[2] > lists(plan, 4096 * 272)[2]
+
+
+@pytest.mark.parametrize("slots", [64, 4096, 23040, 49152, 921600, 1 << 20, 1 << 21])
+def test_passes_that_queue_light_rays_in_fixed_scratch(plan, slots):
+    """Entry records, lists and 1.25 light rays a sample fit beside each other."""
+    plan.queued_pass.restype = ctypes.c_int64
+    room = (1 << 21) * 36  # (the array has the lists' slack and the counters besides)
+    for most in (1, 2, 30, (1 << 21) // slots):
+        n = slots * plan.queued_pass(ctypes.c_int64(slots), ctypes.c_int64(most), ctypes.c_int64(room))
+        assert n <= slots * most and 32 * n + 4 * n + 40 * n <= room
+        assert n == slots * most or 76 * (n + slots) > room
