@@ -109,7 +109,7 @@ typedef struct {
                                  value, or any other kind of render, sums them with their samples in path
                                  order, so that equal calls give equal bits (radiance caches apart, whose
                                  queries are added to the pixels in any order).  A full queue leaves the
-                                 rest to the tracing lanes */
+                                 rest to the tracing lanes, no memory for a queue all of them */
   int32_t sample_offset;      /* render samples [offset, offset + spp) */
   int32_t samples_per_item;   /* >= 0; checked only: every sample is scheduled by itself */
   int32_t block_size;         /* threads per block: 64, 128, 192 or 256 (0 = default) */

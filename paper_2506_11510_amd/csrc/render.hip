@@ -2213,12 +2213,12 @@ static int render_common(int kind, const tet_grid* g, const tet_density* dens, c
     }
     const size_t term_bytes = train_terms ? (size_t)n_train * (size_t)o.max_bounces * 32 : 0;
     const size_t qb = (size_t)cap * sizeof(LightRec) + sort_bytes + term_bytes;
-    char* q = (char*)dev_alloc(qb);
-    if (!q) return fail(TET_ERR_OUT_OF_MEMORY, "render: light-ray queue");
-    frq_.p = q;
-    set_queue(A, qp, q);
-    if (train_terms) A.terms = (float4*)(q + qb - term_bytes);
-    if (sort_bytes) (void)ls.place(cap, q + (size_t)cap * sizeof(LightRec));
+    if (char* q = (char*)dev_alloc(qb)) {  // (no room: the lanes walk their own light rays)
+      frq_.p = q;
+      set_queue(A, qp, q);
+      if (train_terms) A.terms = (float4*)(q + qb - term_bytes);
+      if (sort_bytes) (void)ls.place(cap, q + (size_t)cap * sizeof(LightRec));
+    }
   }
 
   if (nrc) {
@@ -2348,9 +2348,10 @@ int trace_training_paths(const tet_grid* g, const tet_camera* cam, const tet_med
     const QueuePlan qp = light_queue(n_paths, o);
     const size_t qb = (size_t)qp.records() * sizeof(LightRec);
     fq_.p = dev_alloc(qb + (size_t)n_paths * (size_t)o.max_bounces * 32);
-    if (!fq_.p) return fail(TET_ERR_OUT_OF_MEMORY, "training paths: light-ray queue");
-    set_queue(A, qp, fq_.p);
-    A.terms = (float4*)((char*)fq_.p + qb);
+    if (fq_.p) {  // (no room: the lanes walk their own light rays)
+      set_queue(A, qp, fq_.p);
+      A.terms = (float4*)((char*)fq_.p + qb);
+    }
   }
   float ms = 0.0f, ms_trace = 0.0f, ms_cache = 0.0f;
   int rc;
@@ -2554,6 +2555,11 @@ static int batch_setup(BatchState* B, int32_t n, const tet_grid* const* grids, c
     }
   }
   B->scratch = (char*)dev_alloc(ent_bytes + lq_bytes + sort_bytes);
+  if (!B->scratch && lq_bytes) {  // no room for the queue: the lanes walk their own light rays
+    qp.chunks = 0;
+    sort_bytes = 0;
+    B->scratch = (char*)dev_alloc(ent_bytes);
+  }
   if (hipHostMalloc((void**)&B->pinned, sizeof(SceneDesc) * (size_t)n, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     B->pinned = nullptr;
