@@ -2669,6 +2669,7 @@ static int batch_run(BatchState* B, const uint64_t* seeds, hipStream_t st, tet_r
     stats->truncated = hs.sum(4);
     stats->ms = ms;
     stats->trace_ms = ms;
+    stats->light_rays_queued = hs.sum(6);
   }
   return TET_OK;
 }

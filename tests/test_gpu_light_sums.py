@@ -127,6 +127,18 @@ def test_batch_bits(tv, opts, scale):
         assert st["tet_steps"] == got[OWN, 0][1]["tet_steps"]
 
 
+@pytest.mark.parametrize("guard", [QUEUED, OWN])
+def test_batch_counts_its_queued_light_rays(tv, guard):
+    """Every light ray of two small scenes is queued, or none (a ray per collision)."""
+    say(f"case batch statistics, guard {guard}")
+    g = grid_of(tv)
+    r = dict(max_bounces=4, max_steps_per_path=guard)
+    cams = [dict(SC["camera"], width=w, height=h) for w, h in ((33, 17), (64, 48))]
+    _, st = tv.render_batch([g, g], cams, [SC["medium"]] * 2, [SC["light"]] * 2, [3, 2], [7, 8], r)
+    assert st["real_collisions"] > 0
+    assert st["light_rays_queued"] == (st["real_collisions"] if guard == QUEUED else 0)
+
+
 def test_cached_image_bits(tv):
     """With a radiance cache and one sample a pixel (one query at most, so its
     atomic addition has one order): image paths with tracked light rays."""
