@@ -44,20 +44,23 @@ inline int64_t queued_pass(int64_t slots, int64_t most, int64_t bytes) {
 
 // The light-ray queue of a pass of `samples` samples traced by at most `waves`
 // waves, which take it a chunk at a time: at most 4 rays per sample and 2^26 in
-// all, and one more chunk for each wave (its last is partly used).
+// all, and one more chunk for each wave (its last is partly used); no more
+// than 2^27 records however many waves are asked for.
+constexpr int64_t kMostQueued = 1ll << 27;
+
 struct QueuePlan {
   uint32_t chunk, chunks;  // records per chunk, chunks
   int64_t waves;
   uint32_t records() const { return chunk * chunks; }
   // Rays that find room however the waves share the chunks.
-  int64_t sure() const { return ((int64_t)chunks - waves) * chunk; }
+  int64_t sure() const { return std::max<int64_t>(0, ((int64_t)chunks - waves) * chunk); }
 };
 
 inline QueuePlan queue_plan(int64_t samples, int64_t waves) {
   QueuePlan p;
   p.chunk = samples < (1 << 20) ? 64u : 256u;
   p.waves = std::min<int64_t>(waves, (samples + 63) / 64 + 4);
-  p.chunks = (uint32_t)(std::min<int64_t>(1ll << 26, samples * 4) / p.chunk + p.waves);
+  p.chunks = (uint32_t)std::min<int64_t>(kMostQueued / p.chunk, std::min<int64_t>(1ll << 26, samples * 4) / p.chunk + p.waves);
   return p;
 }
 

@@ -13,6 +13,10 @@ extern "C" void list_plan(uint64_t most, uint64_t* out) {
   const tv::ListPlan p = tv::list_plan(most);
   out[0] = p.chunk_blocks; out[1] = p.band_size; out[2] = p.words();
 }
+extern "C" void queue_plan(int64_t samples, int64_t waves, int64_t* out) {
+  const tv::QueuePlan p = tv::queue_plan(samples, waves);
+  out[0] = p.chunk; out[1] = p.chunks; out[2] = p.records(); out[3] = p.sure();
+}
 extern "C" int64_t queued_pass(int64_t slots, int64_t most, int64_t bytes) { return tv::queued_pass(slots, most, bytes); }
 """
 
@@ -68,3 +72,16 @@ def test_passes_that_queue_light_rays_in_fixed_scratch(plan, slots):
         n = slots * plan.queued_pass(ctypes.c_int64(slots), ctypes.c_int64(most), ctypes.c_int64(room))
         assert n <= slots * most and 32 * n + 4 * n + 40 * n <= room
         assert n == slots * most or 76 * (n + slots) > room
+
+
+@pytest.mark.parametrize("samples", [1, 64, 4096, (1 << 20) - 1, 1 << 20, 1 << 25, 1 << 30, (1 << 32) - 1])
+@pytest.mark.parametrize("blocks_per_cu", [1, 8, 64, 1 << 12, 1 << 16, (1 << 31) - 1])
+def test_queue_of_any_number_of_waves(plan, samples, blocks_per_cu):
+    """Records are counted in 32 bits, also for launches of very many blocks;
+    the usual 8 blocks per CU leave room for 4 light rays a sample."""
+    out = (ctypes.c_int64 * 4)()
+    plan.queue_plan(ctypes.c_int64(samples), ctypes.c_int64(256 * blocks_per_cu * 4), out)
+    chunk, chunks, records, sure = out
+    assert records == chunk * chunks <= 1 << 27 and chunks > 0 and 0 <= sure <= records
+    if blocks_per_cu <= 8:
+        assert sure > min(1 << 26, 4 * samples) - chunk
