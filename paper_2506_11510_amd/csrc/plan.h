@@ -30,6 +30,19 @@ inline ListPlan list_plan(uint64_t most) {
   return p;
 }
 
+// Grid of k_first for its image blocks and the blocks of training paths before
+// them: HIP launches fewer than 2^32 threads along x, so the largest batches
+// (the lists' last round reaches past 2^32 records) take two rows.
+struct FirstGrid {
+  uint32_t x, y;
+};
+
+inline FirstGrid first_grid(const ListPlan& p, uint32_t train_blocks) {
+  const uint64_t blocks = train_blocks + p.words() / kFirstBlock, most = (0xFFFFFFFFull / kFirstBlock) & ~7ull;
+  const uint64_t rows = (blocks + most - 1) / most;
+  return {(uint32_t)(((blocks + rows - 1) / rows + 7) / 8 * 8), (uint32_t)rows};
+}
+
 // Samples per pixel of a pass whose records, lists and light-ray queue share
 // `bytes` of fixed scratch (at most `most`), with room for 1.25 light rays per
 // sample; 0: not even one sample per pixel, the light rays are better walked by

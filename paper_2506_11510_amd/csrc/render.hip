@@ -804,8 +804,9 @@ __global__ __launch_bounds__(kFirstBlock) void k_first(RenderArgs A, Med med) {
   float* tab = s_tab + (threadIdx.x >> 6) * (Med::kRows * kTabRow) + (threadIdx.x & 63u);
   const int lane = __lane_id();
   // the first blocks trace the training paths that go with an image
-  const bool with = !BATCH && blockIdx.x < A.train_blocks, train = with || (!BATCH && A.train);
-  const uint32_t blk = blockIdx.x - (with ? 0u : A.train_blocks);
+  const uint32_t block = BATCH ? blockIdx.y * gridDim.x + blockIdx.x : blockIdx.x;  // (first_grid: rows in batches only)
+  const bool with = !BATCH && block < A.train_blocks, train = with || (!BATCH && A.train);
+  const uint32_t blk = block - (with ? 0u : A.train_blocks);
   const uint32_t band = with ? 0u : blk & 7u, j = blk >> 3, g = A.chunk_blocks, round = j / g;
   const uint32_t turn = (band + ((round * 0x9E3779B9u) >> 29)) & 7u;  // (a row of the image may hold a multiple of 8 chunks)
   const uint64_t e = (with ? (uint64_t)blk : ((uint64_t)round * 8u + turn) * g + j % g) * kFirstBlock + threadIdx.x;
@@ -1818,14 +1819,15 @@ static size_t set_lists(RenderArgs& A, uint64_t most) {
 
 template <class Med, bool BATCH>
 static void launch_first(const RenderArgs& P, const Med& med, bool model, hipStream_t st) {
-  const unsigned grid = P.train_blocks + 8u * (P.band_size / kFirstBlock);
+  const FirstGrid f = first_grid({P.chunk_blocks, P.band_size}, P.train_blocks);
+  const dim3 grid(f.x, f.y);
   if constexpr (!std::is_same<Med, VoxelMedium>::value) {
     if (model) {
-      hipLaunchKernelGGL((k_first<Med, BATCH, true>), dim3(grid), dim3(kFirstBlock), 0, st, P, med);
+      hipLaunchKernelGGL((k_first<Med, BATCH, true>), grid, dim3(kFirstBlock), 0, st, P, med);
       return;
     }
   }
-  hipLaunchKernelGGL((k_first<Med, BATCH, false>), dim3(grid), dim3(kFirstBlock), 0, st, P, med);
+  hipLaunchKernelGGL((k_first<Med, BATCH, false>), grid, dim3(kFirstBlock), 0, st, P, med);
 }
 
 // Lanes that wait for an event before the wave handles events: an event

@@ -17,6 +17,10 @@ extern "C" void queue_plan(int64_t samples, int64_t waves, int64_t* out) {
   const tv::QueuePlan p = tv::queue_plan(samples, waves);
   out[0] = p.chunk; out[1] = p.chunks; out[2] = p.records(); out[3] = p.sure();
 }
+extern "C" void first_grid(uint64_t most, uint32_t train_blocks, uint32_t* out) {
+  const tv::FirstGrid g = tv::first_grid(tv::list_plan(most), train_blocks);
+  out[0] = g.x; out[1] = g.y;
+}
 extern "C" int64_t queued_pass(int64_t slots, int64_t most, int64_t bytes) { return tv::queued_pass(slots, most, bytes); }
 """
 
@@ -85,3 +89,18 @@ def test_queue_of_any_number_of_waves(plan, samples, blocks_per_cu):
     assert records == chunk * chunks <= 1 << 27 and chunks > 0 and 0 <= sure <= records
     if blocks_per_cu <= 8:
         assert sure > min(1 << 26, 4 * samples) - chunk
+
+
+@pytest.mark.parametrize("most", [64, 4096, 1 << 25, 1 << 31, (1 << 32) - 300000, (1 << 32) - 65536, (1 << 32) - 64])
+@pytest.mark.parametrize("train_blocks", [0, 8, 4096])
+def test_grid_of_the_first_kernel(plan, most, train_blocks):
+    """Fewer than 2^32 threads along x, every list's blocks, rows in batches
+    (which have no training paths) alone, blocks dealt by eights."""
+    out = (ctypes.c_uint32 * 2)()
+    plan.first_grid(ctypes.c_uint64(most), ctypes.c_uint32(train_blocks), out)
+    x, y = out
+    blocks = train_blocks + lists(plan, most)[2] // 64
+    assert x * 64 < 1 << 32 and x % 8 == 0 and blocks <= x * y < blocks + 8 * y + 8
+    assert y == 1 if most <= 1 << 31 else y <= 2
+    if y == 1:
+        assert x == blocks
