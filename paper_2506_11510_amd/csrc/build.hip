@@ -1395,20 +1395,6 @@ __global__ void k_key_index(int64_t n, const uint64_t* __restrict__ keys, int kb
   kidx[b] = (uint32_t)lo;
 }
 
-// Root Kuhn tets: vertex 1 = S e_p0, vertex 2 = S (e_p0 + e_p1), over the
-// axis orders (0,1,2), (0,2,1), (1,0,2), (1,2,0), (2,0,1), (2,1,0).
-__device__ inline void root_verts(int r, int32_t v[4][3]) {
-  const int p0[6] = {0, 0, 1, 1, 2, 2}, p1[6] = {1, 2, 0, 2, 0, 1};
-#pragma unroll
-  for (int j = 0; j < 4; j++)
-#pragma unroll
-    for (int a = 0; a < 3; a++) v[j][a] = j == 3 ? kLatS : 0;
-  for (int a = 0; a < 3; a++) {
-    if (a == p0[r]) { v[1][a] = kLatS; v[2][a] = kLatS; }
-    if (a == p1[r]) v[2][a] = kLatS;
-  }
-}
-
 __device__ inline int isgn(int32_t x) { return (x > 0) - (x < 0); }
 
 // Outward unit normal of the face (a, b, c) opposite vertex o and its
