@@ -2372,6 +2372,16 @@ int trace_training_paths(const tet_grid* g, const tet_camera* cam, const tet_med
   return TET_OK;
 }
 
+void launch_defaults(const tet_grid* g, tet_render_opts* o) {
+  ExtArgs x;
+  set_ext(x, g, *o);
+  if (!o->waves_per_simd) o->waves_per_simd = o->nrc ? 5 : 4;
+  if (!o->event_wait) o->event_wait = default_event_wait(x);
+  if (!o->batch_items) o->batch_items = (int32_t)kTakeItems;
+  if (!o->block_size) o->block_size = 256;
+  if (!o->record_layout) o->record_layout = g->rec32 ? 32 : 48;
+}
+
 int render_grid(const tet_grid* g, const tet_camera* cam, const tet_medium* m, const tet_light* l, int32_t spp,
                 uint64_t seed, const tet_render_opts* o, float* out, int32_t on_device, hipStream_t st,
                 tet_render_stats* stats) {

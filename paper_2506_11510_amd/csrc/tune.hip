@@ -26,6 +26,8 @@ namespace tv {
 
 int render_grid(const tet_grid*, const tet_camera*, const tet_medium*, const tet_light*, int32_t, uint64_t,
                 const tet_render_opts*, float*, int32_t, hipStream_t, tet_render_stats*);
+// Launch options left at 0 set to what a render of this grid takes for them.
+void launch_defaults(const tet_grid* g, tet_render_opts* o);
 
 namespace {
 
@@ -161,11 +163,7 @@ int autotune(const tet_grid* g, const tet_camera* cam, const tet_medium* med, co
   std::vector<std::vector<int32_t>> cand = {{4, 5}, {16, 32, 48}, {32, 64, 128}, {128, 256}, {48}};
   if (g->rec32) cand[4] = {32, 48};
   tet_render_opts cur = base;
-  if (!cur.waves_per_simd) cur.waves_per_simd = 4;
-  if (!cur.event_wait) cur.event_wait = 48;
-  if (!cur.batch_items) cur.batch_items = 32;
-  if (!cur.block_size) cur.block_size = 256;
-  if (!cur.record_layout) cur.record_layout = g->rec32 ? 32 : 48;
+  launch_defaults(g, &cur);
   const size_t img = (size_t)cam->width * cam->height * 3 * sizeof(float);
   float* out = (float*)dev_alloc(img);
   if (!out) return fail(TET_ERR_OUT_OF_MEMORY, "tet_autotune: image");
