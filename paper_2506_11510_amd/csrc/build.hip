@@ -303,21 +303,6 @@ __global__ void k_vset_seed(const uint64_t* __restrict__ verts, int64_t n, uint6
   const bool added = i < 4 * n && vset_add(tab, mask, verts[i]);
   block_count(added, count);
 }
-// Edges (bits in hanging's order) of a tet of depth d whose midpoints can be
-// vertices while no tet deeper than smax has been split.  Every tet around an
-// edge bisects it at the same depth, if it gets there: by tag (columns 3, 2,
-// 1) and edge, the tet's depth plus
-//   x0x1 2 1 0   x0x2 1 0 2   x0x3 0 2 1   x1x2 2 1 2   x1x3 1 2 1   x2x3 2 2 3
-// The rounds split breadth first, so most new leaves are the deepest yet and
-// have no edge to look up: the lookups are random reads of a table past the
-// caches.  Passes over a 6.2 M tet build: want 900 -> 730 us, mark 430 -> 330.
-__host__ __device__ inline uint32_t edges_upto(int d, int smax) {
-  const int s = smax - d, t = tag_of(d);
-  if (s < 0) return 0u;
-  const uint32_t lv = t == 3 ? 0x3F3F1604u : (t == 2 ? 0x3F3F0B02u : 0x3F1F1501u);  // a byte per s
-  return (lv >> (8 * (s < 3 ? s : 3))) & 0xFFu;
-}
-
 
 // ---------------------------------------------------------------- rounds
 // Leaf flags: bit 0 = the want predicate was false (it depends on the tet

@@ -6,6 +6,7 @@
 
 #include <string>
 
+#include "rules.h"
 #include "tetvol.h"
 
 namespace tv {
@@ -148,7 +149,6 @@ __host__ __device__ inline int id_depth(uint64_t id) {
   return 60 - __builtin_clzll(id);
 #endif
 }
-__host__ __device__ inline int tag_of(int depth) { return 3 - depth % 3; }
 
 // Depth-first keys are id << (60 - depth), so a key's top 4 bits are its
 // root (8..13).  Bucket b of the key index holds the keys whose bits
@@ -190,42 +190,6 @@ __device__ inline void shape_bisector(const int32_t v[4][3], uint32_t w, int32_t
     z[i] = (v[0][i] + v[K][i]) >> 1;
     u[i] = (int32_t)((w >> (2 * i)) & 3u) - 1;
   }
-}
-
-// Heap id at depth dmax (<= 60) of the tet holding a point, from the Kuhn root
-// h whose axis order sorts it: f0 >= f1 >= f2 >= 0 are its coordinates along
-// the root's axes, s the cube's edge.  Every tet whose depth is a multiple of
-// three is a Kuhn tet again: from its vertex x_0 along three signed axes in
-// turn, all by one edge length s.  In its own coordinates (0 <= f2 <= f1 <=
-// f0 <= s) the three bisections below it are the planes f0 + f2 = s; f0 + f1
-// = s or, beyond the first, f1 + f2 = s; and a coordinate = s / 2; each
-// second child lies above its plane.  The Kuhn tet of edge s / 2 reached
-// starts at the vertex with as many of the bits 0 as its own x_0 has axes
-// left at 0, so its coordinates are the f's folded at s (f or s - f).  So
-// three bisections are three compares and a few selects (about 30
-// instructions; from the vertices, with the bisection normals from the shape
-// table, they were 150 in 32-bit integers, 240 in FP64): the links of 6.2 M
-// tets 602 -> 345 us, the camera rays of a 33.6 M sample frame 9.93 -> 9.46 ms.
-// A point on a plane takes the first child (ABOVE: the second).  Exact when
-// f +- f and s - f are.
-template <bool ABOVE, class T>
-__host__ __device__ inline uint64_t fold_path(T f0, T f1, T f2, T s, int dmax, uint64_t h) {
-  for (int d = 0; d < dmax; d += 3) {
-    const T a = f0 + f2;
-    const bool b1 = ABOVE ? a >= s : a > s;
-    const T b = (b1 ? f2 : f0) + f1;
-    const bool b2 = ABOVE ? b >= s : b > s;
-    const T p = b1 ? (b2 ? f2 : f1) : (b2 ? f1 : f0), r = s - p;
-    const bool b3 = ABOVE ? p >= r : p > r;
-    const T r0 = s - f0;
-    const T g1 = b1 ? (b2 ? s - f1 : f2) : (b2 ? r0 : f1);
-    f2 = b1 ? r0 : f2;
-    f1 = g1;
-    f0 = b3 ? r : p;
-    s = s / 2;
-    h = 8 * h + (b1 ? 4 : 0) + (b2 ? 2 : 0) + (b3 ? 1 : 0);
-  }
-  return h >> ((3 - dmax % 3) % 3);
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).

@@ -335,25 +335,11 @@ __device__ inline int64_t locate_point(const uint64_t* __restrict__ keys, const 
 // reciprocal is the correctly rounded one; NaN where dir_N . d = 0 (such a
 // face is never crossed), and 0 for all 9 when a dot product is too small
 // for exit_face's bounds (|dir_N . d| < 2^-40, or NaN, or d = 0), which makes every
-// step of the segment take its general path.
+// step of the segment take its general path (seg_dirs).
 // Each wave has a table of its own, entry k of lane i at k * kTabRow + i: a
 // lane's reads stay in its own bank whichever entry it reads.
 constexpr int kTabRow = 64;
 constexpr int kTabDot = 9, kTabDen = 18, kTabRows = 27;
-
-struct SegDirs {
-  float r[9], d[9];
-};
-
-__host__ __device__ inline void seg_dirs(float x, float y, float z, SegDirs& s) {
-  const float d[9] = {x, y, z, x + y, x - y, x + z, x - z, y + z, y - z};
-  bool tiny = x == 0.0f && y == 0.0f && z == 0.0f;
-  for (int N = 0; N < 9; N++) tiny = tiny || (d[N] != 0.0f && !(d[N] <= -0x1p-40f || d[N] >= 0x1p-40f));
-  for (int N = 0; N < 9; N++) {
-    s.d[N] = d[N];
-    s.r[N] = tiny ? 0.0f : (d[N] == 0.0f ? __builtin_nanf("") : 1.0f / d[N]);
-  }
-}
 
 // The origin's 9 entries, at tab[N * kTabRow].
 __device__ inline void set_origin(float* tab, float3 o, float oscale) {
