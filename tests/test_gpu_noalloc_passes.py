@@ -27,3 +27,32 @@ def test_short_last_pass_of_a_dense_view(w, h, spp):
         tv.render_noalloc(g, cam, dict(albedo=0.9, g=0.3), sc["light"], spp, 5, render=r, out=out)
         torch.cuda.synchronize()
         assert_image_parity(out.cpu().numpy(), ref.cpu().numpy(), f"noalloc {w}x{h}")
+
+
+@pytest.mark.parametrize("w,h,spp", [(64, 48, 9), (251, 187, 30)])  # one pass, two
+def test_captured_render_replays(w, h, spp):
+    """A captured call, replayed with the program's own work between the
+    replays, gives the eager call's bits every time (dense: the queue fills
+    and paths wait for the second launch)."""
+    import torch
+    assert torch.cuda.is_available(), "no GPU"
+    import paper_2506_11510_amd as tv
+    print(f"case noalloc captured, {w}x{h} spp {spp}", flush=True)
+    sc = synthetic.scene("tiny")
+    cam = dict(sc["camera"], pos=[0.5, 0.5, 0.2], width=w, height=h)
+    g = tv.leb_build(torch.from_numpy(sc["density_fn"]()).cuda(), 64, cam, build=dict(sc["build"], density_scale=30.0))
+    out = torch.full((h, w, 3), -1.0, device="cuda")
+    call = lambda: tv.render_noalloc(g, cam, dict(albedo=1.0, g=0.3), sc["light"], spp, 5, render=dict(max_bounces=24), out=out)
+    call()
+    torch.cuda.synchronize()
+    want = out.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for rep in range(4):
+        out.fill_(-1.0)
+        tv.render(g, cam, sc["medium"], sc["light"], 2, rep)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), rep
