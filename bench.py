@@ -37,7 +37,7 @@ TRAFFIC_GLOB = os.path.join(ROOT, "profiles", "render_cloud1024*_traffic.txt")
 PLUME_TRAFFIC_GLOB = os.path.join(ROOT, "profiles", "render_plume1024*_traffic.txt")
 LAUNCH_KEYS = ("waves_per_simd", "event_wait", "batch_items", "block_size", "record_layout", "samples_per_item")
 COPY_BYTES = 1 << 30  # plain device copy used to calibrate the traffic counters
-KERNEL_SOURCES = ["paper_2506_11510_amd/csrc/render.hip", "paper_2506_11510_amd/csrc/common.h"]
+KERNEL_SOURCES = ["paper_2506_11510_amd/csrc/" + f for f in ("render.hip", "common.h", "rules.h", "plan.h")]
 
 
 def kernel_source_hash() -> str:

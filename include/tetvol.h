@@ -143,7 +143,7 @@ typedef struct {
   int64_t escapes;
   int64_t truncated;       /* paths stopped by max_steps_per_path */
   double ms;               /* device time of the whole render call */
-  double trace_ms;         /* device time of the persistent tracing kernel(s) alone */
+  double trace_ms;         /* device time of the tracing: camera segments, paths, light rays, sample sums */
   double cache_ms;         /* device time of the radiance-cache queries (0 without a cache) */
   int64_t cache_queries;   /* paths that stopped at the cache */
   int64_t cache_records;   /* training records of the frame (nrc_train) */
@@ -259,9 +259,11 @@ int tet_render_noalloc(const tet_grid* grid, const tet_camera* camera, const tet
                        float* out_rgb, void* hip_stream);
 
 /* Renders n scenes (each its own grid, camera, medium, light, spp and
- * seed) with one persistent launch of the same path tracer: the scenes'
- * samples are work items of one queue, so small images fill the GPU
- * together instead of one after another.  out_rgb[i]: device pointer,
+ * seed) with one sequence of launches of the same path tracer: the scenes'
+ * samples are listed together and so are their light rays, so small images
+ * fill the GPU together instead of one after another.  The call waits for the
+ * number of queued light rays before it walks them, and for the end.
+ * out_rgb[i]: device pointer,
  * width_i*height_i*3 FP32, as tet_render would write it.  Per-scene
  * images equal tet_render's up to FP32 summation order.  opts (nullable):
  * max_bounces, transmittance, max_steps_per_path, sample_offset,
@@ -277,8 +279,11 @@ int tet_render_batch(int32_t n, const tet_grid* const* grids, const tet_camera* 
                      tet_render_stats* stats);
 
 /* The same batch as a reusable frame: tet_batch_create fixes the scenes,
- * allocates the scratch memory and captures the frame's kernels in a HIP
- * graph; tet_batch_render replays it with new seeds (n values).  The grids
+ * allocates the scratch memory and captures the tracing of camera and
+ * scattered segments in a HIP graph (all of the frame where no light rays are
+ * queued); tet_batch_render replays it with new seeds (n values), then sorts
+ * and walks the light rays and sums the samples by launches of its own (the
+ * sort needs the rays' number on the host).  The grids
  * and output buffers must outlive the handle, and the grids' channels and
  * density models must not be replaced meanwhile (the frame reads them
  * where they were at creation). */

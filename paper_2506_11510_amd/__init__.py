@@ -348,7 +348,7 @@ class _SceneArrays:
 
 
 def render_batch(grids, cameras, media, lights, spp, seeds, render: dict | None = None, outs=None):
-    """Renders a batch of scenes with one persistent launch; returns (list
+    """Renders a batch of scenes with one sequence of launches; returns (list
     of (H, W, 3) CUDA tensors, batch stats)."""
     a = _SceneArrays(grids, cameras, media, lights, spp, outs)
     sd = (ctypes.c_uint64 * a.n)(*[int(x) for x in seeds])

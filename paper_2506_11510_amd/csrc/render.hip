@@ -757,7 +757,11 @@ __global__ __launch_bounds__(256) void k_resolve_batch(RenderArgs A, uint64_t to
 enum { M_TRACK = 0, M_SHADOW = 1, M_COLLIDE = 2, M_SCATTER = 3, M_ESCAPE = 4, M_FINISH = 5, M_FETCH = 6,
        M_DONE = 7, M_PARK = 8 };
 
-constexpr uint32_t kMinTake = 16;  // paths a wave takes at least
+// Paths a wave takes at least.  At 1, 4, 8, 16 and 64 the frame with a learning
+// cache took 2.06, 2.11, 2.15, 2.20 and 2.25 ms (its training paths spread over
+// more waves); thumbnail, preview, emissive, cloud and batch frames stay within
+// the spread of their runs.
+constexpr uint32_t kMinTake = 16;
 // Adds each lane's v[0..n) to the block's statistics slot: wave reductions,
 // one atomic per wave and counter.
 template <int N>
@@ -1738,13 +1742,18 @@ struct LightSort {
 
 // Whether light rays are sorted before they are walked: below, the records of
 // the grids stay in an XCD's 4 MB of L2 however the rays are ordered, or
-// there are too few rays to pay for the sort and the wait for their count
-// (the 3,072-tet thumbnail, 59 K rays: frame 418 us sorted, 327 us as queued;
-// twelve scenes of 3 K to 1.5 M tets: walks 2.99 ms as queued, 1.56 ms
-// sorted, the sort 0.24 ms).
+// there are too few rays to pay for the sort and the wait for their count.
+// Frames in us, as queued / sorted, by tets and samples:
+//             33 K         131 K         524 K         4.2 M
+//   25 K    401 /  467   479 /  581    794 /  951    2922 / 2931
+//   197 K   637 /  696   697 /  786   1172 / 1225    4918 / 4045
+//   786 K   938 /  991  1031 / 1077   1803 / 1623    8792 / 5602
+//   3.1 M  1384 / 1446  1611 / 1580   3014 / 2501   15893 / 8961
+// (a uniform grid's; its light rays are short, an adaptive one's cross more).
 static bool sort_pays(int64_t cells, int64_t samples) { return cells >= (1 << 17) && samples >= (1 << 17); }
 
-// The walks of a pass's queued light rays, taken as queued (no host
+// The walks of a pass's queued light rays: the n in `order`, or (order NULL)
+// as they were queued, their number read on the device (no host
 // synchronisation: capturable).
 template <class Med, bool BATCH>
 static void launch_light(const RenderArgs& P, const Med& med, bool model, const uint32_t* order, uint32_t n,
@@ -1830,11 +1839,11 @@ static int default_event_wait(const ExtArgs& X) { return X.model || X.ch_t || X.
 constexpr uint32_t kTakeItems = 32;
 
 // The tracing kernel at an occupancy target.  Five waves per SIMD fit beside
-// the segments' tables (27 KB of LDS per 256 lanes), so on tet grids 6 and 8
-// mean 5.  The default is 4 without a cache (fewer paths in flight leave each
-// more of the L2: emissive frame 3.41 ms against 3.35, both with 32 paths
-// at a time; the cloud frame 35.7 against 35.6), 5 with one (its kernels have
-// that form only).
+// the segments' tables (28 KB of LDS per 256 lanes), so on tet grids 6 and 8
+// mean 5.  The default is 4 without a cache: medians of ten renders in turn at
+// 4 and 5, emissive frame 3.25 and 3.33 ms, linear model 8.82 and 8.99 (their
+// kernels spill at 5), cloud 35.33 and 35.33, plume 27.93 and 27.83, thumbnail
+// 0.235 and 0.236.  With a cache it is 5 (its kernels have that form only).
 template <class Med, int NRC>
 static void launch_render(const RenderArgs& P, const Med& med, bool ext, int waves, dim3 grid, dim3 block,
                           hipStream_t st) {
