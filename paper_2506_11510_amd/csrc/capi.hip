@@ -123,7 +123,8 @@ void dev_free(void* p) {
 // and goes back only when its copy is known to be complete.
 namespace {
 constexpr size_t kHostBlock = 8192, kHostBlocks = 16;
-std::vector<void*> g_host;  // idle blocks, at most kHostBlocks (under g_mu)
+void* g_host[kHostBlocks];  // idle blocks (under g_mu); an array, whose use cannot throw through the C entry
+size_t g_hosts = 0;
 }  // namespace
 
 hipError_t fetch(void* dst, const void* src, size_t bytes, hipStream_t st) {
@@ -131,10 +132,7 @@ hipError_t fetch(void* dst, const void* src, size_t bytes, hipStream_t st) {
   if (bytes <= kHostBlock) {
     {
       std::lock_guard<std::mutex> lk(g_mu);
-      if (!g_host.empty()) {
-        p = g_host.back();
-        g_host.pop_back();
-      }
+      if (g_hosts) p = g_host[--g_hosts];
     }
     if (!p && hipHostMalloc(&p, kHostBlock, hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
@@ -147,8 +145,8 @@ hipError_t fetch(void* dst, const void* src, size_t bytes, hipStream_t st) {
   if (e == hipSuccess) {
     memcpy(dst, p, bytes);
     std::lock_guard<std::mutex> lk(g_mu);
-    if (g_host.size() < kHostBlocks) {
-      g_host.push_back(p);
+    if (g_hosts < kHostBlocks) {
+      g_host[g_hosts++] = p;
       p = nullptr;
     }
   }
@@ -506,8 +504,7 @@ void tet_release_cache(void) {
       it = fl->erase(it);
     }
   }
-  for (void* p : g_host) (void)hipHostFree(p);
-  g_host.clear();
+  while (g_hosts) (void)hipHostFree(g_host[--g_hosts]);
   (void)hipSetDevice(cur);
 }
 
